@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -298,46 +299,6 @@ __global__ __launch_bounds__(NT) void k_mg_split(const MgGeo G, const double *__
   dst[row * G.n[0] + (i & 1) * hrow + (i >> 1)] = src[mg_off(G, i, j, k)];
 }
 
-// The coarsest-level solver: `sweeps` red-black sweeps by one workgroup,
-// the colours separated by workgroup barriers instead of launches.  With
-// lds != 0 the level's arrays (u, f and the given a, a2) are first copied
-// into dynamic LDS, relaxed there and u copied back: the sweeps are then
-// bound by LDS rather than global-memory latency.
-__global__ __launch_bounds__(NT) void k_mg_coarse(const MgGeo G, double *u, const double *__restrict__ f,
-                                                  const double *__restrict__ a, const double *__restrict__ a2,
-                                                  int sweeps, int lds) {
-  extern __shared__ double sm[];
-  double *uu = u;
-  const double *ff = f, *aa = a, *aa2 = a2;
-  if (lds) {
-    double *p = sm;
-    for (long e = threadIdx.x; e < G.nt; e += NT) p[e] = u[e];
-    uu = p;
-    p += G.nt;
-    for (long e = threadIdx.x; e < G.nt; e += NT) p[e] = f[e];
-    ff = p;
-    p += G.nt;
-    if (a) {
-      for (long e = threadIdx.x; e < G.nt; e += NT) p[e] = a[e];
-      aa = p;
-      p += G.nt;
-    }
-    if (a2) {
-      for (long e = threadIdx.x; e < G.nt; e += NT) p[e] = a2[e];
-      aa2 = p;
-    }
-    __syncthreads();
-  }
-  const long nc = (long)((G.n[0] + 1) >> 1) * G.n[1] * G.n[2];
-  for (int s = 0; s < sweeps; s++)
-    for (int c = 0; c < 2; c++) {
-      for (long t = threadIdx.x; t < nc; t += NT) mg_smooth_one(G, uu, ff, aa, aa2, c, t);
-      __syncthreads();
-    }
-  if (lds)
-    for (long e = threadIdx.x; e < G.nt; e += NT) u[e] = uu[e];
-}
-
 // ---- Line relaxation --------------------------------------------------------
 // An alternative to the paper's point smoother for the anisotropic cells on
 // which section 2.7 notes that point smoothers converge slowly (spherical
@@ -586,13 +547,10 @@ __global__ __launch_bounds__(NT) void k_mg_restrict(const MgGeo F, const MgGeo C
   coarse[mg_off(C, i, j, k)] = s / w;
 }
 
-// FAS coarse problem: f_c = L_c(u_c) + r_c, and uo_c = u_c (u_c's ghosts set).
-__global__ __launch_bounds__(NT) void k_mg_fas_rhs(const MgGeo C, const double *__restrict__ u,
-                                                   const double *__restrict__ a, const double *__restrict__ a2,
-                                                   const double *__restrict__ r, double *__restrict__ f,
-                                                   double *__restrict__ uo) {
-  const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t >= mg_cells(C)) return;
+// FAS coarse problem: f_c = L_c(u_c) + r_c, and uo_c = u_c, at cell t (r and
+// f may be the same array).
+__device__ __forceinline__ void mg_fas_one(const MgGeo &C, const double *u, const double *a, const double *a2,
+                                           const double *r, double *f, double *uo, long t) {
   int i, j, k;
   mg_cell(C, t, i, j, k);
   const long o = mg_off(C, i, j, k);
@@ -600,15 +558,21 @@ __global__ __launch_bounds__(NT) void k_mg_fas_rhs(const MgGeo C, const double *
   uo[o] = u[o];
 }
 
+__global__ __launch_bounds__(NT) void k_mg_fas_rhs(const MgGeo C, const double *__restrict__ u,
+                                                   const double *__restrict__ a, const double *__restrict__ a2,
+                                                   const double *__restrict__ r, double *__restrict__ f,
+                                                   double *__restrict__ uo) {
+  const long t = (long)blockIdx.x * NT + threadIdx.x;
+  if (t < mg_cells(C)) mg_fas_one(C, u, a, a2, r, f, uo, t);
+}
+
 // Coarse problem of a fine level in one pass over the coarse cells: the
 // residual f - L(u) of each child (boundary rule inline) and the
-// volume-weighted means of u and of the residual into the coarse u and r.
-__global__ __launch_bounds__(NT) void k_mg_restrict_res(const MgGeo F, const MgGeo C, const double *__restrict__ u,
-                                                        const double *__restrict__ f, const double *__restrict__ a,
-                                                        const double *__restrict__ a2, double *__restrict__ uc,
-                                                        double *__restrict__ rc) {
-  const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t >= mg_cells(C)) return;
+// volume-weighted means of u and of the residual into the coarse u and r,
+// at coarse cell t.
+__device__ __forceinline__ void mg_restrict_res_one(const MgGeo &F, const MgGeo &C, const double *u, const double *f,
+                                                    const double *a, const double *a2, double *uc, double *rc,
+                                                    long t) {
   int i, j, k;
   mg_cell(C, t, i, j, k);
   double su = 0.0, sr = 0.0, w = 0.0;
@@ -628,6 +592,14 @@ __global__ __launch_bounds__(NT) void k_mg_restrict_res(const MgGeo F, const MgG
   rc[oc] = sr / w;
 }
 
+__global__ __launch_bounds__(NT) void k_mg_restrict_res(const MgGeo F, const MgGeo C, const double *__restrict__ u,
+                                                        const double *__restrict__ f, const double *__restrict__ a,
+                                                        const double *__restrict__ a2, double *__restrict__ uc,
+                                                        double *__restrict__ rc) {
+  const long t = (long)blockIdx.x * NT + threadIdx.x;
+  if (t < mg_cells(C)) mg_restrict_res_one(F, C, u, f, a, a2, uc, rc, t);
+}
+
 // u_F += P (u_C - uo_C): Kwak prolongation of the coarse correction, whose
 // values across the boundary follow the boundary rule (it is homogeneous,
 // so the correction obeys it too); NC components back to back.
@@ -637,10 +609,8 @@ __device__ __forceinline__ double mg_corr(const MgGeo &C, const double *__restri
 }
 
 template <int NC>
-__global__ __launch_bounds__(NT) void k_mg_correct(const MgGeo C, const MgGeo F, const double *__restrict__ uc0,
-                                                   const double *__restrict__ uoc0, double *__restrict__ fine0) {
-  const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t >= mg_cells(F)) return;
+__device__ __forceinline__ void mg_correct_one(const MgGeo &C, const MgGeo &F, const double *uc0, const double *uoc0,
+                                               double *fine0, long t) {
   int fc[3];
   mg_cell(F, t, fc[0], fc[1], fc[2]);
   int cc[3];
@@ -678,6 +648,399 @@ __global__ __launch_bounds__(NT) void k_mg_correct(const MgGeo C, const MgGeo F,
     }
     fine[mg_off(F, fc[0], fc[1], fc[2])] += s;
   }
+}
+
+template <int NC>
+__global__ __launch_bounds__(NT) void k_mg_correct(const MgGeo C, const MgGeo F, const double *__restrict__ uc0,
+                                                   const double *__restrict__ uoc0, double *__restrict__ fine0) {
+  const long t = (long)blockIdx.x * NT + threadIdx.x;
+  if (t < mg_cells(F)) mg_correct_one<NC>(C, F, uc0, uoc0, fine0, t);
+}
+
+// ---- Tail of the hierarchy -------------------------------------------------
+// A V-cycle (or the whole FMG cycle) over the coarse levels 0 .. top by one
+// workgroup, on copies of the levels' arrays in LDS, every phase separated by
+// a workgroup barrier (sweeps of at most one wavefront's cells run in one
+// wavefront without one).  As launches these levels are latency alone: eleven
+// launches of 3 to 5 us per level and cycle, whatever the level's size.  The
+// phases are a program made on the host, so that each body is compiled once
+// and the kernel stays small in registers and instruction cache (a version
+// with the bodies inlined per level ran at the launches' speed).  A phase is
+// bound by its chain of LDS reads and FP64 operations, about 1 us: on a
+// 128 x 96 grid the levels 64 x 48 and below take 64 us per V-cycle (with ten
+// coarsest sweeps) against about 160 us as launches, and the cleaning solve
+// 1.14 instead of 2.05 ms; the limit of 4096 cells is the LDS that four
+// arrays per level leave.
+
+constexpr int kTailThreads = 1024;
+constexpr int kTailLds = 20352;   // doubles of LDS (159 KB of the CU's 160)
+constexpr int kTailCells = 4096;  // most cells of a tail level
+constexpr int kTailLevels = 13;
+constexpr int kTailSlots = 2;     // cells of one colour per thread, at most
+enum { kOpSweep = 0, kOpCoarse = 1, kOpCorrect = 2 };
+
+// One level of the tail: sizes, magic multipliers of the divisions by
+// (n0 + 1) / 2, n0 and n1, and the places of its arrays in LDS (offsets in
+// doubles, interior cells only, x fastest; -1: absent; tab: the 1D tables
+// a0m, a0p, g1, g2, vol0 and a1m, a1p, s2t, vol1 of curvilinear levels).
+struct MgLev {
+  int n[3], s2, nc, cells;
+  unsigned mh, mn0, mn1;
+  int u, f, a, a2, uo, tab;
+  int per[3];         // periodic axes
+  unsigned rob;       // faces with a position-dependent Robin factor (bit 2 axis + side)
+  double fac[3][2];   // boundary factor of the other faces
+  double w[3];        // Cartesian weights 1 / h^2 (w[2] also of the others' axis 2)
+  double x0[3], h[3];
+};
+
+struct MgTail {
+  MgLev lev[kTailLevels];
+  int ndim, coord, power, power2, top;
+  double offset;
+  int nprog[2];                 // V-cycle, FMG cycle
+  int prog[2][512];             // op + 4 level + 64 sweeps
+};
+
+// u / d with the magic multiplier m of d (0: d = 1); exact for u d < 2^32.
+__device__ __forceinline__ int mg_div(int u, unsigned m) { return m ? (int)__umulhi((unsigned)u, m) : u; }
+
+// a (u + c)^p + a2 (u + c)^q and its derivative.
+__device__ __forceinline__ double mg_nl_both(int power, int power2, double offset, double a, double a2, double u,
+                                             double &du) {
+  const double w = u + offset;
+  double nl = a, rw = 0.0;
+  du = 0.0;
+  if (power == 1) {
+    nl = a * w;
+    du = a;
+  } else if (power == -1) {
+    rw = rcp(w);
+    nl = a * rw;
+    du = -nl * rw;
+  }
+  if (a2 != 0.0) {
+    if (power != -1) rw = rcp(w);
+    double t;
+    if (power2 == -7) {
+      const double r2 = rw * rw;
+      t = a2 * (r2 * r2) * (r2 * rw);
+    } else {
+      t = a2 * mg_ipow(power2 < 0 ? rw : w, power2 < 0 ? -power2 : power2);
+    }
+    nl += t;
+    du += power2 * t * rw;
+  }
+  return nl;
+}
+
+// A tail cell's stencil: its offset, the steps to its neighbours (0 across a
+// face of the domain, whose value is the boundary rule applied to the cell
+// itself), the faces it lies on (bit 2 axis + side) and the rule's factor per
+// axis (a level has at least two cells along an axis, so at most one face
+// per axis).  CA: Cartesian weights (three scalars; else from the level's
+// tables); ROB: faces whose Robin factor depends on the position exist; NL:
+// power -1 or a second term.
+struct MgCell {
+  int o, dm[3], dp[3], i, j;
+  unsigned edge;
+  double fac[3];
+};
+
+template <bool ROB>
+__device__ __forceinline__ MgCell mg_tail_stencil(const MgTail &T, const MgLev &V, int i, int j, int k) {
+  MgCell c;
+  const int x[3] = {i, j, k}, S[3] = {1, V.n[0], V.s2};
+  c.i = i;
+  c.j = j;
+  c.o = i + V.n[0] * j + V.s2 * k;
+  c.edge = 0;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const int n = V.n[a], wrap = V.per[a] ? (n - 1) * S[a] : 0;
+    const bool lo = x[a] == 0, hi = x[a] == n - 1;
+    c.dm[a] = lo ? wrap : -S[a];
+    c.dp[a] = hi ? -wrap : S[a];
+    if (!V.per[a]) c.edge |= (lo ? 1u : 0u) << (2 * a) | (hi ? 2u : 0u) << (2 * a);
+    c.fac[a] = hi ? V.fac[a][1] : V.fac[a][0];
+  }
+  if (ROB && (c.edge & V.rob)) {
+    // r_in / r_ghost = r_in^2 / sqrt(r_in^2 r_ghost^2)
+    double y[3], rr = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      y[a] = V.x0[a] + (x[a] + 0.5) * V.h[a];
+      if (a < T.ndim && (a < 2 || T.coord == GMUNU_CART)) rr += y[a] * y[a];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      if (!((c.edge & V.rob) >> (2 * a) & 3)) continue;
+      const double g = (c.edge >> (2 * a)) & 2 ? y[a] + V.h[a] : y[a] - V.h[a];
+      c.fac[a] = rr * rsq(rr * (rr - y[a] * y[a] + g * g));
+    }
+  }
+  return c;
+}
+
+// L(u) and dL/du at a tail cell with coefficients av, a2v.
+template <bool CA, bool NL>
+__device__ __forceinline__ double mg_tail_L(const MgTail &T, const MgLev &V, const double *sm, const MgCell &c,
+                                            double av, double a2v, double &dg) {
+  const double *u = sm + V.u;
+  const double uc = u[c.o];
+  const int I = c.i + 1, J = c.j + (T.ndim > 1 ? 1 : 0), t0 = V.n[0] + 2, t1 = V.n[1] + (T.ndim > 1 ? 2 : 0);
+  const double *p0 = sm + V.tab, *p1 = p0 + 5 * t0;
+  double lap = 0.0, d = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    if (a >= T.ndim) continue;
+    double um = u[c.o + c.dm[a]], up = u[c.o + c.dp[a]];
+    if ((c.edge >> (2 * a)) & 1) um *= c.fac[a];
+    if ((c.edge >> (2 * a)) & 2) up *= c.fac[a];
+    double wm, wp;
+    if (CA) {
+      wm = wp = V.w[a];
+    } else if (a == 0) {
+      wm = p0[I];
+      wp = p0[t0 + I];
+    } else if (a == 1) {
+      wm = p0[2 * t0 + I] * p1[J];
+      wp = p0[2 * t0 + I] * p1[t1 + J];
+    } else {
+      wm = wp = p0[3 * t0 + I] * p1[2 * t1 + J] * V.w[2];
+    }
+    lap += wp * (up - uc) - wm * (uc - um);
+    d -= wm + wp;
+  }
+  if (NL) {
+    double du;
+    lap -= mg_nl_both(T.power, T.power2, T.offset, av, a2v, uc, du);
+    dg = d - du;
+  } else {
+    const bool lin = T.power == 1;
+    lap -= lin ? av * (uc + T.offset) : av;
+    dg = lin ? d - av : d;
+  }
+  return lap;
+}
+
+__device__ __forceinline__ void mg_tail_cell(const MgLev &V, int t, int &i, int &j, int &k) {
+  const int r = mg_div(t, V.mn0);
+  i = t - r * V.n[0];
+  k = mg_div(r, V.mn1);
+  j = r - k * V.n[1];
+}
+
+// Order of LDS accesses between the lanes of one wavefront.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sum over the 2^ndim lanes of one coarse cell.
+__device__ __forceinline__ double mg_sum_children(double x, int ndim) {
+  for (int o = 1; o < 1 << ndim; o <<= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+// Red-black sweeps of one level.  A thread keeps the stencils and coefficients
+// of its cells (up to kTailSlots of each colour) in registers over the sweeps.
+template <bool CA, bool ROB, bool NL>
+__device__ __forceinline__ void mg_tail_sweeps(const MgTail &T, const MgLev &V, double *sm, int sweeps) {
+  const int nc = V.nc, hrow = (V.n[0] + 1) >> 1, n0 = V.n[0], n1 = V.n[1];
+  const bool one_wave = nc <= 64;
+  if (!one_wave || threadIdx.x < 64) {
+    MgCell c[kTailSlots][2];
+    double f[kTailSlots][2], av[kTailSlots][2], a2v[kTailSlots][2];
+    bool on[kTailSlots][2];
+#pragma unroll
+    for (int m = 0; m < kTailSlots; m++) {
+      const int t = threadIdx.x + m * blockDim.x;
+      const int row = mg_div(t, V.mh), k = mg_div(row, V.mn1), j = row - k * n1, h = 2 * (t - row * hrow);
+#pragma unroll
+      for (int s = 0; s < 2; s++) {
+        const int i = h + ((j + k + s) & 1);
+        on[m][s] = t < nc && i < n0;
+        if (!on[m][s]) continue;
+        c[m][s] = mg_tail_stencil<ROB>(T, V, i, j, k);
+        f[m][s] = sm[V.f + c[m][s].o];
+        av[m][s] = V.a >= 0 ? sm[V.a + c[m][s].o] : 0.0;
+        a2v[m][s] = NL && V.a2 >= 0 ? sm[V.a2 + c[m][s].o] : 0.0;
+      }
+    }
+    for (int n = 0; n < sweeps; n++) {
+#pragma unroll
+      for (int s = 0; s < 2; s++) {
+#pragma unroll
+        for (int m = 0; m < kTailSlots; m++) {
+          if (!on[m][s]) continue;
+          double dg;
+          const double L = mg_tail_L<CA, NL>(T, V, sm, c[m][s], av[m][s], a2v[m][s], dg);
+          sm[V.u + c[m][s].o] -= (L - f[m][s]) * rcp(dg);
+        }
+        if (one_wave)
+          wave_fence();
+        else
+          __syncthreads();
+      }
+    }
+  }
+  if (one_wave) __syncthreads();
+}
+
+// The coarse problem of level C below F, one lane per child in the restriction.
+template <bool CA, bool ROB, bool NL>
+__device__ __forceinline__ void mg_tail_coarse_problem(const MgTail &T, const MgLev &F, const MgLev &C, double *sm) {
+  const int nc = C.cells, nd = T.ndim;
+  // every lane of a wavefront takes part in the sums: rounds of whole blocks
+  for (int t0 = 0; t0 < nc << nd; t0 += blockDim.x) {
+    const int t = t0 + threadIdx.x, oc = t >> nd;
+    double su = 0.0, sr = 0.0, w = 0.0;
+    if (oc < nc) {
+      int i, j, k;
+      mg_tail_cell(C, oc, i, j, k);
+      i = 2 * i + (t & 1);
+      if (nd > 1) j = 2 * j + ((t >> 1) & 1);
+      if (nd > 2) k = 2 * k + ((t >> 2) & 1);
+      const MgCell c = mg_tail_stencil<ROB>(T, F, i, j, k);
+      const double *v0 = sm + F.tab + 4 * (F.n[0] + 2), *v1 = v0 + F.n[0] + 2 + 3 * (F.n[1] + (nd > 1 ? 2 : 0));
+      w = CA ? 1.0 : v0[i + 1] * v1[j + (nd > 1 ? 1 : 0)];
+      double dg;
+      const double L = mg_tail_L<CA, NL>(T, F, sm, c, F.a >= 0 ? sm[F.a + c.o] : 0.0,
+                                         NL && F.a2 >= 0 ? sm[F.a2 + c.o] : 0.0, dg);
+      su = w * sm[F.u + c.o];
+      sr = w * (sm[F.f + c.o] - L);
+    }
+    su = mg_sum_children(su, nd);
+    sr = mg_sum_children(sr, nd);
+    w = CA ? (double)(1 << nd) : mg_sum_children(w, nd);
+    if (oc < nc && (t & ((1 << nd) - 1)) == 0) {
+      sm[C.u + oc] = sm[C.uo + oc] = su / w;
+      sm[C.f + oc] = sr / w;
+    }
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < nc; t += blockDim.x) {
+    int i, j, k;
+    mg_tail_cell(C, t, i, j, k);
+    const MgCell c = mg_tail_stencil<ROB>(T, C, i, j, k);
+    double dg;
+    sm[C.f + t] += mg_tail_L<CA, NL>(T, C, sm, c, C.a >= 0 ? sm[C.a + t] : 0.0, NL && C.a2 >= 0 ? sm[C.a2 + t] : 0.0,
+                                     dg);
+  }
+  __syncthreads();
+}
+
+// u_F += P(u_C - uo_C): k_mg_correct on the LDS arrays.
+__device__ __forceinline__ void mg_tail_correct(const MgTail &T, const MgLev &F, const MgLev &C, double *sm) {
+  const int nd = T.ndim;
+  const double w0 = nd == 1 ? 0.75 : nd == 2 ? 0.5 : 0.25;
+  const double *uc = sm + C.u, *uoc = sm + C.uo;
+  const int S[3] = {1, C.n[0], C.s2};
+  for (int t = threadIdx.x; t < F.cells; t += blockDim.x) {
+    int fc[3];
+    mg_tail_cell(F, t, fc[0], fc[1], fc[2]);
+    const int cc[3] = {fc[0] >> 1, nd > 1 ? fc[1] >> 1 : fc[1], nd > 2 ? fc[2] >> 1 : fc[2]};
+    const int oc = cc[0] + S[1] * cc[1] + S[2] * cc[2];
+    const double e0 = uc[oc] - uoc[oc];
+    double s = w0 * e0;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      if (a >= nd) continue;
+      const bool up = fc[a] & 1;
+      const int n = C.n[a];
+      const bool inside = up ? cc[a] < n - 1 : cc[a] > 0;
+      const int step = inside ? S[a] : C.per[a] ? -(n - 1) * S[a] : 0, on = up ? oc + step : oc - step;
+      double e = uc[on] - uoc[on];
+      if (!inside && !C.per[a]) {
+        double fac = up ? C.fac[a][1] : C.fac[a][0];
+        if ((C.rob >> (2 * a + (up ? 1 : 0))) & 1) {
+          double ri = 0.0, rg = 0.0;
+#pragma unroll
+          for (int b = 0; b < 3; b++) {
+            if (b >= nd || (b == 2 && T.coord != GMUNU_CART)) continue;
+            const double x = C.x0[b] + (cc[b] + 0.5) * C.h[b], g = b == a ? (up ? x + C.h[b] : x - C.h[b]) : x;
+            ri += x * x;
+            rg += g * g;
+          }
+          fac = ri * rsq(ri * rg);
+        }
+        e = fac * e0;
+      }
+      s += 0.25 * e;
+    }
+    sm[F.u + t] += s;
+  }
+  __syncthreads();
+}
+
+// The cells of a level between its global array (ghost layers as in the
+// level's own geometry) and LDS.
+template <bool OUT>
+__device__ __forceinline__ void mg_tail_copy(const MgTail &T, const MgLev &V, double *glob, double *lds) {
+  const int g1 = T.ndim > 1 ? 1 : 0, g2 = T.ndim > 2 ? 1 : 0;
+  const int S1 = V.n[0] + 2, S2 = S1 * (V.n[1] + 2 * g1);
+  for (int t = threadIdx.x; t < V.cells; t += blockDim.x) {
+    int i, j, k;
+    mg_tail_cell(V, t, i, j, k);
+    const int o = (k + g2) * S2 + (j + g1) * S1 + i + 1;
+    if (OUT)
+      glob[o] = lds[t];
+    else
+      lds[t] = glob[o];
+  }
+}
+
+// Tt: the plan; geo: the levels' geometries; u, f, a_top, a2_top: the top
+// level's arrays; ptr: the a (then a2) arrays of the levels below (device
+// memory).
+template <bool CA, bool ROB, bool NL>
+__global__ __launch_bounds__(kTailThreads) void k_mg_tail(const MgTail *__restrict__ Tt, const MgGeo *__restrict__ geo,
+                                                          double *u, const double *__restrict__ f,
+                                                          const double *a_top, const double *a2_top,
+                                                          double *const *__restrict__ ptr, int use_fmg) {
+  __shared__ double sm[kTailLds];
+  const MgTail &T = *Tt;
+  mg_tail_copy<false>(T, T.lev[T.top], u, sm + T.lev[T.top].u);
+  mg_tail_copy<false>(T, T.lev[T.top], const_cast<double *>(f), sm + T.lev[T.top].f);
+  for (int l = 0; l <= T.top; l++) {
+    const MgLev &V = T.lev[l];
+    if (V.a >= 0) mg_tail_copy<false>(T, V, l == T.top ? const_cast<double *>(a_top) : ptr[l], sm + V.a);
+    if (V.a2 >= 0)
+      mg_tail_copy<false>(T, V, l == T.top ? const_cast<double *>(a2_top) : ptr[kTailLevels + l], sm + V.a2);
+    if (!CA) {
+      const MgGeo &g = geo[l];
+      const int t0 = V.n[0] + 2, t1 = V.n[1] + (T.ndim > 1 ? 2 : 0);
+      double *p = sm + V.tab;
+      for (int t = threadIdx.x; t < t0; t += blockDim.x) {
+        p[t] = g.a0m[t];
+        p[t0 + t] = g.a0p[t];
+        p[2 * t0 + t] = g.g1[t];
+        p[3 * t0 + t] = g.g2[t];
+        p[4 * t0 + t] = g.vol0[t];
+      }
+      p += 5 * t0;
+      for (int t = threadIdx.x; t < t1; t += blockDim.x) {
+        p[t] = g.a1m[t];
+        p[t1 + t] = g.a1p[t];
+        p[2 * t1 + t] = g.s2t[t];
+        p[3 * t1 + t] = g.vol1[t];
+      }
+    }
+  }
+  __syncthreads();
+  const int np = T.nprog[use_fmg];
+  for (int pc = 0; pc < np; pc++) {
+    const int op = T.prog[use_fmg][pc], l = (op >> 2) & 15;
+    if ((op & 3) == kOpSweep)
+      mg_tail_sweeps<CA, ROB, NL>(T, T.lev[l], sm, op >> 6);
+    else if ((op & 3) == kOpCoarse)
+      mg_tail_coarse_problem<CA, ROB, NL>(T, T.lev[l], T.lev[l - 1], sm);
+    else
+      mg_tail_correct(T, T.lev[l], T.lev[l - 1], sm);
+  }
+  mg_tail_copy<true>(T, T.lev[T.top], u, sm + T.lev[T.top].u);
 }
 
 // Kwak prolongation of v (coarse, ghosts set) into the fine interior:
@@ -1467,6 +1830,13 @@ struct gmunu_mg {
   // (allocated by the first solve of a large enough level; fs == NULL: none)
   double *fs, *as, *a2s;
   const double *sf, *sa, *sa2;  // the split copies' sources in the cycles being run
+  // the tail's plans by the terms present (bit 0: a, bit 1: a2): top level
+  // (-1: none) and device copy; the levels' geometries and their own a and
+  // a2 arrays on the device
+  int ttop[4];
+  MgTail *tplan;
+  MgGeo *tgeo;
+  double **tptr;
   double *part;  // norm partials + result
   double *br;    // state bridge scratch (6 arrays of the finest level), allocated on first use
   // vector equations (Cartesian): per coarse level u, f, r, uo of three
@@ -1725,10 +2095,36 @@ void correct(gmunu_mg *m, int l, hipStream_t st) {
                      m->u[l]);
 }
 
-// The coarsest level: one workgroup when it is small, else launches.
 // Dynamic LDS a one-workgroup coarsest solve may stage (bytes).
 constexpr long kCoarseLds = 64L * 1024;
 
+// Which of the tail's plans serves the bound equation.
+int tail_kind(const gmunu_mg *m) { return (m->a[0] ? 1 : 0) | (m->a2[0] ? 2 : 0); }
+
+// A V-cycle (the whole FMG cycle) of the tail's levels, u and f of its top
+// level in place.
+void launch_tail(gmunu_mg *m, bool use_fmg, hipStream_t st) {
+  const int kind = tail_kind(m), top = m->ttop[kind];
+  const MgGeo &G = m->geo[top];
+  const long nc = (long)((G.n[0] + 1) / 2) * G.n[1] * G.n[2], th = (nc + 63) / 64 * 64;
+  const dim3 block(th < kTailThreads ? th : kTailThreads);
+  bool rob = G.coord != GMUNU_CART;
+  for (int a = 0; a < G.ndim; a++) rob = rob || G.bc[a][0] == GMUNU_MG_ROBIN || G.bc[a][1] == GMUNU_MG_ROBIN;
+  const bool nl = m->d.power == -1 || m->a2[top];
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), block, 0, st, m->tplan + kind, m->tgeo, m->u[top], m->f[top], m->a[top],
+                       m->a2[top], m->tptr, use_fmg ? 1 : 0);
+  };
+  if (G.coord != GMUNU_CART)
+    run(k_mg_tail<false, true, true>);
+  else if (rob)
+    nl ? run(k_mg_tail<true, true, true>) : run(k_mg_tail<true, true, false>);
+  else
+    nl ? run(k_mg_tail<true, false, true>) : run(k_mg_tail<true, false, false>);
+}
+
+// The coarsest level beyond the tail: launches (the line smoother's own
+// one-workgroup solve when it is small).
 void coarse_solve(gmunu_mg *m, hipStream_t st) {
   const MgGeo &G = m->geo[0];
   if (G.line) {
@@ -1740,16 +2136,14 @@ void coarse_solve(gmunu_mg *m, hipStream_t st) {
       line_sweeps(G, m->u[0], m->f[0], m->a[0], m->a2[0], m->d.coarse, st);
     return;
   }
-  if (cells(G) <= 64L * NT) {
-    const long bytes = (2 + (m->a[0] ? 1 : 0) + (m->a2[0] ? 1 : 0)) * G.nt * (long)sizeof(double);
-    const int lds = bytes <= kCoarseLds;
-    hipLaunchKernelGGL(k_mg_coarse, dim3(1), dim3(NT), lds ? bytes : 0, st, G, m->u[0], m->f[0], m->a[0], m->a2[0],
-                       m->d.coarse, lds);
-  } else
-    sweeps_raw(G, m->u[0], m->f[0], m->a[0], m->a2[0], m->d.coarse, st);
+  sweeps_raw(G, m->u[0], m->f[0], m->a[0], m->a2[0], m->d.coarse, st);
 }
 
 void vcycle(gmunu_mg *m, int l, hipStream_t st) {
+  if (l == m->ttop[tail_kind(m)]) {
+    launch_tail(m, false, st);
+    return;
+  }
   if (l == 0) {
     coarse_solve(m, st);
     return;
@@ -1766,9 +2160,13 @@ void vcycle(gmunu_mg *m, int l, hipStream_t st) {
 
 void fmg(gmunu_mg *m, hipStream_t st) {
   const int top = m->levels - 1;
-  for (int l = top; l > 0; l--) coarse_problem(m, l, st);
-  coarse_solve(m, st);
-  for (int l = 1; l <= top; l++) {
+  const int tail = m->ttop[tail_kind(m)], bottom = tail < 0 ? 0 : tail;
+  for (int l = top; l > bottom; l--) coarse_problem(m, l, st);
+  if (tail >= 0)
+    launch_tail(m, true, st);
+  else
+    coarse_solve(m, st);
+  for (int l = bottom + 1; l <= top; l++) {
     correct(m, l, st);
     vcycle(m, l, st);
   }
@@ -1993,6 +2391,114 @@ bool vector_storage(gmunu_mg *m) {
   return true;
 }
 
+// The plan of the tail for an equation with (kind bit 0) a and (bit 1) a2:
+// the largest level whose tail fits the LDS, -1 if none does.
+int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
+  std::memset(&T, 0, sizeof T);
+  const gmunu_mg_desc &d = m->d;
+  T.ndim = d.ndim;
+  T.coord = d.coord;
+  T.power = d.power;
+  T.power2 = d.power2;
+  T.offset = d.offset;
+  auto magic = [](int v) { return v == 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)v) + 1u; };
+  // u, f, a, a2 of every level and uo below the top, small levels first
+  long at = 0;
+  T.top = -1;
+  for (int l = 0; l < m->levels && l < kTailLevels && cells(m->geo[l]) <= kTailCells; l++) {
+    const MgGeo &G = m->geo[l];
+    if ((long)((G.n[0] + 1) / 2) * G.n[1] * G.n[2] > kTailSlots * kTailThreads) break;
+    MgLev &V = T.lev[l];
+    const int nc = (int)cells(G);
+    for (int a = 0; a < 3; a++) {
+      V.n[a] = G.n[a];
+      V.per[a] = a < G.ndim && G.bc[a][0] == GMUNU_MG_PERIODIC;
+      V.w[a] = G.coord == GMUNU_CART ? G.vih2[a] : G.ih2_2;
+      V.x0[a] = G.x0[a];
+      V.h[a] = G.h[a];
+      for (int sd = 0; sd < 2 && a < G.ndim; sd++) {
+        V.fac[a][sd] = G.bc[a][sd] == GMUNU_MG_DIRICHLET ? -1.0 : 1.0;
+        if (G.bc[a][sd] != GMUNU_MG_ROBIN) continue;
+        if (G.coord == GMUNU_SPH)
+          V.fac[a][sd] = sd ? G.rob_hi : G.rob_lo;
+        else
+          V.rob |= 1u << (2 * a + sd);
+      }
+    }
+    V.s2 = G.n[0] * G.n[1];
+    V.nc = (G.n[0] + 1) / 2 * G.n[1] * G.n[2];
+    V.cells = nc;
+    V.mh = magic((G.n[0] + 1) / 2);
+    V.mn0 = magic(G.n[0]);
+    V.mn1 = magic(G.n[1]);
+    long p = at;
+    auto take = [&p](long n) {
+      p += n;
+      return (int)(p - n);
+    };
+    V.u = take(nc);
+    V.f = take(nc);
+    V.a = kind & 1 ? take(nc) : -1;
+    V.a2 = kind & 2 ? take(nc) : -1;
+    V.tab = G.coord == GMUNU_CART ? 0 : take(5 * (G.n[0] + 2) + 4 * (G.n[1] + 2));
+    if (p > kTailLds) break;
+    T.top = l;
+    V.uo = take(nc);  // used when a level above belongs to the tail too
+    at = p;
+  }
+  auto put = [&T](int f, int op, int l, int sweeps) {
+    if (op != kOpSweep || sweeps) T.prog[f][T.nprog[f]++] = op + 4 * l + 64 * sweeps;
+  };
+  auto vcycle_at = [&](int f, int top) {
+    for (int l = top; l > 0; l--) {
+      put(f, kOpSweep, l, d.pre);
+      put(f, kOpCoarse, l, 0);
+    }
+    put(f, kOpSweep, 0, d.coarse);
+    for (int l = 1; l <= top; l++) {
+      put(f, kOpCorrect, l, 0);
+      put(f, kOpSweep, l, d.post);
+    }
+  };
+  if (T.top < 0) return -1;
+  vcycle_at(0, T.top);
+  for (int l = T.top; l > 0; l--) put(1, kOpCoarse, l, 0);
+  put(1, kOpSweep, 0, d.coarse);
+  for (int l = 1; l <= T.top; l++) {
+    put(1, kOpCorrect, l, 0);
+    vcycle_at(1, l);
+  }
+  return T.top;
+}
+
+// The tail's plans, geometries and array pointers, uploaded once.
+bool tail_plans(gmunu_mg *m) {
+  if (m->d.pre > 1 << 20 || m->d.post > 1 << 20 || m->d.coarse > 1 << 20) return true;  // sweeps of a program word
+  std::vector<MgTail> T(4);
+  int top = -1;
+  for (int k = 0; k < 4; k++) {
+    if ((k & 2) && !m->d.power2) continue;
+    m->ttop[k] = tail_plan(m, k, T[k]);
+    top = m->ttop[k] > top ? m->ttop[k] : top;
+  }
+  if (top < 0) return true;
+  std::vector<double *> ptr(2 * kTailLevels, nullptr);
+  for (int l = 0; l <= top && l < m->levels - 1; l++) {
+    ptr[l] = m->aown[l];
+    ptr[kTailLevels + l] = m->a2own[l];
+  }
+  auto upload = [m](const void *src, size_t bytes) -> void * {
+    double *p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    m->owned.push_back(p);
+    return hipMemcpy(p, src, bytes, hipMemcpyHostToDevice) == hipSuccess ? p : nullptr;
+  };
+  m->tplan = static_cast<MgTail *>(upload(T.data(), T.size() * sizeof(MgTail)));
+  m->tgeo = static_cast<MgGeo *>(upload(m->geo, (top + 1) * sizeof(MgGeo)));
+  m->tptr = static_cast<double **>(upload(ptr.data(), ptr.size() * sizeof(double *)));
+  return m->tplan && m->tgeo && m->tptr;
+}
+
 // ------------------------------------------------- solve driver
 
 // The private stream is ordered after the caller's work on entry and the
@@ -2100,6 +2606,10 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   };
   m->br = nullptr;
   m->xs = nullptr;
+  for (int &t : m->ttop) t = -1;
+  m->tplan = nullptr;
+  m->tgeo = nullptr;
+  m->tptr = nullptr;
   m->fs = m->as = m->a2s = nullptr;
   m->sf = m->sa = m->sa2 = nullptr;
   m->vready = false;
@@ -2150,6 +2660,11 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
     G.s2t = b + off[l][8];
     G.vol1 = b + off[l][9];
     G.sg1 = b + off[l][10];
+  }
+  if (!m->geo[levels - 1].line && !tail_plans(m)) {
+    for (double *p : m->owned) (void)hipFree(p);
+    delete m;
+    return GMUNU_ENOMEM;
   }
   *out = m;
   return GMUNU_OK;
