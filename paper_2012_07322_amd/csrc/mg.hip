@@ -847,7 +847,8 @@ __device__ __forceinline__ double mg_sum_children(double x, int ndim) {
 // Red-black sweeps of one level.  A thread keeps the stencils and coefficients
 // of its cells (up to kTailSlots of each colour) in registers over the sweeps.
 template <bool CA, bool ROB, bool NL>
-__device__ __forceinline__ void mg_tail_sweeps(const MgTail &T, const MgLev &V, double *sm, int sweeps) {
+__device__ __forceinline__ void mg_tail_sweeps(const MgTail &T, const MgLev &Vg, double *sm, int sweeps) {
+  const MgLev V = Vg;  // in registers over the sweeps
   const int nc = V.nc, hrow = (V.n[0] + 1) >> 1, n0 = V.n[0], n1 = V.n[1];
   const bool one_wave = nc <= 64;
   if (!one_wave || threadIdx.x < 64) {
@@ -1335,6 +1336,211 @@ __global__ __launch_bounds__(NT) void k_mgv_smooth2(const MgGeo G, double *u, co
     }
     __syncthreads();
   }
+}
+
+// ---- Tail of the hierarchy, vector equations (Cartesian) ----------------------
+// As k_mg_tail, for levels of at most kVTailCells cells: one lane per cell and
+// component, the components of a cell in one wavefront (at a corner of the
+// domain a component's mixed difference reads the other components of the
+// cell itself, so all must be read before one is written).  A colour is bound
+// by the latency of its 15 LDS reads and their chain, 0.4 us on 8^3 cells
+// against 5 us for the launch of a colour pair; above 1024 cells the LDS reads
+// of one CU take longer than launches over many.
+
+constexpr int kVTailCells = 1024;
+
+struct MgvLev {
+  int n[3], s2, cells;
+  unsigned mn0, mn1;
+  int u, f, uo;        // offsets of component 0 (component stride: cells)
+  int per[3];
+  unsigned odd[3][2];  // components odd across each non-periodic face
+  double w[3], mix[3], idg[3];
+};
+
+struct MgvTail {
+  MgvLev lev[kTailLevels];
+  int ndim, top;
+  int nprog[2];
+  int prog[2][512];
+};
+
+__device__ __forceinline__ double mgv_flip(double v, unsigned bit) {
+  return __hiloint2double(__double2hiint(v) ^ (int)(bit << 31), __double2loint(v));
+}
+
+// Component q of L(X) at cell (i, j, k) of a tail level.
+__device__ __forceinline__ double mgv_tail_L(const MgvLev &V, const double *sm, int q, int i, int j, int k, int o) {
+  const int x[3] = {i, j, k}, S[3] = {1, V.n[0], V.s2};
+  int dm[3], dp[3];
+  unsigned fm[3], fp[3];
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const int n = V.n[a], wrap = V.per[a] ? (n - 1) * S[a] : 0;
+    const bool lo = x[a] == 0, hi = x[a] == n - 1;
+    dm[a] = lo ? wrap : -S[a];
+    dp[a] = hi ? -wrap : S[a];
+    fm[a] = lo ? V.odd[a][0] : 0u;
+    fp[a] = hi ? V.odd[a][1] : 0u;
+  }
+  const double *u = sm + V.u + o, *uq = u + q * V.cells;
+  const double u0 = uq[0];
+  double lap = 0.0, gd = 0.0;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    const double up = mgv_flip(uq[dp[a]], fp[a] >> q & 1u), um = mgv_flip(uq[dm[a]], fm[a] >> q & 1u);
+    const double d2 = (up - 2.0 * u0 + um) * V.w[a];
+    lap += d2;
+    if (a == q) gd = d2;
+  }
+  // mixed differences along q and each other axis b
+  const int qm = q == 0 ? dm[0] : q == 1 ? dm[1] : dm[2], qp = q == 0 ? dp[0] : q == 1 ? dp[1] : dp[2];
+  const unsigned gm = q == 0 ? fm[0] : q == 1 ? fm[1] : fm[2], gp = q == 0 ? fp[0] : q == 1 ? fp[1] : fp[2];
+#pragma unroll
+  for (int e = 0; e < 2; e++) {
+    const bool first = e == 0 ? q == 0 : q == 2;  // the other axis is 1, else 0 (e = 0) or 2 (e = 1)
+    const int b = first ? 1 : 2 * e;
+    const int bm = first ? dm[1] : dm[2 * e], bp = first ? dp[1] : dp[2 * e];
+    const unsigned hm = first ? fm[1] : fm[2 * e], hp = first ? fp[1] : fp[2 * e];
+    const double *ub = u + b * V.cells;
+    const double pp = mgv_flip(ub[qp + bp], (gp ^ hp) >> b & 1u), pm = mgv_flip(ub[qp + bm], (gp ^ hm) >> b & 1u);
+    const double mp = mgv_flip(ub[qm + bp], (gm ^ hp) >> b & 1u), mm = mgv_flip(ub[qm + bm], (gm ^ hm) >> b & 1u);
+    // pairs (0, 1), (0, 2), (1, 2): q + b - 1
+    const double mix = e == 0 ? (q == 2 ? V.mix[1] : V.mix[0]) : (q == 0 ? V.mix[1] : V.mix[2]);
+    gd += (pp - pm - mp + mm) * mix;
+  }
+  return lap + gd * (1.0 / 3.0);
+}
+
+__device__ __forceinline__ void mgv_tail_cell(const MgvLev &V, int t, int &i, int &j, int &k) {
+  const int r = mg_div(t, V.mn0);
+  i = t - r * V.n[0];
+  k = mg_div(r, V.mn1);
+  j = r - k * V.n[1];
+}
+
+__device__ __forceinline__ void mgv_tail_sweeps(const MgvTail &T, const MgvLev &Vg, double *sm, int sweeps) {
+  const MgvLev V = Vg;  // in registers over the sweeps
+  const int nd = T.ndim;
+  // one lane per component of the 2^ndim cells that differ in their parities
+  const int ln = threadIdx.x & 63, q = ln % 3, slot = (threadIdx.x >> 6) * 21 + ln / 3;
+  const int hx = (V.n[0] + 1) >> 1, hy = (V.n[1] + 1) >> 1, hz = (V.n[2] + 1) >> 1;
+  const int r = (int)((unsigned)slot / (unsigned)hx), kk = (int)((unsigned)r / (unsigned)hy);
+  const int i0 = 2 * (slot - r * hx), j0 = 2 * (r - kk * hy), k0 = 2 * kk;
+  const double idg = q == 0 ? V.idg[0] : q == 1 ? V.idg[1] : V.idg[2];
+  const bool one_wave = hx * hy * hz <= 21, live = ln < 63 && kk < hz;
+  if (!one_wave || threadIdx.x < 64) {
+    for (int s = 0; s < sweeps; s++)
+      for (int c = 0; c < 1 << nd; c++) {
+        const int i = i0 + (c & 1), j = j0 + ((c >> 1) & 1), k = k0 + (c >> 2);
+        if (live && i < V.n[0] && j < V.n[1] && k < V.n[2]) {
+          const int o = i + V.n[0] * j + V.s2 * k;
+          const double L = mgv_tail_L(V, sm, q, i, j, k, o);
+          sm[V.u + q * V.cells + o] -= (L - sm[V.f + q * V.cells + o]) * idg;
+        }
+        if (one_wave)
+          wave_fence();
+        else
+          __syncthreads();
+      }
+  }
+  if (one_wave) __syncthreads();
+}
+
+__device__ __forceinline__ void mgv_tail_coarse_problem(const MgvTail &T, const MgvLev &F, const MgvLev &C,
+                                                        double *sm) {
+  const int nc = C.cells, nd = T.ndim;
+  for (int t0 = 0; t0 < 3 * nc << nd; t0 += blockDim.x) {
+    const int t = t0 + threadIdx.x, e = t >> nd;
+    const int q = e >= 2 * nc ? 2 : e >= nc ? 1 : 0, oc = e - q * nc;
+    double su = 0.0, sr = 0.0;
+    if (e < 3 * nc) {
+      int i, j, k;
+      mgv_tail_cell(C, oc, i, j, k);
+      i = 2 * i + (t & 1);
+      if (nd > 1) j = 2 * j + ((t >> 1) & 1);
+      if (nd > 2) k = 2 * k + ((t >> 2) & 1);
+      const int o = i + F.n[0] * j + F.s2 * k;
+      su = sm[F.u + q * F.cells + o];
+      sr = sm[F.f + q * F.cells + o] - mgv_tail_L(F, sm, q, i, j, k, o);
+    }
+    su = mg_sum_children(su, nd);
+    sr = mg_sum_children(sr, nd);
+    if (e < 3 * nc && (t & ((1 << nd) - 1)) == 0) {
+      const double iw = 1.0 / (1 << nd);
+      sm[C.u + e] = sm[C.uo + e] = su * iw;
+      sm[C.f + e] = sr * iw;
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 3 * nc; e += blockDim.x) {
+    const int q = e >= 2 * nc ? 2 : e >= nc ? 1 : 0;
+    int i, j, k;
+    mgv_tail_cell(C, e - q * nc, i, j, k);
+    sm[C.f + e] += mgv_tail_L(C, sm, q, i, j, k, e - q * nc);
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void mgv_tail_correct(const MgvTail &T, const MgvLev &F, const MgvLev &C, double *sm) {
+  const int nd = T.ndim;
+  const double w0 = nd == 1 ? 0.75 : nd == 2 ? 0.5 : 0.25;
+  const int S[3] = {1, C.n[0], C.s2};
+  for (int e = threadIdx.x; e < 3 * F.cells; e += blockDim.x) {
+    const int q = e >= 2 * F.cells ? 2 : e >= F.cells ? 1 : 0;
+    int fc[3];
+    mgv_tail_cell(F, e - q * F.cells, fc[0], fc[1], fc[2]);
+    const int cc[3] = {fc[0] >> 1, nd > 1 ? fc[1] >> 1 : fc[1], nd > 2 ? fc[2] >> 1 : fc[2]};
+    const int oc = cc[0] + S[1] * cc[1] + S[2] * cc[2] + q * C.cells;
+    double s = w0 * (sm[C.u + oc] - sm[C.uo + oc]);
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      if (a >= nd) continue;
+      const bool up = fc[a] & 1, inside = up ? cc[a] < C.n[a] - 1 : cc[a] > 0;
+      const int step = inside ? S[a] : C.per[a] ? -(C.n[a] - 1) * S[a] : 0, on = up ? oc + step : oc - step;
+      const unsigned odd = inside ? 0u : up ? C.odd[a][1] : C.odd[a][0];
+      s += 0.25 * mgv_flip(sm[C.u + on] - sm[C.uo + on], odd >> q & 1u);
+    }
+    sm[F.u + e] += s;
+  }
+  __syncthreads();
+}
+
+template <bool OUT>
+__device__ __forceinline__ void mgv_tail_copy(const MgvTail &T, const MgvLev &V, double *glob, double *lds) {
+  const int g1 = T.ndim > 1 ? 1 : 0, g2 = T.ndim > 2 ? 1 : 0;
+  const int S1 = V.n[0] + 2, S2 = S1 * (V.n[1] + 2 * g1), nt = S2 * (V.n[2] + 2 * g2);
+  for (int e = threadIdx.x; e < 3 * V.cells; e += blockDim.x) {
+    const int q = e >= 2 * V.cells ? 2 : e >= V.cells ? 1 : 0;
+    int i, j, k;
+    mgv_tail_cell(V, e - q * V.cells, i, j, k);
+    const int o = q * nt + (k + g2) * S2 + (j + g1) * S1 + i + 1;
+    if (OUT)
+      glob[o] = lds[e];
+    else
+      lds[e] = glob[o];
+  }
+}
+
+__global__ __launch_bounds__(kTailThreads) void k_mgv_tail(const MgvTail *__restrict__ Tt, double *u,
+                                                           const double *__restrict__ f, int use_fmg) {
+  __shared__ double sm[kVTailCells * 11 + 64];
+  const MgvTail &T = *Tt;
+  const MgvLev &P = T.lev[T.top];
+  mgv_tail_copy<false>(T, P, u, sm + P.u);
+  mgv_tail_copy<false>(T, P, const_cast<double *>(f), sm + P.f);
+  __syncthreads();
+  const int np = T.nprog[use_fmg];
+  for (int pc = 0; pc < np; pc++) {
+    const int op = T.prog[use_fmg][pc], l = (op >> 2) & 15;
+    if ((op & 3) == kOpSweep)
+      mgv_tail_sweeps(T, T.lev[l], sm, op >> 6);
+    else if ((op & 3) == kOpCoarse)
+      mgv_tail_coarse_problem(T, T.lev[l], T.lev[l - 1], sm);
+    else
+      mgv_tail_correct(T, T.lev[l], T.lev[l - 1], sm);
+  }
+  mgv_tail_copy<true>(T, P, u, sm + P.u);
 }
 
 // Coarsest level: all sweeps in one workgroup, colours separated by
@@ -1837,6 +2043,8 @@ struct gmunu_mg {
   MgTail *tplan;
   MgGeo *tgeo;
   double **tptr;
+  int vtop;        // the vector equations' tail (Cartesian point smoother; -1: none)
+  MgvTail *vplan;
   double *part;  // norm partials + result
   double *br;    // state bridge scratch (6 arrays of the finest level), allocated on first use
   // vector equations (Cartesian): per coarse level u, f, r, uo of three
@@ -2332,7 +2540,18 @@ void vcoarse_solve(gmunu_mg *m, hipStream_t st) {
     vsweeps(G, m->vu[0], m->vf[0], m->d.coarse, st);
 }
 
+void launch_vtail(gmunu_mg *m, bool use_fmg, hipStream_t st) {
+  const MgGeo &G = m->geo[m->vtop];
+  const long waves = (colour_cells(G, 0) + 20) / 21;  // 21 cells of one colour per wavefront
+  hipLaunchKernelGGL(k_mgv_tail, dim3(1), dim3(64 * waves), 0, st, m->vplan, m->vu[m->vtop], m->vf[m->vtop],
+                     use_fmg ? 1 : 0);
+}
+
 void vvcycle(gmunu_mg *m, int l, hipStream_t st) {
+  if (l == m->vtop) {
+    launch_vtail(m, false, st);
+    return;
+  }
   if (l == 0) {
     vcoarse_solve(m, st);
     return;
@@ -2345,10 +2564,13 @@ void vvcycle(gmunu_mg *m, int l, hipStream_t st) {
 }
 
 void vfmg(gmunu_mg *m, hipStream_t st) {
-  const int top = m->levels - 1;
-  for (int l = top; l > 0; l--) vcoarse_problem(m, l, st);
-  vcoarse_solve(m, st);
-  for (int l = 1; l <= top; l++) {
+  const int top = m->levels - 1, bottom = m->vtop < 0 ? 0 : m->vtop;
+  for (int l = top; l > bottom; l--) vcoarse_problem(m, l, st);
+  if (m->vtop >= 0)
+    launch_vtail(m, true, st);
+  else
+    vcoarse_solve(m, st);
+  for (int l = bottom + 1; l <= top; l++) {
     vcorrect(m, l, st);
     vvcycle(m, l, st);
   }
@@ -2391,6 +2613,34 @@ bool vector_storage(gmunu_mg *m) {
   return true;
 }
 
+// Magic multiplier of the division by v (mg_div).
+unsigned magic_of(int v) { return v == 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)v) + 1u; }
+
+// The programs of a tail up to level `top`: a V-cycle, and the FMG cycle.
+void tail_program(const gmunu_mg_desc &d, int top, int prog[2][512], int nprog[2]) {
+  auto put = [&](int f, int op, int l, int sweeps) {
+    if (op != kOpSweep || sweeps) prog[f][nprog[f]++] = op + 4 * l + 64 * sweeps;
+  };
+  auto vcycle_at = [&](int f, int lt) {
+    for (int l = lt; l > 0; l--) {
+      put(f, kOpSweep, l, d.pre);
+      put(f, kOpCoarse, l, 0);
+    }
+    put(f, kOpSweep, 0, d.coarse);
+    for (int l = 1; l <= lt; l++) {
+      put(f, kOpCorrect, l, 0);
+      put(f, kOpSweep, l, d.post);
+    }
+  };
+  vcycle_at(0, top);
+  for (int l = top; l > 0; l--) put(1, kOpCoarse, l, 0);
+  put(1, kOpSweep, 0, d.coarse);
+  for (int l = 1; l <= top; l++) {
+    put(1, kOpCorrect, l, 0);
+    vcycle_at(1, l);
+  }
+}
+
 // The plan of the tail for an equation with (kind bit 0) a and (bit 1) a2:
 // the largest level whose tail fits the LDS, -1 if none does.
 int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
@@ -2401,7 +2651,6 @@ int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
   T.power = d.power;
   T.power2 = d.power2;
   T.offset = d.offset;
-  auto magic = [](int v) { return v == 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)v) + 1u; };
   // u, f, a, a2 of every level and uo below the top, small levels first
   long at = 0;
   T.top = -1;
@@ -2428,9 +2677,9 @@ int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
     V.s2 = G.n[0] * G.n[1];
     V.nc = (G.n[0] + 1) / 2 * G.n[1] * G.n[2];
     V.cells = nc;
-    V.mh = magic((G.n[0] + 1) / 2);
-    V.mn0 = magic(G.n[0]);
-    V.mn1 = magic(G.n[1]);
+    V.mh = magic_of((G.n[0] + 1) / 2);
+    V.mn0 = magic_of(G.n[0]);
+    V.mn1 = magic_of(G.n[1]);
     long p = at;
     auto take = [&p](long n) {
       p += n;
@@ -2446,28 +2695,41 @@ int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
     V.uo = take(nc);  // used when a level above belongs to the tail too
     at = p;
   }
-  auto put = [&T](int f, int op, int l, int sweeps) {
-    if (op != kOpSweep || sweeps) T.prog[f][T.nprog[f]++] = op + 4 * l + 64 * sweeps;
-  };
-  auto vcycle_at = [&](int f, int top) {
-    for (int l = top; l > 0; l--) {
-      put(f, kOpSweep, l, d.pre);
-      put(f, kOpCoarse, l, 0);
+  if (T.top >= 0) tail_program(d, T.top, T.prog, T.nprog);
+  return T.top;
+}
+
+// The vector equations' plan (-1: the coarsest level is too large).
+int vtail_plan(const gmunu_mg *m, MgvTail &T) {
+  std::memset(&T, 0, sizeof T);
+  T.ndim = m->d.ndim;
+  T.top = -1;
+  int at = 0;
+  for (int l = 0; l < m->levels && l < kTailLevels && cells(m->geo[l]) <= kVTailCells; l++) {
+    const MgGeo &G = m->geo[l];
+    const int nc = (int)cells(G);
+    // 21 cells of one colour per wavefront; u, f and uo of three components
+    if ((colour_cells(G, 0) + 20) / 21 > kTailThreads / 64 || at + 6 * nc > kVTailCells * 11) break;
+    MgvLev &V = T.lev[l];
+    for (int a = 0; a < 3; a++) {
+      V.n[a] = G.n[a];
+      V.per[a] = a < G.ndim && G.bc[a][0] == GMUNU_MG_PERIODIC;
+      for (int sd = 0; sd < 2; sd++) V.odd[a][sd] = a < G.ndim && !V.per[a] ? G.vodd[a][sd] : 0u;
+      V.w[a] = G.vih2[a];
+      V.mix[a] = G.vmix[a];
+      V.idg[a] = G.vidg[a];
     }
-    put(f, kOpSweep, 0, d.coarse);
-    for (int l = 1; l <= top; l++) {
-      put(f, kOpCorrect, l, 0);
-      put(f, kOpSweep, l, d.post);
-    }
-  };
-  if (T.top < 0) return -1;
-  vcycle_at(0, T.top);
-  for (int l = T.top; l > 0; l--) put(1, kOpCoarse, l, 0);
-  put(1, kOpSweep, 0, d.coarse);
-  for (int l = 1; l <= T.top; l++) {
-    put(1, kOpCorrect, l, 0);
-    vcycle_at(1, l);
+    V.s2 = G.n[0] * G.n[1];
+    V.cells = nc;
+    V.mn0 = magic_of(G.n[0]);
+    V.mn1 = magic_of(G.n[1]);
+    V.u = at;
+    V.f = at + 3 * nc;
+    V.uo = at + 6 * nc;  // used when a level above belongs to the tail too
+    at += 9 * nc;
+    T.top = l;
   }
+  if (T.top >= 0) tail_program(m->d, T.top, T.prog, T.nprog);
   return T.top;
 }
 
@@ -2481,22 +2743,31 @@ bool tail_plans(gmunu_mg *m) {
     m->ttop[k] = tail_plan(m, k, T[k]);
     top = m->ttop[k] > top ? m->ttop[k] : top;
   }
+  MgvTail V;
+  std::memset(&V, 0, sizeof V);
+  if (m->d.coord == GMUNU_CART) m->vtop = vtail_plan(m, V);
   if (top < 0) return true;
   std::vector<double *> ptr(2 * kTailLevels, nullptr);
   for (int l = 0; l <= top && l < m->levels - 1; l++) {
     ptr[l] = m->aown[l];
     ptr[kTailLevels + l] = m->a2own[l];
   }
-  auto upload = [m](const void *src, size_t bytes) -> void * {
-    double *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
-    m->owned.push_back(p);
-    return hipMemcpy(p, src, bytes, hipMemcpyHostToDevice) == hipSuccess ? p : nullptr;
-  };
-  m->tplan = static_cast<MgTail *>(upload(T.data(), T.size() * sizeof(MgTail)));
-  m->tgeo = static_cast<MgGeo *>(upload(m->geo, (top + 1) * sizeof(MgGeo)));
-  m->tptr = static_cast<double **>(upload(ptr.data(), ptr.size() * sizeof(double *)));
-  return m->tplan && m->tgeo && m->tptr;
+  // one upload: the plans, the levels' geometries, the array pointers
+  const size_t b0 = T.size() * sizeof(MgTail), b1 = b0 + sizeof(MgvTail), b2 = b1 + (top + 1) * sizeof(MgGeo);
+  std::vector<char> buf(b2 + ptr.size() * sizeof(double *));
+  std::memcpy(buf.data(), T.data(), b0);
+  std::memcpy(buf.data() + b0, &V, sizeof V);
+  std::memcpy(buf.data() + b1, m->geo, (top + 1) * sizeof(MgGeo));
+  std::memcpy(buf.data() + b2, ptr.data(), ptr.size() * sizeof(double *));
+  char *p = nullptr;
+  if (hipMalloc(&p, buf.size()) != hipSuccess) return false;
+  m->owned.push_back(reinterpret_cast<double *>(p));
+  if (hipMemcpy(p, buf.data(), buf.size(), hipMemcpyHostToDevice) != hipSuccess) return false;
+  m->tplan = reinterpret_cast<MgTail *>(p);
+  m->vplan = reinterpret_cast<MgvTail *>(p + b0);
+  m->tgeo = reinterpret_cast<MgGeo *>(p + b1);
+  m->tptr = reinterpret_cast<double **>(p + b2);
+  return true;
 }
 
 // ------------------------------------------------- solve driver
@@ -2598,18 +2869,14 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   std::vector<double> tab;
   size_t off[kMaxLevels][11];
   for (int l = 0; l < levels; l++) level_tables(*desc, levels - 1 - l, tab, off[l], m->geo[l]);
-  auto alloc = [&](size_t n) -> double * {
-    double *p = nullptr;
-    if (hipMalloc(&p, n * sizeof(double)) != hipSuccess) return nullptr;
-    m->owned.push_back(p);
-    return p;
-  };
   m->br = nullptr;
   m->xs = nullptr;
   for (int &t : m->ttop) t = -1;
   m->tplan = nullptr;
   m->tgeo = nullptr;
   m->tptr = nullptr;
+  m->vtop = -1;
+  m->vplan = nullptr;
   m->fs = m->as = m->a2s = nullptr;
   m->sf = m->sa = m->sa2 = nullptr;
   m->vready = false;
@@ -2617,32 +2884,40 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   m->ev = nullptr;
   for (auto &sl : m->slot) sl = gmunu_mg::Slot{nullptr, false, nullptr, nullptr, nullptr, nullptr};
   m->next_slot = 0;
-  bool ok = (m->tab = alloc(tab.size())) != nullptr && (m->part = alloc(kNormParts + 1 + kGateSlots)) != nullptr;
-  // coarse levels: u, f, a, r (restricted residual) and uo (restricted u);
-  // the finest level only uo (the cleaning's divergence when the caller
-  // passes none)
-  for (int l = 0; l < levels && ok; l++) {
-    const size_t nt = (size_t)m->geo[l].nt;
-    ok = (m->uo[l] = alloc(nt)) != nullptr;
-    m->r[l] = nullptr;
-    m->a2own[l] = nullptr;
-    if (ok && l < levels - 1)
-      ok = (m->r[l] = alloc(nt)) && (m->u[l] = alloc(nt)) && (m->f[l] = alloc(nt)) && (m->aown[l] = alloc(nt));
-    if (ok && l < levels - 1 && desc->power2 != 0) ok = (m->a2own[l] = alloc(nt)) != nullptr;
+  // one allocation: the tables, the norm's partials, then the zeroed level
+  // arrays (ghosts of coarse arrays are then defined): u, f, a, r (restricted
+  // residual), uo (restricted u) and a2 of the coarse levels, uo of the finest
+  // (the cleaning's divergence when the caller passes none)
+  size_t at = 0;
+  auto take = [&at](size_t n) {
+    at = (at + 31) / 32 * 32;
+    at += n;
+    return at - n;
+  };
+  const size_t tab_at = take(tab.size()), part_at = take(kNormParts + 1 + kGateSlots), zero_at = take(0);
+  size_t arr_at[kMaxLevels][6];
+  for (int l = 0; l < levels; l++)
+    for (int q = 0; q < 6; q++)
+      if (q == 0 || (l < levels - 1 && (q < 5 || desc->power2 != 0))) arr_at[l][q] = take(m->geo[l].nt);
+  double *p = nullptr;
+  bool ok = hipMalloc(&p, at * sizeof(double)) == hipSuccess;
+  if (ok) m->owned.push_back(p);
+  m->tab = p + tab_at;
+  m->part = p + part_at;
+  for (int l = 0; l < levels; l++) {
+    const bool coarse = l < levels - 1;
+    m->uo[l] = p + arr_at[l][0];
+    m->u[l] = coarse ? p + arr_at[l][1] : nullptr;
+    m->f[l] = coarse ? p + arr_at[l][2] : nullptr;
+    m->aown[l] = coarse ? p + arr_at[l][3] : nullptr;
+    m->r[l] = coarse ? p + arr_at[l][4] : nullptr;
+    m->a2own[l] = coarse && desc->power2 != 0 ? p + arr_at[l][5] : nullptr;
   }
-  ok = ok && hipMemcpy(m->tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess;
-  // zero every owned level array (ghosts of coarse arrays are then defined)
-  for (int l = 0; l < levels && ok; l++) {
-    const size_t b = (size_t)m->geo[l].nt * sizeof(double);
-    ok = hipMemset(m->uo[l], 0, b) == hipSuccess;
-    if (ok && l < levels - 1)
-      ok = hipMemset(m->r[l], 0, b) == hipSuccess && hipMemset(m->u[l], 0, b) == hipSuccess &&
-           hipMemset(m->f[l], 0, b) == hipSuccess && hipMemset(m->aown[l], 0, b) == hipSuccess &&
-           (!m->a2own[l] || hipMemset(m->a2own[l], 0, b) == hipSuccess);
-  }
-  ok = ok && hipDeviceSynchronize() == hipSuccess;
+  ok = ok && hipMemcpy(m->tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess &&
+       hipMemset(p + zero_at, 0, (at - zero_at) * sizeof(double)) == hipSuccess &&
+       hipDeviceSynchronize() == hipSuccess;
   if (!ok) {
-    for (double *p : m->owned) (void)hipFree(p);
+    for (double *q : m->owned) (void)hipFree(q);
     delete m;
     return GMUNU_ENOMEM;
   }

@@ -59,3 +59,34 @@ def test_one_cycle(name, terms, fmg):
     gmu.Multigrid(p).solve(ug, dev(f), None if a is None else dev(a), a2=None if a2 is None else dev(a2), **opt)
     g, o = mg.interior(p, host(ug)), mg.interior(p, uo)
     assert np.abs(g - o).max() <= 1e-12 * np.abs(o).max()
+
+
+VECTOR = {
+    "2d_1024": cart((32, 32), [D, N], [PER, PER]),
+    "2d_above_1024": cart((34, 32), [D, D], [N, D], coarse=3),
+    "1d": cart((1024,), [D, N], coarse=4),
+    "3d_above_1024": cart((12, 12, 8), [N, N], [PER, PER], [D, D]),
+    "3d_flat": cart((64, 4, 2), [D, N], [N, D], [N, N]),
+    "3d_one_level": cart((6, 5, 3), [D, D], [N, D], [D, D], levels=1, coarse=7),
+    "3d_odd_coarsest": cart((12, 20, 28), [D, N], [N, D], [D, D], pre=3, post=1),
+    "3d_wide": cart((72, 36, 40), [PER, PER], [D, N], [N, D], pre=1, post=1),
+    "2d_big": cart((160, 224), [D, N], [N, D]),
+}
+
+
+@pytest.mark.parametrize("fmg", [True, False])
+@pytest.mark.parametrize("name", list(VECTOR))
+def test_one_vector_cycle(name, fmg):
+    p = VECTOR[name]
+    rng = np.random.default_rng(11)
+    X, f = rng.uniform(-1, 1, (3,) + mg.shape(p)), rng.uniform(-1, 1, (3,) + mg.shape(p))
+    Xo, opt = X.copy(), dict(tol=0.0, max_cycles=1, fmg=fmg)
+    h = mg.vsolve(p, Xo, f, **opt)
+    if not h[1] < h[0]:
+        pytest.skip("the oracle's own cycle diverges from this start: nothing contracts")
+    Xg = dev(X)
+    gmu.Multigrid(p).vsolve(Xg, dev(f), **opt)
+    g = host(Xg)
+    for c in range(3):
+        a, b = mg.interior(p, g[c]), mg.interior(p, Xo[c])
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(Xo).max(), c
