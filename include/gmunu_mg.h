@@ -89,7 +89,10 @@ typedef struct gmunu_mg gmunu_mg;
  * fewer than 2^31 entries per array),
  * build the level hierarchy on the current device and allocate its arrays
  * (5 arrays per coarse level, 6 with power2 != 0; 1 on the finest; the
- * vector equations add 12 per coarse level on their first use).
+ * vector equations add 12 per coarse level on their first use, and on
+ * Cartesian grids of two or three axes 3 per level, the finest included, for
+ * the out-of-place point smoother; without memory for those the level is
+ * relaxed in place).
  * Synchronous. */
 int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out);
 int gmunu_mg_destroy(gmunu_mg *mg);

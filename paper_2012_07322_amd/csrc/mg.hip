@@ -1108,6 +1108,10 @@ __global__ __launch_bounds__(NT) void k_mg_subgrad(const MgGeo G, const double *
 // an axis is an offset and a sign, and a diagonal neighbour takes the
 // product of the two steps' signs.
 
+__device__ __forceinline__ double mgv_flip(double v, unsigned bit) {
+  return __hiloint2double(__double2hiint(v) ^ (int)(bit << 31), __double2loint(v));
+}
+
 struct VStep {
   int dm[3], dp[3];  // offsets of the minus / plus neighbour along each axis
   unsigned neg;      // bit 6 q + a: the minus step negates component q; 6 q + 3 + a: the plus step
@@ -1338,6 +1342,186 @@ __global__ __launch_bounds__(NT) void k_mgv_smooth2(const MgGeo G, double *u, co
   }
 }
 
+// The colours of one parity of k (in 2D all colours) on a Cartesian level, out
+// of place: cells of planes k = kpar, kpar + 2, ... of out from planes k - 1
+// and k + 1 of nb and plane k of u (out may not be u).  Two launches (nb = u, then nb = out) are
+// one sweep.  A workgroup stages the three planes of a TX x TY tile and its
+// halo in LDS, relaxes the four colours of plane k there and writes the
+// tile.  The colours reach beyond the tile: colour (1, 1) at its upper edge
+// needs (0, 1) at x = TX, which needs (1, 0) at TX + 1 and that (0, 0) at
+// TX + 2 (and two cells below x = 0, one row above the tile), so those are
+// relaxed redundantly, one 2 x 2 quad of cells per thread and component.  In LDS a row holds
+// its even cells, then its odd ones: a colour's reads are contiguous.
+// Against a launch per colour pair, which reads the whole field, this halves
+// the launches and reads each plane from memory about once per parity.  Bound
+// by the staged bytes (1.5 times the tile for its halo) on large levels and
+// by one workgroup's chain of load, four colours and store on small ones:
+// 50 us per launch at 128^3 (3.4 TB/s of staged, f and written bytes) and
+// 7.4 us from 16^3 to 32^3 cells, against 33 and 7 us for each of the twice
+// as many launches of a colour pair (one thread per quad and all components:
+// 64 and 13 us).
+constexpr int kPlX = 32, kPlY = 16;           // tile
+constexpr int kPlRow = kPlX + 8, kPlRows = kPlY + 3;  // staged: x -3 .. TX + 3 (row of 40), y -1 .. TY + 1
+constexpr int kPlQx = kPlX / 2 + 3, kPlQy = kPlY / 2 + 1;
+constexpr int kPlCS = kPlRows * kPlRow;  // staged cells of a plane
+constexpr int kPlQuads = 192;  // threads of one component
+static_assert(kPlQx * kPlQy <= kPlQuads && kPlQuads % 64 == 0, "one quad per thread, whole wavefronts");
+
+// Place of tile coordinate x (>= -4) in a staged row.
+__device__ __forceinline__ constexpr int pl_x(int x) { return ((x + 4) & 1) * (kPlRow / 2) + ((x + 4) >> 1); }
+
+// Component Q of the cell of colour (CI, CJ) whose centre in LDS is o (plane k,
+// component 0): steps to its neighbours (EDGE: 0 across a face, with the
+// flips of the components odd there) and L(X)^Q; u0: the component's value.
+template <int ND, int CI, int CJ, bool EDGE, int Q>
+__device__ __forceinline__ double mgv_plane_L(const MgGeo &G, const double *sm, int o, int zm, int zp, unsigned fzm,
+                                              unsigned fzp, int gi, int gj, double &u0) {
+  constexpr int XM = CI ? -(kPlRow / 2) : kPlRow / 2 - 1, XP = CI ? 1 - kPlRow / 2 : kPlRow / 2;
+  int dm[3] = {XM, -kPlRow, zm}, dp[3] = {XP, kPlRow, zp};
+  unsigned fm[3] = {0u, 0u, fzm}, fp[3] = {0u, 0u, fzp};
+  if constexpr (EDGE) {
+    const bool px = G.bc[0][0] == GMUNU_MG_PERIODIC, py = G.bc[1][0] == GMUNU_MG_PERIODIC;
+    if (!px && gi == 0) dm[0] = 0, fm[0] = G.vodd[0][0];
+    if (!px && gi == G.n[0] - 1) dp[0] = 0, fp[0] = G.vodd[0][1];
+    if (!py && gj == 0) dm[1] = 0, fm[1] = G.vodd[1][0];
+    if (!py && gj == G.n[1] - 1) dp[1] = 0, fp[1] = G.vodd[1][1];
+  }
+  auto at = [&](int c, int d, unsigned flip) -> double {
+    const double v = sm[o + c * (3 * kPlCS) + d];
+    return EDGE ? mgv_flip(v, flip >> c & 1u) : v;
+  };
+  u0 = sm[o + Q * (3 * kPlCS)];
+  double lap = 0.0, gd = 0.0;
+#pragma unroll
+  for (int a = 0; a < ND; a++) {
+    const double d2 = (at(Q, dp[a], fp[a]) - 2.0 * u0 + at(Q, dm[a], fm[a])) * G.vih2[a];
+    lap += d2;
+    if (a == Q) gd = d2;
+  }
+#pragma unroll
+  for (int b = 0; b < ND; b++) {
+    if (Q >= ND || b == Q) continue;
+    const double pp = at(b, dp[Q] + dp[b], fp[Q] ^ fp[b]), pm = at(b, dp[Q] + dm[b], fp[Q] ^ fm[b]);
+    const double mp = at(b, dm[Q] + dp[b], fm[Q] ^ fp[b]), mm = at(b, dm[Q] + dm[b], fm[Q] ^ fm[b]);
+    gd += (pp - pm - mp + mm) * G.vmix[Q + b - 1];
+  }
+  return lap + gd * (1.0 / 3.0);
+}
+
+// The four colours, component Q.  The components of one cell are relaxed by
+// three wavefronts; at a corner of the domain one reads the others of its
+// own cell, so there (EDGE) a barrier separates the reads from the writes.
+template <int ND, bool EDGE, int Q>
+__device__ __forceinline__ void mgv_plane_colours(const MgGeo &G, double *sm, int i0, int j0, const bool *on,
+                                                  const double *fv, int zm, int zp, unsigned fzm, unsigned fzp) {
+  const int tq = threadIdx.x % kPlQuads, hx = tq % kPlQx, hy = tq / kPlQx, gi = i0 + 2 * hx - 2, gj = j0 + 2 * hy;
+  const int o = kPlCS + (2 * hy + 1) * kPlRow + pl_x(0) + hx - 1;  // even cell of the quad's lower row, plane k
+  double u0, L;
+#define GM_PL(C)                                                                                                   \
+  {                                                                                                                \
+    const int oc = o + (C & 1) * (kPlRow / 2) + (C >> 1) * kPlRow;                                                 \
+    if (on[C])                                                                                                     \
+      L = mgv_plane_L<ND, C & 1, (C >> 1), EDGE, Q>(G, sm, oc, zm, zp, fzm, fzp, gi + (C & 1), gj + (C >> 1), u0); \
+    if (EDGE) __syncthreads();                                                                                     \
+    if (on[C]) sm[oc + Q * (3 * kPlCS)] = u0 - (L - fv[C]) * G.vidg[Q];                                            \
+    __syncthreads();                                                                                               \
+  }
+  GM_PL(0)
+  GM_PL(1)
+  GM_PL(2)
+  GM_PL(3)
+#undef GM_PL
+}
+
+template <int ND, int Q>
+__device__ __forceinline__ void mgv_plane_tile(const MgGeo &G, const double *u, const double *nb,
+                                               const double *__restrict__ f, double *out, int i0, int j0, int k,
+                                               double *sm) {
+  const int n0 = G.n[0], n1 = G.n[1], n2 = G.n[2], tq = threadIdx.x % kPlQuads;
+  const bool px = G.bc[0][0] == GMUNU_MG_PERIODIC, py = G.bc[1][0] == GMUNU_MG_PERIODIC,
+             pz = ND > 2 && G.bc[2][0] == GMUNU_MG_PERIODIC;
+  const bool lz = ND > 2 && !pz && k == 0, hz = ND > 2 && !pz && k == n2 - 1;
+  const long q0 = Q * G.nt;
+  const double *uk = u + q0 + k * G.s2, *um = nb + q0 + (k == 0 ? n2 - 1 : k - 1) * G.s2,
+               *up = nb + q0 + (k == n2 - 1 ? 0 : k + 1) * G.s2;
+  // every load of the tile before the first LDS write: one memory latency
+  constexpr int NIT = (kPlCS + kPlQuads - 1) / kPlQuads;
+  double v[NIT][3];
+  bool in[NIT];
+#pragma unroll
+  for (int m = 0; m < NIT; m++) {
+    const int e = tq + m * kPlQuads, r = e / kPlRow, xx = e % kPlRow;
+    const int x = xx < kPlRow / 2 ? 2 * xx - 4 : 2 * (xx - kPlRow / 2) - 3;
+    int i = i0 + x, j = j0 + r - 1;
+    if (px) i = i < 0 ? i + (-i + n0 - 1) / n0 * n0 : i >= n0 ? i % n0 : i;
+    if (py) j = j < 0 ? j + n1 : j >= n1 ? j % n1 : j;
+    in[m] = e < kPlCS && i >= 0 && i < n0 && j >= 0 && j < n1 && x != -4;
+    const long o = in[m] ? mg_off(G, i, j, 0) : 0;
+    v[m][1] = in[m] ? uk[o] : 0.0;
+    v[m][0] = in[m] && ND > 2 && !lz ? um[o] : 0.0;
+    v[m][2] = in[m] && ND > 2 && !hz ? up[o] : 0.0;
+  }
+  // which cells of the thread's quad are relaxed, and their right-hand sides
+  const int hx = tq % kPlQx, hy = tq / kPlQx, x = 2 * hx - 2, y = 2 * hy, gi = i0 + x, gj = j0 + y;
+  bool on[4];
+  double fv[4];
+#pragma unroll
+  for (int c = 0; c < 4; c++) {
+    const int ci = c & 1, cj = c >> 1;
+    int ii = gi + ci, jj = gj + cj;
+    on[c] = hy < kPlQy && x + ci <= kPlX + 2 - c && (cj == 0 || (x + ci >= ci && hy < kPlQy - 1));
+    on[c] = on[c] && (px || (ii >= 0 && ii < n0)) && (py || jj < n1);
+    if (px) ii = ii < 0 ? ii + n0 : ii >= n0 ? ii % n0 : ii;
+    if (py) jj = jj >= n1 ? jj % n1 : jj;
+    fv[c] = on[c] ? f[q0 + mg_off(G, ii, jj, k)] : 0.0;
+  }
+#pragma unroll
+  for (int m = 0; m < NIT; m++) {
+    const int e = tq + m * kPlQuads;
+    if (!in[m]) continue;
+    double *d = sm + 3 * Q * kPlCS + e;
+    d[kPlCS] = v[m][1];
+    if (ND > 2) {
+      d[0] = v[m][0];
+      d[2 * kPlCS] = v[m][2];
+    }
+  }
+  __syncthreads();
+  const int zm = lz ? 0 : -kPlCS, zp = hz ? 0 : kPlCS;
+  const unsigned fzm = lz ? G.vodd[2][0] : 0u, fzp = hz ? G.vodd[2][1] : 0u;
+  const bool edge = (!px && (i0 == 0 || i0 + kPlX + 3 >= n0)) || (!py && (j0 == 0 || j0 + kPlY + 1 >= n1));
+  if (edge || lz || hz)
+    mgv_plane_colours<ND, true, Q>(G, sm, i0, j0, on, fv, zm, zp, fzm, fzp);
+  else
+    mgv_plane_colours<ND, false, Q>(G, sm, i0, j0, on, fv, zm, zp, fzm, fzp);
+#pragma unroll
+  for (int m = 0; m < (kPlX * kPlY + kPlQuads - 1) / kPlQuads; m++) {
+    const int e = tq + m * kPlQuads, xe = e % kPlX, ye = e / kPlX;
+    if (e < kPlX * kPlY && i0 + xe < n0 && j0 + ye < n1)
+      out[q0 + mg_off(G, i0 + xe, j0 + ye, k)] = sm[(3 * Q + 1) * kPlCS + (ye + 1) * kPlRow + pl_x(xe)];
+  }
+}
+
+template <int ND>
+__global__ __launch_bounds__(3 * kPlQuads) void k_mgv_planes(const MgGeo G, const double *u, const double *nb,
+                                                             const double *__restrict__ f, double *out, int kpar) {
+  __shared__ double sm[9 * kPlCS];  // [component][plane k - 1, k, k + 1][row][x]
+  // contiguous runs of tiles (x fastest, then y, then k) per XCD
+  const int gx = (G.n[0] + kPlX - 1) / kPlX, gy = (G.n[1] + kPlY - 1) / kPlY;
+  const int nt = gridDim.x, b = blockIdx.x, xc = b % 8, qn = nt / 8, rn = nt % 8;
+  const int t = xc * qn + (xc < rn ? xc : rn) + b / 8;
+  const int i0 = (t % gx) * kPlX, j0 = (t / gx) % gy * kPlY, k = kpar + 2 * (t / (gx * gy));
+  // one component per three wavefronts (the branch is uniform in each of them,
+  // and its three sides pass the same barriers)
+  const int q = threadIdx.x / kPlQuads;
+  if (q == 0)
+    mgv_plane_tile<ND, 0>(G, u, nb, f, out, i0, j0, k, sm);
+  else if (q == 1)
+    mgv_plane_tile<ND, 1>(G, u, nb, f, out, i0, j0, k, sm);
+  else
+    mgv_plane_tile<ND, 2>(G, u, nb, f, out, i0, j0, k, sm);
+}
+
 // ---- Tail of the hierarchy, vector equations (Cartesian) ----------------------
 // As k_mg_tail, for levels of at most kVTailCells cells: one lane per cell and
 // component, the components of a cell in one wavefront (at a corner of the
@@ -1364,10 +1548,6 @@ struct MgvTail {
   int nprog[2];
   int prog[2][512];
 };
-
-__device__ __forceinline__ double mgv_flip(double v, unsigned bit) {
-  return __hiloint2double(__double2hiint(v) ^ (int)(bit << 31), __double2loint(v));
-}
 
 // Component q of L(X) at cell (i, j, k) of a tail level.
 __device__ __forceinline__ double mgv_tail_L(const MgvLev &V, const double *sm, int q, int i, int j, int k, int o) {
@@ -2051,6 +2231,7 @@ struct gmunu_mg {
   // components each, allocated on first use; xs: scratch of the xCFC
   // sequence (17 finest arrays), allocated on first use
   double *vu[kMaxLevels], *vf[kMaxLevels], *vr[kMaxLevels], *vuo[kMaxLevels];
+  double *vs[kMaxLevels];  // second field of the levels that k_mgv_planes relaxes (null: none)
   bool vready;
   double *xs;
   std::vector<double *> owned;
@@ -2501,6 +2682,32 @@ void vsweeps(const MgGeo &G, double *u, const double *f, int sweeps, hipStream_t
     }
 }
 
+// One sweep out of place (k_mgv_planes): u to out.
+void vsweep_planes(const MgGeo &G, const double *u, double *out, const double *f, hipStream_t st) {
+  const int tiles = ((G.n[0] + kPlX - 1) / kPlX) * ((G.n[1] + kPlY - 1) / kPlY);
+  if (G.ndim == 2) {
+    hipLaunchKernelGGL(k_mgv_planes<2>, dim3(tiles), dim3(3 * kPlQuads), 0, st, G, u, u, f, out, 0);
+    return;
+  }
+  hipLaunchKernelGGL(k_mgv_planes<3>, dim3(tiles * ((G.n[2] + 1) / 2)), dim3(3 * kPlQuads), 0, st, G, u, u, f, out, 0);
+  if (G.n[2] > 1)
+    hipLaunchKernelGGL(k_mgv_planes<3>, dim3(tiles * (G.n[2] / 2)), dim3(3 * kPlQuads), 0, st, G, u, out, f, out, 1);
+}
+
+// `sweeps` sweeps of field u, alternating with the second field s (null: in
+// place); *cur: the field that holds the current values, u or s.
+void vsweeps_alt(const MgGeo &G, double *u, double *s, double **cur, const double *f, int sweeps, hipStream_t st) {
+  if (!s) {
+    vsweeps(G, u, f, sweeps, st);
+    return;
+  }
+  for (int n = 0; n < sweeps; n++) {
+    double *next = *cur == u ? s : u;
+    vsweep_planes(G, *cur, next, f, st);
+    *cur = next;
+  }
+}
+
 void vghosts(const MgGeo &G, double *u, hipStream_t st) {
   const long gc = ghost_count(G);
   if (gc) hipLaunchKernelGGL(k_mg_ghosts<3>, dim3(nblocks(gc)), dim3(NT), 0, st, G, u);
@@ -2556,11 +2763,17 @@ void vvcycle(gmunu_mg *m, int l, hipStream_t st) {
     vcoarse_solve(m, st);
     return;
   }
-  vsweeps(m->geo[l], m->vu[l], m->vf[l], m->d.pre, st);
+  // an odd number of sweeps: one in place, so that the field ends where it began
+  const MgGeo &G = m->geo[l];
+  double *u = m->vu[l], *s = m->vs[l];
+  const int odd = s && ((m->d.pre + m->d.post) & 1) ? 1 : 0, in_pre = odd && m->d.pre > 0;
+  vsweeps(G, u, m->vf[l], in_pre, st);
+  vsweeps_alt(G, u, s, &m->vu[l], m->vf[l], m->d.pre - in_pre, st);
   vcoarse_problem(m, l, st);
   vvcycle(m, l - 1, st);
   vcorrect(m, l, st);
-  vsweeps(m->geo[l], m->vu[l], m->vf[l], m->d.post, st);
+  if (odd && !in_pre) vsweeps(G, m->vu[l], m->vf[l], 1, st);
+  vsweeps_alt(G, u, s, &m->vu[l], m->vf[l], m->d.post - (odd && !in_pre), st);
 }
 
 void vfmg(gmunu_mg *m, hipStream_t st) {
@@ -2609,6 +2822,11 @@ bool vector_storage(gmunu_mg *m) {
         !alloc_zeroed(m, n, &m->vuo[l]))
       return false;
   }
+  // second fields of the levels above the tail; without memory for one the
+  // level is relaxed in place
+  for (int l = m->vtop + 1; l < m->levels; l++)
+    if (m->d.coord == GMUNU_CART && m->d.ndim > 1 && !m->geo[l].line && !m->vs[l])
+      (void)alloc_zeroed(m, 3 * (size_t)m->geo[l].nt, &m->vs[l]);
   m->vready = true;
   return true;
 }
@@ -2880,6 +3098,7 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   m->fs = m->as = m->a2s = nullptr;
   m->sf = m->sa = m->sa2 = nullptr;
   m->vready = false;
+  for (double *&v : m->vs) v = nullptr;
   m->gs = nullptr;
   m->ev = nullptr;
   for (auto &sl : m->slot) sl = gmunu_mg::Slot{nullptr, false, nullptr, nullptr, nullptr, nullptr};
@@ -3096,9 +3315,13 @@ int gmunu_mg_vsmooth(gmunu_mg *m, double *X, const double *f, int sweeps, void *
   if (!m || !X || !f) return GMUNU_ENULL;
   if (!ok_ptr(X) || !ok_ptr(f)) return GMUNU_EALIGN;
   if (!vector_ok(m) || sweeps < 0) return GMUNU_EINVAL;
+  (void)vector_storage(m);  // without memory: in place
   const MgGeo &G = m->geo[m->levels - 1];
   hipStream_t st = as_stream(stream);
-  vsweeps(G, X, f, sweeps, st);
+  double *s = m->vs[m->levels - 1], *cur = X;
+  const int odd = s ? sweeps & 1 : 0;  // in place, so that X holds the result
+  vsweeps(G, X, f, odd, st);
+  vsweeps_alt(G, X, s, &cur, f, sweeps - odd, st);
   vghosts(G, X, st);
   return launch_status();
 }
