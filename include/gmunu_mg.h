@@ -102,8 +102,8 @@ int gmunu_mg_levels(const gmunu_mg *mg);
 long gmunu_mg_size(const gmunu_mg *mg, int level);
 
 /* Solve L(u) = f on the finest level in place (with the point smoother, on
- * a large finest level the first call allocates colour-split copies of f,
- * a and a2 that the red-black sweeps read): an FAS full-multigrid cycle
+ * a large finest level the first call allocates a second u, to which the
+ * red-black sweeps alternate): an FAS full-multigrid cycle
  * from the current u first when fmg != 0, then FAS V-cycles until
  * max |f - L(u)| <= tol or max_cycles cycles were done (the FMG cycle
  * counts as one).  a and a2 may be NULL (zero); a2 needs power2 != 0
@@ -120,9 +120,9 @@ int gmunu_mg_residual_norm(gmunu_mg *mg, double *u, const double *f, const doubl
 
 /* Building blocks (finest level unless a level is given), for checking:
  * out = L(u) on the interior with u's ghosts as given; ghost fill; `sweeps`
- * sweeps of the descriptor's smoother (red-black: on a large finest level f,
- * a and a2 are first copied into colour-split buffers of the hierarchy, as
- * in the solve; line relaxation), then the ghost fill; restriction
+ * sweeps of the descriptor's smoother (red-black: on a large finest level
+ * by way of the hierarchy's second u, as in the solve; line relaxation),
+ * then the ghost fill; restriction
  * of level l into level l - 1 (volume-weighted mean of children); Kwak
  * prolongation of level l - 1 (ghosts as given) into level l. */
 int gmunu_mg_apply(gmunu_mg *mg, const double *u, const double *a, const double *a2, double *out, void *stream);

@@ -2,22 +2,24 @@
 // (gfx950): level hierarchy, kernels and the C ABI of include/gmunu_mg.h.
 //
 // Cheong et al., "Gmunu" (arXiv 2012.07322), section 2.7 and section 2.2.
-// Every operation of a cycle is one launch over the cells (or ghosts) of one
-// level, one thread per cell: the smoother updates one colour of the
-// red-black ordering per launch (i + j + k even first), the residual, the
+// On fine levels an operation of a cycle is one launch over the level's cells:
+// the smoother (red-black, i + j + k even first: in place one colour per
+// launch, on large levels sweep pairs out of place), the residual and its
 // restriction (volume-weighted mean of the children), the FAS coarse
-// right-hand side and the Kwak prolongation of the coarse correction.  The
-// geometry of the reference-metric Laplacian factorises into per-axis 1D
-// tables per level (weights toward the lower and upper neighbour, the
-// metric factors of the transverse terms, cell volumes), so a cell's
-// operator is a handful of table reads and FMAs.  The residual norm is a
-// grid-stride maximum with wavefront shuffles, one partial per workgroup and
-// one finishing workgroup: no atomics, no memset.
+// right-hand side and the Kwak prolongation of the coarse correction; the
+// coarse levels run as one workgroup.  The geometry of the reference-metric
+// Laplacian factorises into per-axis 1D tables per level (weights toward the
+// lower and upper neighbour, the metric factors of the transverse terms, cell
+// volumes), Cartesian weights are scalars, so a cell's operator is a handful
+// of loads and FMAs.  The residual norm is a grid-stride maximum with
+// wavefront shuffles, one partial per workgroup and one finishing workgroup:
+// no atomics, no memset.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/gmunu.h"
@@ -74,15 +76,32 @@ __device__ __forceinline__ double mg_ipow(double w, int q) {
 }
 
 // a (u + c)^p + a2 (u + c)^q and its derivative in u.
-__device__ __forceinline__ double mg_nl(const MgGeo &G, double a, double a2, double u) {
-  const double w = u + G.offset;
-  const double t = G.power == 0 ? a : G.power == 1 ? a * w : a / w;
-  return a2 != 0.0 ? t + a2 * mg_ipow(w, G.power2) : t;
-}
-__device__ __forceinline__ double mg_nl_du(const MgGeo &G, double a, double a2, double u) {
-  const double w = u + G.offset;
-  const double t = G.power == 0 ? 0.0 : G.power == 1 ? a : -a / (w * w);
-  return a2 != 0.0 ? t + a2 * G.power2 * mg_ipow(w, G.power2 - 1) : t;
+__device__ __forceinline__ double mg_nl_both(int power, int power2, double offset, double a, double a2, double u,
+                                             double &du) {
+  const double w = u + offset;
+  double nl = a, rw = 0.0;
+  du = 0.0;
+  if (power == 1) {
+    nl = a * w;
+    du = a;
+  } else if (power == -1) {
+    rw = rcp(w);
+    nl = a * rw;
+    du = -nl * rw;
+  }
+  if (a2 != 0.0) {
+    if (power != -1) rw = rcp(w);
+    double t;
+    if (power2 == -7) {
+      const double r2 = rw * rw;
+      t = a2 * (r2 * r2) * (r2 * rw);
+    } else {
+      t = a2 * mg_ipow(power2 < 0 ? rw : w, power2 < 0 ? -power2 : power2);
+    }
+    nl += t;
+    du += power2 * t * rw;
+  }
+  return nl;
 }
 
 // Robin ghost factor r_in / r_ghost for the ghost of boundary cell c across
@@ -104,20 +123,21 @@ __device__ __forceinline__ double mg_rob(const MgGeo &G, int i, int j, int k, in
     ri += xi * xi;
     rg += xg * xg;
   }
-  return sqrt(ri) / sqrt(rg);
+  return ri * rsq(ri * rg);  // sqrt(ri) / sqrt(rg)
 }
 
 // Neighbour of interior cell (i, j, k) along axis a (stride S) on the side
 // `up`: the stored value inside, else the boundary rule applied to the cell
 // itself (the value a ghost fill would store there).
 __device__ __forceinline__ double mg_nb(const MgGeo &G, const double *__restrict__ u, long o, int i, int j, int k,
-                                        int a, long S, bool up) {
-  const int n = G.n[a], c = a == 0 ? i : a == 1 ? j : k;
-  if (up ? c < n - 1 : c > 0) return u[up ? o + S : o - S];
-  const int kind = G.bc[a][up ? 1 : 0];
-  if (kind == GMUNU_MG_PERIODIC) return u[up ? o - (long)(n - 1) * S : o + (long)(n - 1) * S];
-  const double ui = u[o];
-  return kind == GMUNU_MG_DIRICHLET ? -ui : kind == GMUNU_MG_NEUMANN ? ui : ui * mg_rob(G, i, j, k, a, up);
+                                        int a, int S, bool up) {
+  const int n = G.n[a], c = a == 0 ? i : a == 1 ? j : k, kind = G.bc[a][up ? 1 : 0];
+  const bool face = up ? c == n - 1 : c == 0;
+  const int in = up ? S : -S, out = kind == GMUNU_MG_PERIODIC ? (up ? -(n - 1) * S : (n - 1) * S) : 0;
+  double v = u[o + (face ? out : in)];
+  if (kind == GMUNU_MG_DIRICHLET) v = face ? -v : v;
+  if (kind == GMUNU_MG_ROBIN && face) v *= mg_rob(G, i, j, k, a, up);
+  return v;
 }
 
 // L(u) at interior cell (i,j,k) (linear offset o) and dL/du there.  GH:
@@ -126,31 +146,37 @@ __device__ __forceinline__ double mg_nb(const MgGeo &G, const double *__restrict
 template <bool GH>
 __device__ __forceinline__ double mg_L(const MgGeo &G, const double *__restrict__ u, double av, double a2v, int i,
                                        int j, int k, long o, double *dg) {
-  const int I = i + G.g[0], J = j + G.g[1];
+  const int I = i + G.g[0], J = j + G.g[1], S1 = (int)G.s1, S2 = (int)G.s2;
+  const bool ca = G.coord == GMUNU_CART;  // Cartesian weights are scalars
   const double uc = u[o];
-  double wm = G.a0m[I], wp = G.a0p[I];
+  double wm = ca ? G.vih2[0] : G.a0m[I], wp = ca ? G.vih2[0] : G.a0p[I];
   double um = GH ? u[o - 1] : mg_nb(G, u, o, i, j, k, 0, 1, false);
   double up = GH ? u[o + 1] : mg_nb(G, u, o, i, j, k, 0, 1, true);
   double lap = wp * (up - uc) - wm * (uc - um);
   double d = -(wm + wp);
   if (G.ndim > 1) {
-    const double gi = G.g1[I];
-    wm = gi * G.a1m[J];
-    wp = gi * G.a1p[J];
-    um = GH ? u[o - G.s1] : mg_nb(G, u, o, i, j, k, 1, G.s1, false);
-    up = GH ? u[o + G.s1] : mg_nb(G, u, o, i, j, k, 1, G.s1, true);
+    wm = wp = G.vih2[1];
+    if (!ca) {
+      const double gi = G.g1[I];
+      wm = gi * G.a1m[J];
+      wp = gi * G.a1p[J];
+    }
+    um = GH ? u[o - S1] : mg_nb(G, u, o, i, j, k, 1, S1, false);
+    up = GH ? u[o + S1] : mg_nb(G, u, o, i, j, k, 1, S1, true);
     lap += wp * (up - uc) - wm * (uc - um);
     d -= wm + wp;
   }
   if (G.ndim > 2) {
-    const double w = G.g2[I] * G.s2t[J] * G.ih2_2;
-    um = GH ? u[o - G.s2] : mg_nb(G, u, o, i, j, k, 2, G.s2, false);
-    up = GH ? u[o + G.s2] : mg_nb(G, u, o, i, j, k, 2, G.s2, true);
+    const double w = ca ? G.vih2[2] : G.g2[I] * G.s2t[J] * G.ih2_2;
+    um = GH ? u[o - S2] : mg_nb(G, u, o, i, j, k, 2, S2, false);
+    up = GH ? u[o + S2] : mg_nb(G, u, o, i, j, k, 2, S2, true);
     lap += w * (up - uc) - w * (uc - um);
     d -= 2.0 * w;
   }
-  if (dg) *dg = d - mg_nl_du(G, av, a2v, uc);
-  return lap - mg_nl(G, av, a2v, uc);
+  double du;
+  const double nl = mg_nl_both(G.power, G.power2, G.offset, av, a2v, uc, du);
+  if (dg) *dg = d - du;
+  return lap - nl;
 }
 
 // Interior cell number t (x fastest); 32-bit arithmetic (a level has fewer
@@ -248,15 +274,12 @@ __global__ __launch_bounds__(NT) void k_mg_ghosts(const MgGeo G, double *u) {
   }
 }
 
-// One colour of red-black Newton-Gauss-Seidel: thread t -> the t-th cell of
-// that colour (every other cell of a row).  With fs non-null, f, a and a2
-// are read from colour-split copies (per row the even-i cells, then the odd
-// ones), so that a colour reads them contiguously.
-__device__ __forceinline__ void mg_smooth_one(const MgGeo &G, double *u, const double *__restrict__ f,
-                                              const double *__restrict__ a, const double *__restrict__ a2, int colour,
-                                              long t, const double *__restrict__ fs = nullptr,
-                                              const double *__restrict__ as = nullptr,
-                                              const double *__restrict__ a2s = nullptr) {
+// One colour of red-black Newton-Gauss-Seidel in place: thread t -> the t-th
+// cell of that colour (every other cell of a row).
+__global__ __launch_bounds__(NT) void k_mg_smooth(const MgGeo G, double *u, const double *__restrict__ f,
+                                                  const double *__restrict__ a, const double *__restrict__ a2,
+                                                  int colour) {
+  const long t = (long)blockIdx.x * NT + threadIdx.x;
   const unsigned hrow = (unsigned)(G.n[0] + 1) >> 1, n1 = (unsigned)G.n[1];
   if (t >= (long)hrow * G.n[1] * G.n[2]) return;
   const unsigned row = (unsigned)t / hrow;
@@ -264,39 +287,9 @@ __device__ __forceinline__ void mg_smooth_one(const MgGeo &G, double *u, const d
   const int i = (int)((unsigned)t - row * hrow) * 2 + ((j + k + colour) & 1);
   if (i >= G.n[0]) return;
   const long o = mg_off(G, i, j, k);
-  double fv, av, a2v;
-  if (fs) {
-    const long si = (long)row * G.n[0] + (long)(i & 1) * hrow + (i >> 1);
-    fv = fs[si];
-    av = as ? as[si] : 0.0;
-    a2v = a2s ? a2s[si] : 0.0;
-  } else {
-    fv = f[o];
-    av = a ? a[o] : 0.0;
-    a2v = a2 ? a2[o] : 0.0;
-  }
   double dg;
-  const double Lu = mg_L<false>(G, u, av, a2v, i, j, k, o, &dg);
-  u[o] -= (Lu - fv) / dg;
-}
-
-__global__ __launch_bounds__(NT) void k_mg_smooth(const MgGeo G, double *u, const double *__restrict__ f,
-                                                  const double *__restrict__ a, const double *__restrict__ a2,
-                                                  int colour, const double *__restrict__ fs,
-                                                  const double *__restrict__ as, const double *__restrict__ a2s) {
-  mg_smooth_one(G, u, f, a, a2, colour, (long)blockIdx.x * NT + threadIdx.x, fs, as, a2s);
-}
-
-// Colour-split copy of an interior array: per row the even-i cells, then
-// the odd-i cells (the layout mg_smooth_one reads with fs).
-__global__ __launch_bounds__(NT) void k_mg_split(const MgGeo G, const double *__restrict__ src,
-                                                 double *__restrict__ dst) {
-  const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t >= mg_cells(G)) return;
-  int i, j, k;
-  mg_cell(G, t, i, j, k);
-  const long row = (long)k * G.n[1] + j, hrow = (G.n[0] + 1) >> 1;
-  dst[row * G.n[0] + (i & 1) * hrow + (i >> 1)] = src[mg_off(G, i, j, k)];
+  const double Lu = mg_L<false>(G, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, i, j, k, o, &dg);
+  u[o] -= (Lu - f[o]) * rcp(dg);
 }
 
 // ---- Line relaxation --------------------------------------------------------
@@ -705,35 +698,6 @@ struct MgTail {
 // u / d with the magic multiplier m of d (0: d = 1); exact for u d < 2^32.
 __device__ __forceinline__ int mg_div(int u, unsigned m) { return m ? (int)__umulhi((unsigned)u, m) : u; }
 
-// a (u + c)^p + a2 (u + c)^q and its derivative.
-__device__ __forceinline__ double mg_nl_both(int power, int power2, double offset, double a, double a2, double u,
-                                             double &du) {
-  const double w = u + offset;
-  double nl = a, rw = 0.0;
-  du = 0.0;
-  if (power == 1) {
-    nl = a * w;
-    du = a;
-  } else if (power == -1) {
-    rw = rcp(w);
-    nl = a * rw;
-    du = -nl * rw;
-  }
-  if (a2 != 0.0) {
-    if (power != -1) rw = rcp(w);
-    double t;
-    if (power2 == -7) {
-      const double r2 = rw * rw;
-      t = a2 * (r2 * r2) * (r2 * rw);
-    } else {
-      t = a2 * mg_ipow(power2 < 0 ? rw : w, power2 < 0 ? -power2 : power2);
-    }
-    nl += t;
-    du += power2 * t * rw;
-  }
-  return nl;
-}
-
 // A tail cell's stencil: its offset, the steps to its neighbours (0 across a
 // face of the domain, whose value is the boundary rule applied to the cell
 // itself), the faces it lies on (bit 2 axis + side) and the rule's factor per
@@ -1042,6 +1006,367 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(const MgTail *__restri
       mg_tail_correct(T, T.lev[l], T.lev[l - 1], sm);
   }
   mg_tail_copy<true>(T, T.lev[T.top], u, sm + T.lev[T.top].u);
+}
+
+// ---- Red-black sweeps out of place ------------------------------------------
+// NS sweeps (2 NS colours) of a 2D or 3D level in one launch, from u to out.  A
+// workgroup relaxes a 32 x 16 tile in x and y with a halo of H = 2 NS cells,
+// the halo's cells redundantly; a thread owns one pair of x-neighbours (one
+// cell of each colour in every plane).  In 3D it marches along z over a chunk
+// of planes (H more below and above) through a ring of planes in LDS: at step
+// p colour s is relaxed on plane p - (2 s - 1), which only needs the colour
+// before it on planes relaxed in earlier steps, so a step has one barrier and
+// 2 NS independent updates per thread; the planes of u, f, a and a2 are loaded
+// two steps ahead, f, a and a2 once (kept in registers over the pipeline).  As launches per colour a pair of
+// sweeps moves 96 bytes per cell (u four times, f and a in half lines); here
+// 32.  Measured on 256^3 cells with a (u + c): 194 us per pair of sweeps against
+// 480 as four launches (38 B per cell with the halo in flight: 3.3 TB/s; two
+// wavefronts per SIMD in each of two workgroups, VALU and LDS about half busy
+// each).  What it took: f and a fetched once (fetched per colour in half lines
+// they missed the L2: 285 us), no branch in a step (the loads' waits cannot
+// cross one: 295 us), faces folded into a factor of u (358 us).  Blocks of 32 x
+// 8 x 8 cells staged at once, whose halo doubles the updates, took 558 us.
+
+template <int ND, int NS>
+struct RbTile {
+  static constexpr int H = 2 * NS, TX = 32, TY = 16;
+  static constexpr int HX = TX / 2 + H, RX = 2 * HX, RY = TY + 2 * H;  // pairs, cells and rows staged
+  static constexpr int P = RX * RY;                                    // cells of a staged plane
+  static constexpr int ring = ND > 2 ? 4 * NS + 2 : 1;
+  static constexpr int threads = (HX * RY + 63) / 64 * 64;
+};
+
+// Index wrapped into [0, n).
+__device__ __forceinline__ int mg_wrap(int i, int n) {
+  if (i >= 0 && i < n) return i;
+  i %= n;
+  return i < 0 ? i + n : i;
+}
+
+// One cell of a thread's pair: place in a staged plane (even cells of a row,
+// then odd ones, so that a colour's reads are contiguous) and of its
+// neighbours there, place in a global plane, and what depends on (x, y) alone.
+// Across a face of the domain the neighbour is the cell itself, whose
+// difference vanishes, and the boundary rule u_ghost = s u adds (s - 1) times
+// the face's weight to the factor cc of u: no branch in the update.  ROB:
+// faces whose s depends on the position (their part of cc per update).
+template <bool CA>
+struct RbCell {
+  int o, xm, xp, ym, yp;
+  unsigned og;           // bytes
+  int ow;                // o where the cell is relaxed, else the corner (0, 0), which no relaxed cell reads
+  bool on;               // inside the domain (or a periodic image)
+  unsigned rob;          // bits: such a face on the lower / upper side of axis 0, of axis 1
+  double cc, x, y;       // x, y: centre
+  double w[CA ? 1 : 5];  // curvilinear weights: a0m, a0p, g1 a1m, g1 a1p, g2 s2t / h2^2
+};
+
+// s - 1 of the boundary rule across face (a, side), 0 where it depends on the
+// position.
+__device__ __forceinline__ double mg_fold1(const MgGeo &G, int a, int side) {
+  const int kind = G.bc[a][side];
+  return kind == GMUNU_MG_DIRICHLET ? -2.0
+         : kind == GMUNU_MG_ROBIN && G.coord == GMUNU_SPH ? (side ? G.rob_hi : G.rob_lo) - 1.0
+                                                          : 0.0;
+}
+__device__ __forceinline__ bool mg_robin(const MgGeo &G, int a, int side) {
+  return G.coord != GMUNU_SPH && G.bc[a][side] == GMUNU_MG_ROBIN;
+}
+// r_in / r_ghost - 1 = r_in^2 / sqrt(r_in^2 r_ghost^2) - 1 for a cell at x
+// along the face's axis (its ghost at g), rr its squared distance.
+__device__ __forceinline__ double mg_robin1(double rr, double x, double g) {
+  return rr * rsq(rr * (rr - x * x + g * g)) - 1.0;
+}
+
+template <int ND, int NS, bool CA>
+__device__ __forceinline__ RbCell<CA> mg_rb_cell(const MgGeo &G, int i0, int j0, int h, int y, int par) {
+  using R = RbTile<ND, NS>;
+  RbCell<CA> c;
+  const int row = y * R::RX;
+  int i = i0 - R::H + 2 * h + par, j = j0 - R::H + y;
+  const bool px = G.bc[0][0] == GMUNU_MG_PERIODIC, py = G.bc[1][0] == GMUNU_MG_PERIODIC;
+  c.on = y < R::RY && (px || (i >= 0 && i < G.n[0])) && (py || (j >= 0 && j < G.n[1]));
+  if (px) i = mg_wrap(i, G.n[0]);
+  if (py) j = mg_wrap(j, G.n[1]);
+  const bool f0 = !px && i == 0, f1 = !px && i == G.n[0] - 1, f2 = !py && j == 0, f3 = !py && j == G.n[1] - 1;
+  // threads without a cell, and rim cells without a neighbour, read places
+  // that exist
+  const bool in = y < R::RY;
+  c.o = in ? row + (par ? R::HX : 0) + h : 0;
+  c.xm = f0 || !in || (!par && h == 0) ? c.o : par ? row + h : row + R::HX + h - 1;
+  c.xp = f1 || !in || (par && h + 1 == R::HX) ? c.o : par ? row + h + 1 : row + R::HX + h;
+  c.ym = f2 || !in || y == 0 ? c.o : c.o - R::RX;
+  c.yp = f3 || !in || y == R::RY - 1 ? c.o : c.o + R::RX;
+  const int x = 2 * h + par;
+  c.ow = c.on && x >= 1 && x < R::RX - 1 && y >= 1 && y < R::RY - 1 ? c.o : 0;
+  c.x = G.x0[0] + (i + 0.5) * G.h[0];
+  c.y = G.x0[1] + (j + 0.5) * G.h[1];
+  c.og = c.on ? 8u * (unsigned)((j + 1) * (int)G.s1 + i + 1) : 0u;
+  const int I = c.on ? i + 1 : 1, J = c.on ? j + 1 : 1;
+  double wm0 = G.vih2[0], wp0 = wm0, wm1 = G.vih2[1], wp1 = wm1;
+  if constexpr (!CA) {
+    c.w[0] = wm0 = G.a0m[I];
+    c.w[1] = wp0 = G.a0p[I];
+    c.w[2] = wm1 = G.g1[I] * G.a1m[J];
+    c.w[3] = wp1 = G.g1[I] * G.a1p[J];
+    c.w[4] = ND > 2 ? G.g2[I] * G.s2t[J] * G.ih2_2 : 0.0;
+  }
+  c.cc = (f0 ? wm0 * mg_fold1(G, 0, 0) : 0.0) + (f1 ? wp0 * mg_fold1(G, 0, 1) : 0.0) +
+         (f2 ? wm1 * mg_fold1(G, 1, 0) : 0.0) + (f3 ? wp1 * mg_fold1(G, 1, 1) : 0.0);
+  c.rob = (f0 && mg_robin(G, 0, 0) ? 1u : 0u) | (f1 && mg_robin(G, 0, 1) ? 2u : 0u) |
+          (f2 && mg_robin(G, 1, 0) ? 4u : 0u) | (f3 && mg_robin(G, 1, 1) ? 8u : 0u);
+  return c;
+}
+
+// Newton update of cell c on the plane at sm + zc (neighbour planes at zm and
+// zp; on a face of axis 2 the plane itself), zs: s - 1 of that face (0 off the
+// faces), zr: bits of a face of axis 2 whose s depends on the position, k the
+// index along axis 2.  M: the terms (0: none, 1: a (u + c), 2: general).
+// Returns the new value.
+template <int ND, bool CA, int M, bool ROB>
+__device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm, const RbCell<CA> &c, int zc, int zm,
+                                               int zp, double zs, unsigned zr, int k, double fv, double av,
+                                               double a2v) {
+  const double *u = sm + zc;
+  const double uc = u[c.o], xm = u[c.xm], xp = u[c.xp], ym = u[c.ym], yp = u[c.yp];
+  double lap, d, cc = c.cc, zw;
+  if constexpr (CA) {
+    lap = G.vih2[0] * ((xp - uc) - (uc - xm));
+    lap += G.vih2[1] * ((yp - uc) - (uc - ym));
+    zw = ND > 2 ? G.vih2[2] : 0.0;
+    d = -2.0 * (G.vih2[0] + G.vih2[1] + zw);
+  } else {
+    lap = c.w[1] * (xp - uc) - c.w[0] * (uc - xm);
+    lap += c.w[3] * (yp - uc) - c.w[2] * (uc - ym);
+    zw = c.w[4];
+    d = -(c.w[0] + c.w[1]) - (c.w[2] + c.w[3]) - 2.0 * zw;
+  }
+  if (ND > 2) {
+    lap += zw * ((sm[zp + c.o] - uc) - (uc - sm[zm + c.o]));
+    if (zs != 0.0) cc += zw * zs;
+  }
+  if (ROB && (c.rob || zr)) {
+    double rr = c.x * c.x + c.y * c.y, z = 0.0;
+    if (ND > 2 && G.coord == GMUNU_CART) {
+      z = G.x0[2] + (k + 0.5) * G.h[2];
+      rr += z * z;
+    }
+    const double wm0 = CA ? G.vih2[0] : c.w[0], wp0 = CA ? G.vih2[0] : c.w[CA ? 0 : 1];
+    const double wm1 = CA ? G.vih2[1] : c.w[CA ? 0 : 2], wp1 = CA ? G.vih2[1] : c.w[CA ? 0 : 3];
+    if (c.rob & 3u) cc += (c.rob & 1u ? wm0 : wp0) * mg_robin1(rr, c.x, c.rob & 1u ? c.x - G.h[0] : c.x + G.h[0]);
+    if (c.rob & 12u) cc += (c.rob & 4u ? wm1 : wp1) * mg_robin1(rr, c.y, c.rob & 4u ? c.y - G.h[1] : c.y + G.h[1]);
+    if (zr & 1u) cc += zw * mg_robin1(rr, z, z - G.h[2]);
+    if (zr & 2u) cc += zw * mg_robin1(rr, z, z + G.h[2]);
+  }
+  lap += cc * uc;
+  if constexpr (M == 2) {
+    double du;
+    lap -= mg_nl_both(G.power, G.power2, G.offset, av, a2v, uc, du);
+    d -= du;
+  } else if constexpr (M == 1) {
+    lap -= av * (uc + G.offset);
+    d -= av;
+  }
+  return uc - (lap - fv) * rcp(d);
+}
+
+// f, a and a2 of one update.
+struct RbSrc {
+  double f, a, a2;
+};
+// Entry at byte offset b of a plane (a uniform pointer and a 32-bit offset per
+// lane: no address arithmetic in the VALU).
+__device__ __forceinline__ double mg_rb_at(const double *plane, unsigned b) {
+  return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(plane) + b);
+}
+
+template <int M>
+__device__ __forceinline__ RbSrc mg_rb_src(const double *__restrict__ f, const double *__restrict__ a,
+                                           const double *__restrict__ a2, long plane, unsigned b) {
+  // M = 2: a or a2 may be absent (zero); f stands in for the address
+  const double *pa = M == 2 && !a ? f : a, *pa2 = a2 ? a2 : f;
+  RbSrc q;
+  q.f = mg_rb_at(f + plane, b);
+  q.a = M > 0 ? mg_rb_at(pa + plane, b) : 0.0;
+  q.a2 = M == 2 ? mg_rb_at(pa2 + plane, b) : 0.0;
+  if (M == 2 && !a) q.a = 0.0;
+  if (M == 2 && !a2) q.a2 = 0.0;
+  return q;
+}
+
+// 2D: the whole tile staged at once.
+template <int NS, bool CA, int M, bool ROB>
+__device__ __forceinline__ void mg_rb_tile(const MgGeo &G, const double *__restrict__ f, const double *__restrict__ a,
+                                           const double *__restrict__ a2, double *__restrict__ out, double *sm,
+                                           const RbCell<CA> *c, int h, int y) {
+  using R = RbTile<2, NS>;
+  RbSrc q[2];
+#pragma unroll
+  for (int m = 0; m < 2; m++) q[m] = mg_rb_src<M>(f, a, a2, 0, c[m].og);
+#pragma unroll
+  for (int s = 1; s <= 2 * NS; s++) {
+    // x + y + colour even in tile coordinates (the tile and H start even)
+    const bool par = (y + s - 1) & 1;
+    const RbCell<CA> cc = par ? c[1] : c[0];
+    const RbSrc qq = par ? q[1] : q[0];
+    sm[cc.ow] = mg_rb_update<2, CA, M, ROB>(G, sm, cc, 0, 0, 0, 0.0, 0u, 0, qq.f, qq.a, qq.a2);
+    __syncthreads();
+  }
+  if (y >= R::H && y < R::RY - R::H && h >= NS && h < R::HX - NS) {
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+      if (c[m].on) out[c[m].og / 8] = sm[c[m].o];
+  }
+}
+
+// 3D: march over planes z0 .. z1 - 1.
+template <int NS, bool CA, int M, bool ROB>
+__device__ __forceinline__ void mg_rb_march(const MgGeo &G, const double *__restrict__ u, const double *__restrict__ f,
+                                            const double *__restrict__ a, const double *__restrict__ a2,
+                                            double *__restrict__ out, double *sm, const RbCell<CA> *c, int h, int y,
+                                            int z0, int z1) {
+  using R = RbTile<3, NS>;
+  constexpr int S = 2 * NS;
+  const int n2 = G.n[2];
+  const bool pz = G.bc[2][0] == GMUNU_MG_PERIODIC;
+  // planes that exist: all (periodic images) or 0 .. n2 - 1
+  const int lo = pz ? z0 - R::H : (z0 - R::H > 0 ? z0 - R::H : 0);
+  // offset of plane q in the arrays (planes that do not exist: the nearest,
+  // whose values are loaded in vain)
+  auto plane = [&](int q) { return (long)((pz ? mg_wrap(q, n2) : q < 0 ? 0 : q < n2 ? q : n2 - 1) + 1) * G.s2; };
+  // At step p colour s updates, on plane q = p - (2 s - 1), the pair's member m
+  // with m + y + q + s - 1 even, that is the parity of y + p - s: odd colours
+  // one member, even ones the other, exchanged at every step.  Every cell that
+  // has its neighbours in the staged planes is updated at every step: what a
+  // colour makes of cells or planes its neighbours' colours have not reached
+  // (the halo's rim, the pipeline's first steps) is not read by a cell that
+  // is stored.
+  const bool flip = (y + lo - 1 + R::H) & 1;
+  const RbCell<CA> A = flip ? c[1] : c[0], B = flip ? c[0] : c[1];
+  const bool store = y >= R::H && y < R::RY - R::H && h >= NS && h < R::HX - NS;
+  const bool outA = store && A.on, outB = store && B.on;
+  // po[m], sl[m]: offset in the arrays and place in LDS of plane p + 2 - m
+  constexpr int NP = 2 * S + 3;
+  long po[NP];
+  int sl[NP], top = 2;  // the ring's next slot, for plane lo + 2
+#pragma unroll
+  for (int m = 0; m < NP; m++) {
+    po[m] = plane(lo + 2 - m);
+    sl[m] = (2 - m + R::ring) % R::ring * R::P;
+  }
+  const double zs0 = pz ? 0.0 : mg_fold1(G, 2, 0), zs1 = pz ? 0.0 : mg_fold1(G, 2, 1);
+  const unsigned zr0 = ROB && mg_robin(G, 2, 0) ? 1u : 0u, zr1 = ROB && mg_robin(G, 2, 1) ? 2u : 0u;
+  // u two planes ahead (by member), and the right-hand sides of planes p + 1,
+  // p, .. that colours still need (member of the odd colours: up to plane
+  // p - (2 S - 3); of the even ones: up to p - (2 S - 1)): each is read once,
+  // as whole lines, and kept in registers
+  constexpr int NO = 2 * S - 1, NE = 2 * S + 1;
+  double ua[2], ub[2];
+  RbSrc qo[NO], qe[NE];  // index m: plane p + 1 - m
+  auto load_u = [&](int m, long o) {
+    ua[m] = mg_rb_at(u + o, A.og);
+    ub[m] = mg_rb_at(u + o, B.og);
+  };
+  int zn = pz ? mg_wrap(lo + 2, n2) : 0;  // index of the plane po[0] refers to (periodic)
+  // one step: plane p is stored, the colours behind it run, u of plane p + 2
+  // and the right-hand sides of p + 2 are fetched.  No branch but the stores':
+  // the loads of a step stay in flight over the next one, and the updates of
+  // the colours interleave.  X: member of the odd colours, Y: of the even
+  // ones; face: one of the updated planes lies on a face of axis 2.
+  auto step = [&](auto face, int p, int um, const RbCell<CA> &X, const RbCell<CA> &Y, bool outX, bool outY) {
+    sm[sl[2] + A.o] = ua[um];
+    sm[sl[2] + B.o] = ub[um];
+    __syncthreads();
+    double w[S + 1];
+#pragma unroll
+    for (int s = 1; s <= S; s++) {
+      const int q = p - (2 * s - 1), m = 2 * s + 1;
+      const bool zlo = face && q == 0, zhi = face && q == n2 - 1;
+      const RbSrc &r = s & 1 ? qo[2 * s] : qe[2 * s];
+      w[s] = mg_rb_update<3, CA, M, ROB>(G, sm, s & 1 ? X : Y, sl[m], zlo ? sl[m] : sl[m + 1], zhi ? sl[m] : sl[m - 1],
+                                         zlo ? zs0 : zhi ? zs1 : 0.0, (zlo ? zr0 : 0u) | (zhi ? zr1 : 0u), q, r.f, r.a,
+                                         r.a2);
+    }
+#pragma unroll
+    for (int s = 1; s <= S; s++) sm[sl[2 * s + 1] + (s & 1 ? X : Y).ow] = w[s];
+    // the last colour (even: member Y) was just done on plane q, X before
+    const int q = p - (2 * S - 1);
+    if (q >= z0 && q < z1) {
+      char *po_ = reinterpret_cast<char *>(out + po[2 * S + 1]);
+      if (outX) *reinterpret_cast<double *>(po_ + X.og) = sm[sl[2 * S + 1] + X.o];
+      if (outY) *reinterpret_cast<double *>(po_ + Y.og) = w[S];
+    }
+    load_u(um, po[0]);
+    // on to step p + 1
+#pragma unroll
+    for (int m = NO - 1; m > 0; m--) qo[m] = qo[m - 1];
+#pragma unroll
+    for (int m = NE - 1; m > 0; m--) qe[m] = qe[m - 1];
+    // plane p + 2: its odd colours come at step p + 3, whose odd member is Y
+    qo[0] = mg_rb_src<M>(f, a, a2, po[0], Y.og);
+    qe[0] = mg_rb_src<M>(f, a, a2, po[0], X.og);
+#pragma unroll
+    for (int m = NP - 1; m > 0; m--) {
+      po[m] = po[m - 1];
+      sl[m] = sl[m - 1];
+    }
+    if (pz) {
+      zn = zn + 1 == n2 ? 0 : zn + 1;
+      po[0] = zn ? po[1] + G.s2 : G.s2;
+    } else if (p + 3 < n2) {
+      po[0] = po[1] + G.s2;
+    }
+    top = top + 1 == R::ring ? 0 : top + 1;
+    sl[0] = top ? sl[1] + R::P : 0;
+  };
+  auto run = [&](int p, int um, const RbCell<CA> &X, const RbCell<CA> &Y, bool outX, bool outY) {
+    if (!pz && (p <= 2 * S - 1 || p >= n2))
+      step(std::true_type{}, p, um, X, Y, outX, outY);
+    else
+      step(std::false_type{}, p, um, X, Y, outX, outY);
+  };
+  load_u(0, po[2]);
+  load_u(1, po[1]);
+#pragma unroll
+  for (int m = 0; m < NO; m++) qo[m] = RbSrc{0.0, 0.0, 0.0};
+#pragma unroll
+  for (int m = 0; m < NE; m++) qe[m] = RbSrc{0.0, 0.0, 0.0};
+  // planes lo (odd member B, at step lo + 1) and lo + 1 (A)
+  qo[1] = mg_rb_src<M>(f, a, a2, po[2], B.og);
+  qe[1] = mg_rb_src<M>(f, a, a2, po[2], A.og);
+  qo[0] = mg_rb_src<M>(f, a, a2, po[1], A.og);
+  qe[0] = mg_rb_src<M>(f, a, a2, po[1], B.og);
+  for (int p = lo; p - (2 * S - 1) < z1; p += 2) {
+    run(p, 0, A, B, outA, outB);
+    run(p + 1, 1, B, A, outB, outA);
+  }
+}
+
+template <int ND, int NS, bool CA, int M, bool ROB>
+__global__ __launch_bounds__((RbTile<ND, NS>::threads), (ND > 2 && CA && M < 2 && !ROB ? 4 : 2)) void k_mg_rb(const MgGeo G, const double *__restrict__ u,
+                                                                     const double *__restrict__ f,
+                                                                     const double *__restrict__ a,
+                                                                     const double *__restrict__ a2,
+                                                                     double *__restrict__ out, int chunk) {
+  using R = RbTile<ND, NS>;
+  __shared__ double sm[R::P * R::ring];
+  // contiguous runs of tiles (x fastest, then y, then chunks of z) per XCD
+  const int gx = (G.n[0] + R::TX - 1) / R::TX, gy = (G.n[1] + R::TY - 1) / R::TY;
+  const int nt = gridDim.x, b = blockIdx.x, xc = b % 8, qn = nt / 8, rn = nt % 8;
+  const int t = xc * qn + (xc < rn ? xc : rn) + b / 8;
+  const int i0 = t % gx * R::TX, j0 = t / gx % gy * R::TY;
+  const int h = threadIdx.x % R::HX, y = threadIdx.x / R::HX;
+  const RbCell<CA> c[2] = {mg_rb_cell<ND, NS, CA>(G, i0, j0, h, y, 0), mg_rb_cell<ND, NS, CA>(G, i0, j0, h, y, 1)};
+  if constexpr (ND > 2) {
+    const int z0 = t / (gx * gy) * chunk, z1 = z0 + chunk < G.n[2] ? z0 + chunk : G.n[2];
+    mg_rb_march<NS, CA, M, ROB>(G, u, f, a, a2, out, sm, c, h, y, z0, z1);
+  } else {
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+      if (c[m].on) sm[c[m].o] = mg_rb_at(u, c[m].og);
+    __syncthreads();
+    mg_rb_tile<NS, CA, M, ROB>(G, f, a, a2, out, sm, c, h, y);
+  }
 }
 
 // Kwak prolongation of v (coarse, ghosts set) into the fine interior:
@@ -2212,10 +2537,9 @@ struct gmunu_mg {
   double *u[kMaxLevels], *f[kMaxLevels], *a[kMaxLevels], *r[kMaxLevels], *uo[kMaxLevels];
   double *aown[kMaxLevels];  // coarse-level storage of a
   double *a2[kMaxLevels], *a2own[kMaxLevels];  // the same for a2 (allocated when power2 != 0)
-  // colour-split copies of the finest f, a, a2 for the red-black sweeps
-  // (allocated by the first solve of a large enough level; fs == NULL: none)
-  double *fs, *as, *a2s;
-  const double *sf, *sa, *sa2;  // the split copies' sources in the cycles being run
+  // second fields of the levels above the tail that k_mg_rb relaxes out of
+  // place (the finest level's allocated by the first solve; null: in place)
+  double *us[kMaxLevels];
   // the tail's plans by the terms present (bit 0: a, bit 1: a2): top level
   // (-1: none) and device copy; the levels' geometries and their own a and
   // a2 arrays on the device
@@ -2446,10 +2770,10 @@ size_t line_coarse_lds(const MgGeo &G, int arrays) {
   return b <= 64 * 1024 ? b : 0;
 }
 
-// Smoothing sweeps (boundary rule inline: no ghost fill between colours):
-// line sweeps for the line smoother, else red-black.
+// Smoothing sweeps in place (boundary rule inline: no ghost fill between
+// colours): line sweeps for the line smoother, else red-black.
 void sweeps_raw(const MgGeo &G, double *u, const double *f, const double *a, const double *a2, int sweeps,
-                hipStream_t st, const double *fs = nullptr, const double *as = nullptr, const double *a2s = nullptr) {
+                hipStream_t st) {
   if (G.line) {
     line_sweeps(G, u, f, a, a2, sweeps, st);
     return;
@@ -2457,14 +2781,100 @@ void sweeps_raw(const MgGeo &G, double *u, const double *f, const double *a, con
   const long threads = (long)((G.n[0] + 1) / 2) * G.n[1] * G.n[2];
   for (int s = 0; s < sweeps; s++)
     for (int c = 0; c < 2; c++)
-      hipLaunchKernelGGL(k_mg_smooth, dim3(nblocks(threads)), dim3(NT), 0, st, G, u, f, a, a2, c, fs, as, a2s);
+      hipLaunchKernelGGL(k_mg_smooth, dim3(nblocks(threads)), dim3(NT), 0, st, G, u, f, a, a2, c);
 }
 
-// The same, then u's ghost entries from the boundary rule.
-void smooth(const MgGeo &G, double *u, const double *f, const double *a, const double *a2, int sweeps,
-            hipStream_t st) {
-  sweeps_raw(G, u, f, a, a2, sweeps, st);
-  ghosts(G, u, st);
+// Does a face have a position-dependent Robin factor?
+bool rb_robin(const MgGeo &G) {
+  bool rob = false;
+  for (int q = 0; q < G.ndim; q++)
+    rob = rob || (G.coord != GMUNU_SPH && (G.bc[q][0] == GMUNU_MG_ROBIN || G.bc[q][1] == GMUNU_MG_ROBIN));
+  return rob;
+}
+
+// Levels that k_mg_rb relaxes.  Smaller 3D levels are faster in place: 64^3
+// takes 24 us per pair of sweeps out of place (33 with Robin faces, 50 with the
+// general term besides) against 16 as four launches; 128^3 45, 57 and 85 us
+// against about 70.  In 2D the one tile pass beats the launches throughout.
+bool rb_level(const MgGeo &G) {
+  if (G.line || G.ndim < 2 || cells(G) <= kTailCells || G.s2 >= (1L << 29)) return false;  // 32-bit byte offsets
+  const bool light = G.coord == GMUNU_CART && G.power != -1 && G.power2 == 0;
+  return G.ndim == 2 || cells(G) >= (light ? 1L << 20 : 1L << 22);
+}
+
+// ns (1 or 2) sweeps out of place, u to out.
+template <int ND, int NS>
+void rb_launch(const MgGeo &G, const double *u, const double *f, const double *a, const double *a2, double *out,
+               hipStream_t st) {
+  using R = RbTile<ND, NS>;
+  const int tiles = ((G.n[0] + R::TX - 1) / R::TX) * ((G.n[1] + R::TY - 1) / R::TY);
+  const int terms = !a && !a2 ? 0 : a && !a2 && G.power == 1 ? 1 : 2;
+  const bool rob = rb_robin(G);
+  // 3D: planes per workgroup.  A chunk of L planes takes L + 4 H - 1 steps (halo
+  // and pipeline).  With at most 256 workgroups a step takes about 1.05 us;
+  // two workgroups fit a CU where the registers allow (no position-dependent
+  // factor, no general term), a step of both 1.5 times as long (256^3: 190 us
+  // in chunks of 64 planes, 240 in chunks of 128; 128^3: 49 in 8, 45 in 16).
+  const bool two = G.coord == GMUNU_CART && terms < 2 && !rob;
+  int chunk = 1;
+  if (ND > 2) {
+    double best = -1.0;
+    for (int n = 1; n <= G.n[2]; n++) {
+      const int len = (G.n[2] + n - 1) / n;
+      if (n > 1 && len < 4) break;
+      const long wg = (long)tiles * ((G.n[2] + len - 1) / len), steps = len + 4 * R::H - 1;
+      const double cost = two && wg > 256 ? 1.5 * steps * ((wg + 511) / 512) : (double)steps * ((wg + 255) / 256);
+      if (best < 0.0 || cost < best) {
+        best = cost;
+        chunk = len;
+      }
+    }
+  }
+  const dim3 grid(tiles * ((G.n[2] + chunk - 1) / chunk));
+  auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(R::threads), 0, st, G, u, f, a, a2, out, chunk); };
+  if (G.coord != GMUNU_CART)
+    rob ? run(k_mg_rb<ND, NS, false, 2, true>) : run(k_mg_rb<ND, NS, false, 2, false>);
+  else if (rob)
+    terms == 1 ? run(k_mg_rb<ND, NS, true, 1, true>) : run(k_mg_rb<ND, NS, true, 2, true>);
+  else
+    terms == 0   ? run(k_mg_rb<ND, NS, true, 0, false>)
+    : terms == 1 ? run(k_mg_rb<ND, NS, true, 1, false>)
+                 : run(k_mg_rb<ND, NS, true, 2, false>);
+}
+
+void rb(const MgGeo &G, int ns, const double *u, const double *f, const double *a, const double *a2, double *out,
+        hipStream_t st) {
+  if (G.ndim == 2)
+    ns == 2 ? rb_launch<2, 2>(G, u, f, a, a2, out, st) : rb_launch<2, 1>(G, u, f, a, a2, out, st);
+  else
+    ns == 2 ? rb_launch<3, 2>(G, u, f, a, a2, out, st) : rb_launch<3, 1>(G, u, f, a, a2, out, st);
+}
+
+// `sweeps` sweeps of field u, alternating with the second field s, in pairs;
+// *cur: the field that holds the current values, u or s.  flips: how many
+// launches, at least (sweeps + 1) / 2 and at most `sweeps`.
+void rb_sweeps(const MgGeo &G, double *u, double *s, double **cur, const double *f, const double *a, const double *a2,
+               int sweeps, int flips, hipStream_t st) {
+  for (; sweeps > 0; flips--) {
+    const int ns = sweeps > flips ? 2 : 1;
+    double *next = *cur == u ? s : u;
+    rb(G, ns, *cur, f, a, a2, next, st);
+    *cur = next;
+    sweeps -= ns;
+  }
+}
+
+// `sweeps` sweeps whose result is in u again: an even number of launches (a
+// single sweep in place).
+void rb_sweeps_back(const MgGeo &G, double *u, double *s, const double *f, const double *a, const double *a2,
+                    int sweeps, hipStream_t st) {
+  if (sweeps == 1 || !s) {
+    sweeps_raw(G, u, f, a, a2, sweeps, st);
+    return;
+  }
+  const int least = (sweeps + 1) / 2;
+  double *cur = u;
+  rb_sweeps(G, u, s, &cur, f, a, a2, sweeps, least + (least & 1), st);
 }
 
 // Coarse problem of level l: u_{l-1} = R u_l (kept in uo_{l-1}),
@@ -2537,14 +2947,26 @@ void vcycle(gmunu_mg *m, int l, hipStream_t st) {
     coarse_solve(m, st);
     return;
   }
-  const bool sp = l == m->levels - 1 && m->sf;  // finest level: colour-split f, a, a2
-  sweeps_raw(m->geo[l], m->u[l], m->f[l], m->a[l], m->a2[l], m->d.pre, st, sp ? m->fs : nullptr,
-             sp && m->sa ? m->as : nullptr, sp && m->sa2 ? m->a2s : nullptr);
+  const MgGeo &G = m->geo[l];
+  double *u = m->u[l], *s = m->us[l];
+  const double *f = m->f[l], *a = m->a[l], *a2 = m->a2[l];
+  const int pre = m->d.pre, post = m->d.post, h0 = (pre + 1) / 2, h1 = (post + 1) / 2;
+  if (!s || pre + post < 2) {
+    sweeps_raw(G, u, f, a, a2, pre, st);
+    coarse_problem(m, l, st);
+    vcycle(m, l - 1, st);
+    correct(m, l, st);
+    sweeps_raw(G, u, f, a, a2, post, st);
+    return;
+  }
+  // an even number of launches in all, so that the field ends where it began:
+  // if need be, one pair of sweeps as two launches
+  const int odd = (h0 + h1) & 1, more0 = odd && pre >= 2, more1 = odd && !more0;
+  rb_sweeps(G, u, s, &m->u[l], f, a, a2, pre, h0 + more0, st);
   coarse_problem(m, l, st);
   vcycle(m, l - 1, st);
   correct(m, l, st);
-  sweeps_raw(m->geo[l], m->u[l], m->f[l], m->a[l], m->a2[l], m->d.post, st, sp ? m->fs : nullptr,
-             sp && m->sa ? m->as : nullptr, sp && m->sa2 ? m->a2s : nullptr);
+  rb_sweeps(G, u, s, &m->u[l], f, a, a2, post, h1 + more1, st);
 }
 
 void fmg(gmunu_mg *m, hipStream_t st) {
@@ -2581,10 +3003,8 @@ int norm(gmunu_mg *m, double *out, hipStream_t st) {
   return launch_status();
 }
 
-void split_copies(gmunu_mg *m, const double *f, const double *a, const double *a2, hipStream_t st);
-
-// Bind the caller's finest-level arrays, restrict a and a2 to the coarse
-// levels and refresh the colour-split copies.
+// Bind the caller's finest-level arrays and restrict a and a2 to the coarse
+// levels.
 void bind(gmunu_mg *m, double *u, const double *f, const double *a, const double *a2, hipStream_t st) {
   const int top = m->levels - 1;
   m->u[top] = u;
@@ -2601,28 +3021,18 @@ void bind(gmunu_mg *m, double *u, const double *f, const double *a, const double
       hipLaunchKernelGGL(k_mg_restrict, dim3(nblocks(cells(m->geo[l - 1]))), dim3(NT), 0, st, m->geo[l],
                          m->geo[l - 1], m->a2[l], m->a2[l - 1]);
   }
-  split_copies(m, f, a, a2, st);
 }
 
-// Colour-split copies of the finest f, a, a2 for the red-black sweeps
-// (large levels only: the copies cost one pass and save one per sweep).
-void split_copies(gmunu_mg *m, const double *f, const double *a, const double *a2, hipStream_t st) {
-  const MgGeo &G = m->geo[m->levels - 1];
-  m->sf = m->sa = m->sa2 = nullptr;
-  if (G.line || cells(G) < 32768 || G.n[0] < 16) return;
-  const size_t bytes = (size_t)cells(G) * sizeof(double);
-  auto get = [&](double *&p) {
-    if (!p && hipMalloc(&p, bytes) == hipSuccess) m->owned.push_back(p);
-    return p != nullptr;
-  };
-  if (!get(m->fs) || (a && !get(m->as)) || (a2 && !get(m->a2s))) return;
-  const dim3 gr(nblocks(cells(G)));
-  hipLaunchKernelGGL(k_mg_split, gr, dim3(NT), 0, st, G, f, m->fs);
-  if (a) hipLaunchKernelGGL(k_mg_split, gr, dim3(NT), 0, st, G, a, m->as);
-  if (a2) hipLaunchKernelGGL(k_mg_split, gr, dim3(NT), 0, st, G, a2, m->a2s);
-  m->sf = f;
-  m->sa = a;
-  m->sa2 = a2;
+// The second field of the finest level (without memory for it the level is
+// relaxed in place).
+void second_field(gmunu_mg *m) {
+  const int top = m->levels - 1;
+  const MgGeo &G = m->geo[top];
+  if (m->us[top] || !rb_level(G)) return;
+  double *p = nullptr;
+  if (hipMalloc(&p, (size_t)G.nt * sizeof(double)) != hipSuccess) return;
+  m->owned.push_back(p);
+  m->us[top] = p;
 }
 
 // a2 is accepted only by a hierarchy whose equation has the second term.
@@ -3095,8 +3505,7 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   m->tptr = nullptr;
   m->vtop = -1;
   m->vplan = nullptr;
-  m->fs = m->as = m->a2s = nullptr;
-  m->sf = m->sa = m->sa2 = nullptr;
+  for (double *&v : m->us) v = nullptr;
   m->vready = false;
   for (double *&v : m->vs) v = nullptr;
   m->gs = nullptr;
@@ -3105,7 +3514,7 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   m->next_slot = 0;
   // one allocation: the tables, the norm's partials, then the zeroed level
   // arrays (ghosts of coarse arrays are then defined): u, f, a, r (restricted
-  // residual), uo (restricted u) and a2 of the coarse levels, uo of the finest
+  // residual), uo (restricted u), a2 and second field of the coarse levels, uo of the finest
   // (the cleaning's divergence when the caller passes none)
   size_t at = 0;
   auto take = [&at](size_t n) {
@@ -3114,10 +3523,15 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
     return at - n;
   };
   const size_t tab_at = take(tab.size()), part_at = take(kNormParts + 1 + kGateSlots), zero_at = take(0);
-  size_t arr_at[kMaxLevels][6];
+  size_t arr_at[kMaxLevels][7];
   for (int l = 0; l < levels; l++)
-    for (int q = 0; q < 6; q++)
-      if (q == 0 || (l < levels - 1 && (q < 5 || desc->power2 != 0))) arr_at[l][q] = take(m->geo[l].nt);
+    for (int q = 0; q < 7; q++) {
+      const bool second = rb_level(m->geo[l]);
+      if (q == 0 || (l < levels - 1 && (q < 5 || (q == 5 ? desc->power2 != 0 : second))))
+        arr_at[l][q] = take(m->geo[l].nt);
+      else
+        arr_at[l][q] = SIZE_MAX;
+    }
   double *p = nullptr;
   bool ok = hipMalloc(&p, at * sizeof(double)) == hipSuccess;
   if (ok) m->owned.push_back(p);
@@ -3131,6 +3545,7 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
     m->aown[l] = coarse ? p + arr_at[l][3] : nullptr;
     m->r[l] = coarse ? p + arr_at[l][4] : nullptr;
     m->a2own[l] = coarse && desc->power2 != 0 ? p + arr_at[l][5] : nullptr;
+    m->us[l] = arr_at[l][6] != SIZE_MAX ? p + arr_at[l][6] : nullptr;
   }
   ok = ok && hipMemcpy(m->tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess &&
        hipMemset(p + zero_at, 0, (at - zero_at) * sizeof(double)) == hipSuccess &&
@@ -3193,6 +3608,7 @@ int gmunu_mg_solve(gmunu_mg *m, double *u, const double *f, const double *a, con
   hipStream_t cst = as_stream(stream);
   int rc = enter(m, cst);
   if (rc) return rc;
+  second_field(m);
   bind(m, u, f, a, a2, m->gs);
   hipGraphExec_t exec = cycle_graph(m, false, u, f, a, a2);
   if (!exec) return GMUNU_EHIP;
@@ -3240,10 +3656,8 @@ int gmunu_mg_smooth(gmunu_mg *m, double *u, const double *f, const double *a, co
   if (sweeps < 0 || !a2_ok(m, a2)) return GMUNU_EINVAL;
   hipStream_t st = as_stream(stream);
   const MgGeo &G = m->geo[m->levels - 1];
-  split_copies(m, f, a, a2, st);
-  const bool sp = m->sf != nullptr;
-  sweeps_raw(G, u, f, a, a2, sweeps, st, sp ? m->fs : nullptr, sp && a ? m->as : nullptr,
-             sp && a2 ? m->a2s : nullptr);
+  second_field(m);
+  rb_sweeps_back(G, u, m->us[m->levels - 1], f, a, a2, sweeps, st);
   ghosts(G, u, st);
   return launch_status();
 }
