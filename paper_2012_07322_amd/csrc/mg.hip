@@ -513,11 +513,17 @@ __global__ __launch_bounds__(NT) void k_mg_norm(const MgGeo G, const double *__r
   if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
+// Eight loads in flight per thread (16384 partials one by one took 22 us).
 __global__ __launch_bounds__(NT) void k_mg_norm_finish(double *part, int nparts) {
-  double m = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += NT) m = fmax(m, part[b]);
-  m = block_max(m);
-  if (threadIdx.x == 0) part[kNormParts] = m;
+  double m[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int b = threadIdx.x; b < nparts; b += 8 * NT)
+#pragma unroll
+    for (int q = 0; q < 8; q++)
+      if (b + q * NT < nparts) m[q] = fmax(m[q], part[b + q * NT]);
+#pragma unroll
+  for (int q = 1; q < 8; q++) m[0] = fmax(m[0], m[q]);
+  const double r = block_max(m[0]);
+  if (threadIdx.x == 0) part[kNormParts] = r;
 }
 
 // coarse = volume-weighted mean of the children (F: fine level, C: coarse).
@@ -1369,6 +1375,117 @@ __global__ __launch_bounds__((RbTile<ND, NS>::threads), (ND > 2 && CA && M < 2 &
   }
 }
 
+// ---- Residual passes ---------------------------------------------------------
+// The residual f - L(u) of a 2D or 3D level reduced to its maximum (OP 0: one
+// per workgroup, at part) or restricted (OP 1: volume-weighted means of u and of
+// the residual over the 2^ndim children, to uc and rc).  A wavefront holds
+// 32 x 2 cells, so the children of a coarse cell meet by two lane exchanges;
+// a workgroup's four cover 32 x 8 and march along z, the column's two
+// neighbours along z staying in registers.  What depends on (x, y) alone
+// (offsets, weights, the faces folded into a factor of u as in k_mg_rb) is set
+// up once per column.  Bound by memory: 256^3 cells with a (u + c) take
+// 103 us for the norm and 112 us for the restriction (24 B per cell
+// read); one thread per cell with the general operator took 167 us, one thread
+// per coarse cell (eight children in turn) 190 us.
+template <int ND, bool CA, int M, bool ROB, int OP>
+__global__ __launch_bounds__(NT) void k_mg_res(const MgGeo G, const double *__restrict__ u,
+                                               const double *__restrict__ f, const double *__restrict__ a,
+                                               const double *__restrict__ a2, const MgGeo C, double *__restrict__ uc,
+                                               double *__restrict__ rc, double *part, int zlen, int tiles) {
+  const int n0 = G.n[0], n1 = G.n[1], n2 = ND > 2 ? G.n[2] : 1, lane = threadIdx.x & 63;
+  const int gx = (n0 + 31) / 32, gy = (n1 + 7) / 8;
+  const bool px = G.bc[0][0] == GMUNU_MG_PERIODIC, py = G.bc[1][0] == GMUNU_MG_PERIODIC,
+             pz = ND > 2 && G.bc[2][0] == GMUNU_MG_PERIODIC;
+  double mx = 0.0;
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int x = t % gx * 32 + (lane & 31), y = t / gx % gy * 8 + (int)(threadIdx.x >> 6) * 2 + (lane >> 5);
+    const int z0 = t / (gx * gy) * zlen, z1 = z0 + zlen < n2 ? z0 + zlen : n2;
+    const bool in = x < n0 && y < n1;
+    const int i = x < n0 ? x : n0 - 1, j = y < n1 ? y : n1 - 1, I = i + 1, J = j + 1;
+    const bool f0 = i == 0, f1 = i == n0 - 1, f2 = j == 0, f3 = j == n1 - 1;
+    const int s1 = (int)G.s1;
+    const long o = (long)(j + 1) * s1 + i + 1;
+    const int xm = f0 ? (px ? n0 - 1 : 0) : -1, xp = f1 ? (px ? 1 - n0 : 0) : 1;
+    const int ym = f2 ? (py ? (n1 - 1) * s1 : 0) : -s1, yp = f3 ? (py ? (1 - n1) * s1 : 0) : s1;
+    const double wm0 = CA ? G.vih2[0] : G.a0m[I], wp0 = CA ? G.vih2[0] : G.a0p[I];
+    const double wm1 = CA ? G.vih2[1] : G.g1[I] * G.a1m[J], wp1 = CA ? G.vih2[1] : G.g1[I] * G.a1p[J];
+    const double w2 = ND < 3 ? 0.0 : CA ? G.vih2[2] : G.g2[I] * G.s2t[J] * G.ih2_2;
+    const double vol = CA ? 1.0 : G.vol0[I] * G.vol1[J];
+    const double cxy = (f0 && !px ? wm0 * mg_fold1(G, 0, 0) : 0.0) + (f1 && !px ? wp0 * mg_fold1(G, 0, 1) : 0.0) +
+                       (f2 && !py ? wm1 * mg_fold1(G, 1, 0) : 0.0) + (f3 && !py ? wp1 * mg_fold1(G, 1, 1) : 0.0);
+    const double xc = G.x0[0] + (i + 0.5) * G.h[0], yc = G.x0[1] + (j + 0.5) * G.h[1];
+    const long g2 = ND > 2 ? 1 : 0;
+    double um = 0.0, ucen = u[o + (z0 + g2) * G.s2], up = 0.0, su = 0.0, sr = 0.0;
+    if (ND > 2) um = z0 > 0 ? u[o + z0 * G.s2] : pz ? u[o + n2 * G.s2] : ucen;
+    for (int z = z0; z < z1; z++) {
+      const long oz = o + (z + g2) * G.s2;
+      const bool zlo = ND > 2 && !pz && z == 0, zhi = ND > 2 && !pz && z == n2 - 1;
+      if (ND > 2) up = z < n2 - 1 ? u[oz + G.s2] : pz ? u[o + G.s2] : ucen;
+      const double vxm = u[oz + xm], vxp = u[oz + xp], vym = u[oz + ym], vyp = u[oz + yp];
+      const double fv = f[oz], av = M > 0 && a ? a[oz] : 0.0, a2v = M == 2 && a2 ? a2[oz] : 0.0;
+      double lap = wp0 * (vxp - ucen) - wm0 * (ucen - vxm);
+      lap += wp1 * (vyp - ucen) - wm1 * (ucen - vym);
+      double cc = cxy;
+      if (ND > 2) {
+        lap += w2 * (up - ucen) - w2 * (ucen - um);
+        if (zlo) cc += w2 * mg_fold1(G, 2, 0);
+        if (zhi) cc += w2 * mg_fold1(G, 2, 1);
+      }
+      if (ROB) {
+        double rr = xc * xc + yc * yc, zc = 0.0;
+        if (ND > 2 && G.coord == GMUNU_CART) {
+          zc = G.x0[2] + (z + 0.5) * G.h[2];
+          rr += zc * zc;
+        }
+        if (f0 && !px && mg_robin(G, 0, 0)) cc += wm0 * mg_robin1(rr, xc, xc - G.h[0]);
+        if (f1 && !px && mg_robin(G, 0, 1)) cc += wp0 * mg_robin1(rr, xc, xc + G.h[0]);
+        if (f2 && !py && mg_robin(G, 1, 0)) cc += wm1 * mg_robin1(rr, yc, yc - G.h[1]);
+        if (f3 && !py && mg_robin(G, 1, 1)) cc += wp1 * mg_robin1(rr, yc, yc + G.h[1]);
+        if (zlo && mg_robin(G, 2, 0)) cc += w2 * mg_robin1(rr, zc, zc - G.h[2]);
+        if (zhi && mg_robin(G, 2, 1)) cc += w2 * mg_robin1(rr, zc, zc + G.h[2]);
+      }
+      lap += cc * ucen;
+      if (M == 2) {
+        double du;
+        lap -= mg_nl_both(G.power, G.power2, G.offset, av, a2v, ucen, du);
+      } else if (M == 1) {
+        lap -= av * (ucen + G.offset);
+      }
+      const double r = fv - lap;
+      if (OP == 0) {
+        if (in) mx = mg_absmax(mx, r);
+      } else {
+        su += vol * ucen;
+        sr += vol * r;
+        if (ND < 3 || (z & 1)) {
+          double w = vol;
+          su += __shfl_xor(su, 1, 64);
+          sr += __shfl_xor(sr, 1, 64);
+          su += __shfl_xor(su, 32, 64);
+          sr += __shfl_xor(sr, 32, 64);
+          if (!CA) {
+            w += __shfl_xor(w, 1, 64);
+            w += __shfl_xor(w, 32, 64);
+          }
+          const double iw = CA ? 1.0 / (1 << ND) : 1.0 / (ND > 2 ? 2.0 * w : w);
+          if (in && !(x & 1) && !(y & 1)) {
+            const long oc = mg_off(C, x >> 1, y >> 1, z >> 1);
+            uc[oc] = su * iw;
+            rc[oc] = sr * iw;
+          }
+          su = sr = 0.0;
+        }
+      }
+      um = ucen;
+      ucen = up;
+    }
+  }
+  if (OP == 0) {
+    mx = block_max(mx);
+    if (threadIdx.x == 0) part[blockIdx.x] = mx;
+  }
+}
+
 // Kwak prolongation of v (coarse, ghosts set) into the fine interior:
 // fine = P v (add = 0) or fine += P v (add = 1).
 __global__ __launch_bounds__(NT) void k_mg_prolong(const MgGeo C, const MgGeo F, const double *__restrict__ v,
@@ -2189,31 +2306,40 @@ __global__ __launch_bounds__(NT) void k_mgv_norm(const MgGeo G, const double *__
 }
 
 // Coarse problem of a fine level for the vector equation: the children's
-// residuals and values, volume-weighted means into the coarse r and u.
+// residuals and values, volume-weighted means into the coarse r and u.  One
+// thread per child, the 2^ndim of a coarse cell meeting by lane exchanges:
+// bound by the latency of the operator's loads, which eight children in turn
+// paid eight times (31 to 35 us from 64^3, 32^3 and 16^3 cells; now 13, 8 and 8; from 128^3 85, now 82).
 __global__ __launch_bounds__(NT) void k_mgv_restrict_res(const MgGeo F, const MgGeo C, const double *__restrict__ u,
                                                          const double *__restrict__ f, double *__restrict__ uc,
                                                          double *__restrict__ rc) {
   const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t >= mg_cells(C)) return;
-  int i, j, k;
-  mg_cell(C, t, i, j, k);
+  const int nd = F.ndim, ch = (int)(t & ((1 << nd) - 1));
+  const bool live = t >> nd < mg_cells(C);
   double su[3] = {0.0, 0.0, 0.0}, sr[3] = {0.0, 0.0, 0.0}, w = 0.0;
-  const int nch = 1 << F.ndim;
-  for (int ch = 0; ch < nch; ch++) {
+  int i = 0, j = 0, k = 0;
+  if (live) {
+    mg_cell(C, t >> nd, i, j, k);
     const int fi = 2 * i + (ch & 1);
-    const int fj = F.ndim > 1 ? 2 * j + ((ch >> 1) & 1) : j;
-    const int fk = F.ndim > 2 ? 2 * k + ((ch >> 2) & 1) : k;
+    const int fj = nd > 1 ? 2 * j + ((ch >> 1) & 1) : j;
+    const int fk = nd > 2 ? 2 * k + ((ch >> 2) & 1) : k;
     const long o = mg_off(F, fi, fj, fk);
-    const double v = F.vol0[fi + F.g[0]] * F.vol1[fj + F.g[1]];
+    w = F.vol0[fi + F.g[0]] * F.vol1[fj + F.g[1]];
     double L[3], idg[3];
     mgv_L(F, u, o, fi, fj, fk, L, idg);
 #pragma unroll
     for (int q = 0; q < 3; q++) {
-      su[q] += v * u[q * F.nt + o];
-      sr[q] += v * (f[q * F.nt + o] - L[q]);
+      su[q] = w * u[q * F.nt + o];
+      sr[q] = w * (f[q * F.nt + o] - L[q]);
     }
-    w += v;
   }
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+    su[q] = mg_sum_children(su[q], nd);
+    sr[q] = mg_sum_children(sr[q], nd);
+  }
+  w = mg_sum_children(w, nd);
+  if (!live || ch) return;
   const long oc = mg_off(C, i, j, k);
 #pragma unroll
   for (int q = 0; q < 3; q++) {
@@ -2877,12 +3003,50 @@ void rb_sweeps_back(const MgGeo &G, double *u, double *s, const double *f, const
   rb_sweeps(G, u, s, &cur, f, a, a2, sweeps, least + (least & 1), st);
 }
 
+// The residual of a 2D or 3D level: its maxima (OP 0, at part) or restricted
+// to level C (OP 1).  Returns the workgroups launched.
+template <int ND, int OP>
+int residual_nd(const MgGeo &G, const double *u, const double *f, const double *a, const double *a2, const MgGeo &C,
+                double *uc, double *rc, double *part, hipStream_t st) {
+  const long cols = (long)((G.n[0] + 31) / 32) * ((G.n[1] + 7) / 8);
+  // planes per workgroup: as many as leave about eight workgroups per CU (even:
+  // a coarse cell's planes stay together)
+  long len = 1;
+  if (ND > 2)
+    for (len = 2; len < 16 && cols * (G.n[2] / (2 * len)) >= 2048;) len *= 2;
+  const long tiles = ND > 2 ? cols * ((G.n[2] + len - 1) / len) : cols;
+  const int grid = OP == 0 && tiles > kNormParts ? kNormParts : (int)tiles;
+  const int terms = !a && !a2 ? 0 : a && !a2 && G.power == 1 ? 1 : 2;
+  const bool rob = rb_robin(G);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), 0, st, G, u, f, a, a2, C, uc, rc, part, (int)len, (int)tiles);
+  };
+  if (G.coord != GMUNU_CART)
+    rob ? run(k_mg_res<ND, false, 2, true, OP>) : run(k_mg_res<ND, false, 2, false, OP>);
+  else if (rob)
+    terms == 1 ? run(k_mg_res<ND, true, 1, true, OP>) : run(k_mg_res<ND, true, 2, true, OP>);
+  else
+    terms == 0   ? run(k_mg_res<ND, true, 0, false, OP>)
+    : terms == 1 ? run(k_mg_res<ND, true, 1, false, OP>)
+                 : run(k_mg_res<ND, true, 2, false, OP>);
+  return grid;
+}
+template <int OP>
+int residual(const MgGeo &G, const double *u, const double *f, const double *a, const double *a2, const MgGeo &C,
+             double *uc, double *rc, double *part, hipStream_t st) {
+  return G.ndim == 2 ? residual_nd<2, OP>(G, u, f, a, a2, C, uc, rc, part, st)
+                     : residual_nd<3, OP>(G, u, f, a, a2, C, uc, rc, part, st);
+}
+
 // Coarse problem of level l: u_{l-1} = R u_l (kept in uo_{l-1}),
 // f_{l-1} = L_{l-1}(R u_l) + R (f_l - L_l(u_l)).
 void coarse_problem(gmunu_mg *m, int l, hipStream_t st) {
   const MgGeo &F = m->geo[l], &C = m->geo[l - 1];
-  hipLaunchKernelGGL(k_mg_restrict_res, dim3(nblocks(cells(C))), dim3(NT), 0, st, F, C, m->u[l], m->f[l], m->a[l],
-                     m->a2[l], m->u[l - 1], m->r[l - 1]);
+  if (F.ndim > 1)
+    residual<1>(F, m->u[l], m->f[l], m->a[l], m->a2[l], C, m->u[l - 1], m->r[l - 1], nullptr, st);
+  else
+    hipLaunchKernelGGL(k_mg_restrict_res, dim3(nblocks(cells(C))), dim3(NT), 0, st, F, C, m->u[l], m->f[l], m->a[l],
+                       m->a2[l], m->u[l - 1], m->r[l - 1]);
   hipLaunchKernelGGL(k_mg_fas_rhs, dim3(nblocks(cells(C))), dim3(NT), 0, st, C, m->u[l - 1], m->a[l - 1],
                      m->a2[l - 1], m->r[l - 1], m->f[l - 1], m->uo[l - 1]);
 }
@@ -2989,9 +3153,12 @@ void norm_enqueue(gmunu_mg *m, hipStream_t st) {
   const int top = m->levels - 1;
   const MgGeo &G = m->geo[top];
   const long nb = nblocks(cells(G));
-  const int np = (int)(nb < kNormParts ? nb : kNormParts);
-  hipLaunchKernelGGL(k_mg_norm, dim3(np), dim3(NT), 0, st, G, m->u[top], m->f[top], m->a[top], m->a2[top],
-                     m->part);
+  int np = (int)(nb < kNormParts ? nb : kNormParts);
+  if (G.ndim > 1)
+    np = residual<0>(G, m->u[top], m->f[top], m->a[top], m->a2[top], G, nullptr, nullptr, m->part, st);
+  else
+    hipLaunchKernelGGL(k_mg_norm, dim3(np), dim3(NT), 0, st, G, m->u[top], m->f[top], m->a[top], m->a2[top],
+                       m->part);
   hipLaunchKernelGGL(k_mg_norm_finish, dim3(1), dim3(NT), 0, st, m->part, np);
 }
 
@@ -3125,7 +3292,7 @@ void vghosts(const MgGeo &G, double *u, hipStream_t st) {
 
 void vcoarse_problem(gmunu_mg *m, int l, hipStream_t st) {
   const MgGeo &F = m->geo[l], &C = m->geo[l - 1];
-  hipLaunchKernelGGL(k_mgv_restrict_res, dim3(nblocks(cells(C))), dim3(NT), 0, st, F, C, m->vu[l], m->vf[l],
+  hipLaunchKernelGGL(k_mgv_restrict_res, dim3(nblocks(cells(C) << F.ndim)), dim3(NT), 0, st, F, C, m->vu[l], m->vf[l],
                      m->vu[l - 1], m->vr[l - 1]);
   hipLaunchKernelGGL(k_mgv_fas_rhs, dim3(nblocks(cells(C))), dim3(NT), 0, st, C, m->vu[l - 1], m->vr[l - 1],
                      m->vf[l - 1], m->vuo[l - 1]);
