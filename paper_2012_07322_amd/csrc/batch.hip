@@ -12,7 +12,8 @@
 // one contiguous run of items so that the tiles of a block share that XCD's
 // L2.  Per-cell arithmetic is the single-grid path's (gmunu_tile.hpp): a
 // block advanced here is bitwise equal to the same block advanced alone,
-// whatever tile shape is used.
+// whatever tile shape is used (and equal to rounding where the grid alone is
+// large enough for the marched stage, march_plan in gmunu.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -2,8 +2,9 @@
 // C ABI.
 //
 // One RK stage is up to three launches on the caller's stream:
-//   k_stage   per tile of cells (16x4x3 in 3D, 16x15 in 2D, 255 in 1D, so
-//             that each direction's faces fit one per thread): the tile's
+//   k_stage   (large Cartesian 3D grids: k_stage_march, which marches columns
+//             along z) per tile of cells (16x4x3 in 3D, 16x15 in 2D, 255 in
+//             1D, so that each direction's faces fit one per thread): the tile's
 //             plus-shaped region of prim and metric is staged in LDS once,
 //             then per direction each face is reconstructed (MC, MP5 or
 //             PPM) and its HLLE or TVDLF flux (optionally positivity-limited)
@@ -102,6 +103,21 @@ __global__ __launch_bounds__(NT, (stage_occupancy<TX, TY, TZ, ND, recon_halo(REC
                                             kij, fc);
 }
 
+// The same for large Cartesian 3D grids, one workgroup per column of TX x TY
+// cells and chunk of zlen planes (stage_march; MODE 0 or 1).
+template <int TX, int TY, int MODE, int REC, int R, int P>
+__global__ __launch_bounds__(NT, 2) void k_stage_march(
+    const Grid G, const double *__restrict__ prim, const double *__restrict__ met, const double *qn, const double *qs,
+    double *out, const double *__restrict__ dtp, double ca, double cb, const double *__restrict__ skipp,
+    const double *__restrict__ kij, int zlen) {
+  __shared__ double sF[March<TX, TY, REC>::LDS];
+  if (skipp && *skipp == 0.0) return;
+  int bx, by, bz;
+  xcd_tile(G, TX, TY, zlen, bx, by, bz);
+  const int z0 = bz * zlen, z1 = z0 + zlen < G.n[2] ? z0 + zlen : G.n[2];
+  stage_march<TX, TY, MODE, REC, R, P>(G, bx * TX, by * TY, z0, z1, prim, met, qn, qs, out, dtp, ca, cb, sF, kij);
+}
+
 // Recovery of one interior cell per thread.  gaxes: also write the face
 // ghosts of the first gaxes axes copied from the recovered cells.  part
 // (nullable): the workgroup's maximum CFL rate of the primitives just
@@ -180,6 +196,50 @@ void launch_stage_t(const gmunu_ctx *ctx, const double *prim, const double *met,
                      dtp, ca, cb, skipp, kij, fc);
 }
 
+// Which 3D stage kernel a grid takes: planes per workgroup of the marched
+// one, 0 for the tiles, and its column's shape.  The least of the times that
+// rounds of resident workgroups take (in 0.1 us, measured on full rounds): 512
+// tiles 14.5 us with MC, 256 tiles 26.7 us with MP5 or PPM; 512 columns of L
+// planes 1.0 L + 1.8 (31x7 cells, MC), 1.1 L + 1.8 (15x15, MC) and 3.1 L + 3.0
+// (15x15, MP5 or PPM) times 10 us, the constant for the planes below the
+// first.  So 64^3 stays on tiles (43 against 58 us), 96^3 (132 against 140 us)
+// and larger grids march; the shape follows the grid's remainders.
+struct March3 {
+  int zlen;
+  bool wide;
+};
+
+March3 march_plan(const Grid &G) {
+  March3 m{0, false};
+  if (G.ndim < 3 || G.coord != CART) return m;
+  const bool mc = G.recon == GMUNU_RECON_MC;
+  auto up = [](long a, long b) { return (a + b - 1) / b; };
+  const long tiles = up(G.n[0], 16) * up(G.n[1], 4) * up(G.n[2], 3);
+  if (tiles <= 512) return m;
+  long best = mc ? up(tiles, 512) * 145 : up(tiles, 256) * 267;
+  for (int wide = 0; wide < (mc ? 2 : 1); wide++) {
+    const long cols = wide ? up(G.n[0], 31) * up(G.n[1], 7) : up(G.n[0], 15) * up(G.n[1], 15);
+    for (int len = 4; len <= 16; len++) {
+      const long t = up(cols * up(G.n[2], len), 512) * (wide ? 100 * len + 180 : mc ? 110 * len + 180 : 310 * len + 300);
+      if (t < best) {
+        best = t;
+        m = March3{len, wide == 1};
+      }
+    }
+  }
+  return m;
+}
+
+template <int TX, int TY, int MODE, int REC, int R, int P>
+void launch_march_t(const gmunu_ctx *ctx, int zlen, const double *prim, const double *met, const double *kij,
+                    const double *qn, const double *qs, double *out, const double *dtp, double ca, double cb,
+                    const double *skipp, hipStream_t st) {
+  const Grid &G = ctx->G;
+  const int grid = ((G.n[0] + TX - 1) / TX) * ((G.n[1] + TY - 1) / TY) * ((G.n[2] + zlen - 1) / zlen);
+  hipLaunchKernelGGL((k_stage_march<TX, TY, MODE, REC, R, P>), dim3(grid), dim3(NT), 0, st, G, prim, met, qn, qs, out,
+                     dtp, ca, cb, skipp, kij, zlen);
+}
+
 template <int MODE>
 void launch_stage(const gmunu_ctx *ctx, const double *prim, const double *met, const double *kij,
                   const double *qn, const double *qs, double *out, const double *dtp, double ca, double cb,
@@ -187,6 +247,29 @@ void launch_stage(const gmunu_ctx *ctx, const double *prim, const double *met, c
   const int rec = ctx->G.recon, lf = ctx->G.riemann == GMUNU_RIEMANN_TVDLF;
   // the limiter acts on the stage's Euler step, so the RHS alone (MODE 0) is unlimited
   const int pp = MODE != 0 && ctx->G.pp;
+  if constexpr (MODE != 2) {
+    const March3 m = march_plan(ctx->G);
+    if (m.zlen) {
+      switch (m.wide * 16 + rec * 4 + lf * 2 + pp) {
+#define GM_CASE(W, TX, TY, M, L, P)                                                                          \
+  case W * 16 + M * 4 + L * 2 + P:                                                                           \
+    launch_march_t<TX, TY, MODE, M, L, MODE == 1 && P>(ctx, m.zlen, prim, met, kij, qn, qs, out, dtp, ca, cb, \
+                                                       skipp, st);                                           \
+    break;
+#define GM_CASES(W, TX, TY, M) \
+  GM_CASE(W, TX, TY, M, 0, 0) GM_CASE(W, TX, TY, M, 0, 1) GM_CASE(W, TX, TY, M, 1, 0) GM_CASE(W, TX, TY, M, 1, 1)
+        GM_CASES(1, 31, 7, GMUNU_RECON_MC)
+        GM_CASES(0, 15, 15, GMUNU_RECON_MC)
+        GM_CASES(0, 15, 15, GMUNU_RECON_MP5)
+        GM_CASES(0, 15, 15, GMUNU_RECON_PPM)
+#undef GM_CASES
+#undef GM_CASE
+        default:
+          break;
+      }
+      return;
+    }
+  }
   switch (ctx->G.ndim * 16 + rec * 4 + lf * 2 + pp) {
 #define GM_CASE(NDIM, TX, TY, TZ, M, L, P)                                                                      \
   case NDIM * 16 + M * 4 + L * 2 + P:                                                                            \
@@ -253,7 +336,9 @@ int rk_stage_impl(gmunu_ctx *ctx, int stage, const double *dt_dev, const double 
   // with separate input and output primitives (and no limiter) the stage
   // kernel recovers the primitives itself; otherwise the recovery is its
   // own kernel after the stage
-  const bool fuse = prim_out != prim_in && !ctx->G.pp;
+  // (separate on grids that march: the marched stage and a recovery at the
+  // copy rate are faster than a fused tile)
+  const bool fuse = prim_out != prim_in && !ctx->G.pp && !march_plan(ctx->G).zlen;
   {
     ProfScope ps(ctx, st, GMUNU_K_STAGE);
     if (fuse)

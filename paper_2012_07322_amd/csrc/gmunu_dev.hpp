@@ -105,6 +105,14 @@ __device__ __forceinline__ double rsq(double x) {
 // sqrt(x) for x >= 0 (0 below 1e-300).
 __device__ __forceinline__ double sqrt_pos(double x) { return x > 1e-300 ? x * rsq(x) : 0.0; }
 
+// The same without a branch: the two states of a face then share one basic
+// block, in which their dependent chains are interleaved.
+__device__ __forceinline__ double sqrt_pos_flat(double x) {
+  const bool pos = x > 1e-300;
+  const double r = x * rsq(pos ? x : 1.0);
+  return pos ? r : 0.0;
+}
+
 // Monotonised-central limited slope: minmod(2 dl, (dl + dr) / 2, 2 dr).
 __device__ __forceinline__ double mc_slope(double a, double b, double c) {
   double dl = b - a, dr = c - b;
@@ -171,8 +179,8 @@ __device__ __forceinline__ double ppm_face(double a, double b, double c, double 
 // Conserved vector U, flux F along direction D and the two wave-speed bounds
 // of one primitive state at one point (section 2.1 and 2.3).  g1, g2: the
 // reference metric diagonal (the first entry is 1 in every coordinate
-// system used here).
-template <int D>
+// system used here).  FLAT: no branch at the square root.
+template <int D, bool FLAT = false>
 __device__ __forceinline__ void state_flux(const double gam, const double gfac, const double *pr, double psi4,
                                            double psi6, double alpha, const double *beta, double g1, double g2,
                                            double gud, double *U, double *F, double &lm, double &lp) {
@@ -236,7 +244,8 @@ __device__ __forceinline__ void state_flux(const double gam, const double gfac, 
   const double one_a2 = 1.0 - a2;
   const double va = v[D];
   const double va2a = 1.0 - v2 * a2;
-  const double sq = sqrt_pos(a2 * (1.0 - v2) * (va2a * gud - one_a2 * va * va));
+  const double disc = a2 * (1.0 - v2) * (va2a * gud - one_a2 * va * va);
+  const double sq = FLAT ? sqrt_pos_flat(disc) : sqrt_pos(disc);
   const double iden = rcp(va2a);
   lm = alpha * ((one_a2 * va - sq) * iden) - beta[D];
   lp = alpha * ((one_a2 * va + sq) * iden) - beta[D];

@@ -141,45 +141,23 @@ __device__ __forceinline__ int met_index(int c, int x, int y, int z) {
   }
 }
 
-// Face flux times face factor through the lower face (along D) of cell
-// (i,j,k): reconstruction REC from the cells across the face (MC from four
-// cells, halo H = 2; MP5 or PPM from six, H = 3), metric as the mean of the
-// two adjacent centres, HLLE (R = 0) or TVDLF (R = 1).  The stencil comes
-// from the workgroup's staged region S (NP cells per variable, primitive
-// variables 0-7): ix[m], m = 0 .. 2H-1, is the region index of the cell
-// H - m below the face (ix[H-1], ix[H] are the two adjacent cells, whose
-// metric (psi, alpha, beta^1..3) is ma, mb).  nonflat is set when the two
-// adjacent cells differ in psi or alpha or either has a non-zero shift.
-//
-// P = 1 applies the positivity-preserving limiter (section 2.4): the flux is
-// blended with the first-order Lax-Friedrichs flux of the two adjacent cell
-// states, with the largest theta that keeps D and tau of the Euler update of
-// both adjacent interior cells above eps (ghost cells are not advanced and do
-// not take part).
-template <int D, int REC, int R, int P = 0>
-__device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP, const int *ix, const double *ma,
-                                          const double *mb, int i, int j, int k, double *Fo, bool &nonflat,
-                                          const PPBase &pb = PPBase{nullptr, 0.0}) {
-  constexpr int H = recon_halo(REC);
-  const int cd = (D == 0 ? i : D == 1 ? j : k) + G.g[D];
-  // zero-area faces (r = 0, theta = 0 or pi) are evaluated like any other
-  // and their flux replaced by 0 at the end; no load-dependent branch here
-  const double fa = G.geo.fa[D][cd];
-  const int r1 = ix[H - 1], r2 = ix[H];
-  double pl[NV], pr[NV];
+// Reconstruction REC of the two states at a face from the cells across it
+// (MC from four cells, halo H = 2; MP5 or PPM from six, H = 3): st(v, m),
+// m = 0 .. 2H-1, is variable v of the cell H - m below the face (H-1 and H
+// are the two adjacent cells).
+template <int REC, typename St>
+__device__ __forceinline__ void face_states(const St &st, double *pl, double *pr) {
   if constexpr (REC == GMUNU_RECON_MC) {
 #pragma unroll
     for (int v = 0; v < NV; v++) {
-      const double *Sv = S + v * NP;
-      const double a = Sv[ix[0]], b = Sv[r1], e = Sv[r2], f = Sv[ix[3]];
+      const double a = st(v, 0), b = st(v, 1), e = st(v, 2), f = st(v, 3);
       pl[v] = b + mc_half_slope(a, b, e);
       pr[v] = e - mc_half_slope(b, e, f);
     }
   } else {
 #pragma unroll
     for (int v = 0; v < NV; v++) {
-      const double *Sv = S + v * NP;
-      const double u0 = Sv[ix[0]], u1 = Sv[ix[1]], u2 = Sv[ix[2]], u3 = Sv[ix[3]], u4 = Sv[ix[4]], u5 = Sv[ix[5]];
+      const double u0 = st(v, 0), u1 = st(v, 1), u2 = st(v, 2), u3 = st(v, 3), u4 = st(v, 4), u5 = st(v, 5);
       if constexpr (REC == GMUNU_RECON_MP5) {
         pl[v] = mp5_face(u0, u1, u2, u3, u4);
         pr[v] = mp5_face(u5, u4, u3, u2, u1);
@@ -193,11 +171,35 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
     if (!(pl[0] > 0.0 && pl[4] > 0.0 && pr[0] > 0.0 && pr[4] > 0.0)) {
 #pragma unroll
       for (int v = 0; v < NV; v++) {
-        pl[v] = S[v * NP + r1];
-        pr[v] = S[v * NP + r2];
+        pl[v] = st(v, 2);
+        pr[v] = st(v, 3);
       }
     }
   }
+}
+
+// Face flux times face factor through the lower face (along D) of cell
+// (i,j,k) from its two reconstructed states pl and pr: metric as the mean of
+// the two adjacent centres (psi, alpha, beta^1..3: ma below, mb above), HLLE
+// (R = 0) or TVDLF (R = 1); cell(v, s) is variable v of the cell below
+// (s = 0) and above (s = 1).  nonflat is set when the two adjacent cells
+// differ in psi or alpha or either has a non-zero shift.
+//
+// P = 1 applies the positivity-preserving limiter (section 2.4): the flux is
+// blended with the first-order Lax-Friedrichs flux of the two adjacent cell
+// states, with the largest theta that keeps D and tau of the Euler update of
+// both adjacent interior cells above eps (ghost cells are not advanced and do
+// not take part).
+// CA: a Cartesian grid (unit face factors and reference metric; cell widths
+// from the grid's parameters).
+template <bool CA, int D, int R, int P, typename Cell>
+__device__ __forceinline__ void face_flux(const Grid &G, const double *pl, const double *pr, const Cell &cell,
+                                          const double *ma, const double *mb, int i, int j, int k, double *Fo,
+                                          bool &nonflat, const PPBase &pb = PPBase{nullptr, 0.0}) {
+  const int cd = (D == 0 ? i : D == 1 ? j : k) + G.g[D];
+  // zero-area faces (r = 0, theta = 0 or pi) are evaluated like any other
+  // and their flux replaced by 0 at the end; no load-dependent branch here
+  const double fa = CA ? 1.0 : G.geo.fa[D][cd];
   const double psi = 0.5 * (ma[0] + mb[0]);
   const double alpha = 0.5 * (ma[1] + mb[1]);
   double beta[3];
@@ -209,7 +211,7 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
   }
   nonflat = nonflat || shift || ma[0] != mb[0] || ma[1] != mb[1];
   double g1 = 1.0, g2 = 1.0;
-  if (G.coord != CART) {
+  if (!CA && G.coord != CART) {
     const double r2c = (D == 0) ? G.geo.r2f[i + G.g[0]] : G.geo.r2c[i + G.g[0]];
     const double s2 = (D == 1) ? G.geo.s2f[j + G.g[1]] : G.geo.s2c[j + G.g[1]];
     ref_diag(G.coord, r2c, s2, g1, g2);
@@ -222,8 +224,8 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
   // together with the face factor
   const double fs = fa * psi6;
   double UL[NV], FL[NV], UR[NV], FR[NV], lmL, lpL, lmR, lpR;
-  state_flux<D>(G.gam, G.gfac, pl, psi4, 1.0, alpha, beta, g1, g2, gud, UL, FL, lmL, lpL);
-  state_flux<D>(G.gam, G.gfac, pr, psi4, 1.0, alpha, beta, g1, g2, gud, UR, FR, lmR, lpR);
+  state_flux<D, CA>(G.gam, G.gfac, pl, psi4, 1.0, alpha, beta, g1, g2, gud, UL, FL, lmL, lpL);
+  state_flux<D, CA>(G.gam, G.gfac, pr, psi4, 1.0, alpha, beta, g1, g2, gud, UR, FR, lmR, lpR);
   if constexpr (R == GMUNU_RIEMANN_TVDLF) {
     // local Lax-Friedrichs: the largest speed magnitude of both states
     const double c = fmax(fmax(fabs(lmL), fabs(lpL)), fmax(fabs(lmR), fabs(lpR)));
@@ -231,7 +233,7 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
 #pragma unroll
     for (int v = 0; v < NV; v++) {
       const double f = h * (FL[v] + FR[v]) - hc * (UR[v] - UL[v]);
-      Fo[v] = fa == 0.0 ? 0.0 : f;
+      Fo[v] = !CA && fa == 0.0 ? 0.0 : f;
     }
   } else {
     // HLLE as three weights: F = cL F_L + cR F_R + cU (U_R - U_L), with
@@ -248,21 +250,21 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
 #pragma unroll
     for (int v = 0; v < NV; v++) {
       const double f = cL * FL[v] + cR * FR[v] + cU * (UR[v] - UL[v]);
-      Fo[v] = fa == 0.0 ? 0.0 : f;
+      Fo[v] = !CA && fa == 0.0 ? 0.0 : f;
     }
   }
   if constexpr (P) {
     // zero-area faces carry no flux either way
-    if (fa == 0.0) return;
+    if (!CA && fa == 0.0) return;
     double p0[NV], p1[NV];
 #pragma unroll
     for (int v = 0; v < NV; v++) {
-      p0[v] = S[v * NP + r1];
-      p1[v] = S[v * NP + r2];
+      p0[v] = cell(v, 0);
+      p1[v] = cell(v, 1);
     }
     double U0[NV], F0[NV], U1[NV], F1[NV], lm0, lp0, lm1, lp1;
-    state_flux<D>(G.gam, G.gfac, p0, psi4, psi6, alpha, beta, g1, g2, gud, U0, F0, lm0, lp0);
-    state_flux<D>(G.gam, G.gfac, p1, psi4, psi6, alpha, beta, g1, g2, gud, U1, F1, lm1, lp1);
+    state_flux<D, CA>(G.gam, G.gfac, p0, psi4, psi6, alpha, beta, g1, g2, gud, U0, F0, lm0, lp0);
+    state_flux<D, CA>(G.gam, G.gfac, p1, psi4, psi6, alpha, beta, g1, g2, gud, U1, F1, lm1, lp1);
     const double c = fmax(fmax(fabs(lm0), fabs(lp0)), fmax(fabs(lm1), fabs(lp1)));
     double Fl[NV];
 #pragma unroll
@@ -271,8 +273,8 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
     const int cd = D == 0 ? i : D == 1 ? j : k;
     const bool in0 = cd >= 1, in1 = cd < G.n[D];
     const long o1 = cell_offset(G, i, j, k), o0 = o1 - G.s[D];
-    const double w0 = in0 ? 2.0 * pb.dt * G.geo.icv[D][cd - 1 + G.g[D]] : 0.0;
-    const double w1 = in1 ? 2.0 * pb.dt * G.geo.icv[D][cd + G.g[D]] : 0.0;
+    const double w0 = in0 ? 2.0 * pb.dt * (CA ? G.idx[D] : G.geo.icv[D][cd - 1 + G.g[D]]) : 0.0;
+    const double w1 = in1 ? 2.0 * pb.dt * (CA ? G.idx[D] : G.geo.icv[D][cd + G.g[D]]) : 0.0;
     double theta = 1.0;
 #pragma unroll
     for (int m = 0; m < 2; m++) {
@@ -297,10 +299,10 @@ __device__ __forceinline__ void face_flux(const Grid &G, const double *S, int NP
 // (nullable): the extrinsic curvature K_ij of the cell (6 components xx, xy,
 // xz, yy, yz, zz, covariant; component m at kij[m * kst]); when null it
 // follows from the shift by the CFC relation under maximal slicing.
-template <typename MetFn>
+template <bool CA, typename MetFn>
 __device__ __forceinline__ void cell_sources(const Grid &G, const double *pr, MetFn m, bool flat, const double *kij,
                                              long kst, int i, int j, double *s) {
-  const bool geom = G.coord != CART;
+  const bool geom = !CA && G.coord != CART;
   if (flat && !geom) return;
   const double psi = m(0, -1, 0), alpha = m(1, -1, 0);
   double beta[3];
@@ -373,12 +375,12 @@ __device__ __forceinline__ void cell_sources(const Grid &G, const double *pr, Me
     for (int a = 0; a < 3; a++)
 #pragma unroll
       for (int c = 0; c < 3; c++) nb[a][c] = db[a][c];
-    if (G.coord == CYL) {
+    if (!CA && G.coord == CYL) {
       const double R = G.geo.xc0[i + G.g[0]], iR = rcp(R);
       nb[2][0] += -R * beta[2];
       nb[0][2] += iR * beta[2];
       nb[2][2] += iR * beta[0];
-    } else if (G.coord == SPH) {
+    } else if (!CA && G.coord == SPH) {
       const double r = G.geo.xc0[i + G.g[0]], ir = rcp(r);
       const double sn = G.geo.sc1[j + G.g[1]], cs = G.geo.cc1[j + G.g[1]], ct = cs * rcp(sn);
       nb[1][0] += -r * beta[1];
@@ -625,7 +627,10 @@ __device__ __forceinline__ void pass_fluxes(const Grid &G, const double *S, cons
         mb[w] = met[w * G.nv + ob];
       }
     }
-    face_flux<D, REC, R, P>(G, S, NP, ix, ma, mb, ci, cj, ck, Fo, nonflat, pb);
+    double pl[NV], pr[NV];
+    face_states<REC>([&](int v, int m) { return S[v * NP + ix[m]]; }, pl, pr);
+    face_flux<false, D, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + ix[H - 1 + m]]; }, ma, mb, ci, cj, ck, Fo,
+                       nonflat, pb);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; v++) Fo[v] = 0.0;
@@ -747,7 +752,7 @@ __device__ __forceinline__ void stage_staged(const Grid &G, int i0, int j0, int 
         return met[w * G.nv + oc + (a < 0 ? 0 : o * G.s[a])];
       }
     };
-    cell_sources(G, prc, metv, flat && !kij, kij ? kij + oc : nullptr, G.nv, i, j, acc);
+    cell_sources<false>(G, prc, metv, flat && !kij, kij ? kij + oc : nullptr, G.nv, i, j, acc);
   }
   // the caller's loads (the next tile's region) go out together with the
   // loads of the RK combination, so that their latencies overlap
@@ -812,6 +817,280 @@ __device__ __forceinline__ void stage_tile(const Grid &G, int i0, int j0, int k0
   __syncthreads();
   stage_staged<TX, TY, TZ, ND, MODE, REC, R, P>(G, i0, j0, k0, met, qn, qs, out, dtp, ca, cb, sF, kij, NoPrefetch{},
                                                fc);
+}
+
+// The stage of a large Cartesian 3D grid, marched along z: a workgroup owns a
+// column of TX x TY cells, one thread per lower x-face and y-face ((TX + 1)
+// (TY + 1) = NT threads, the last column and row only faces), and takes it
+// plane by plane from z0 to z1.  LDS holds one plane of primitives with REC's
+// halo on a padded rectangle, so that a stencil is one address and immediate
+// offsets, and its metric with a halo of one cell; a lane's upper x-flux is
+// the next lane's, the y-fluxes go through LDS, and a z-face needs no
+// exchange (its lower flux and, with MC, its lower slope are the thread's own
+// from the plane before).  The terms and their order are stage_staged's; the
+// results agree to rounding (where a product fuses into a sum is the
+// compiler's choice per kernel).
+//
+// Bound by the memory pipe and by latency between the phases of a plane: 256
+// VGPRs leave two waves per SIMD (at three, spilled registers cost more memory
+// traffic than the stage itself: 3600 us at 256^3).  256^3, MC, HLLE, per
+// launch: 1737 us (2.7 TB/s; its VALU instructions take 970 us at 4 clocks each) against
+// 2574 us with the tile of 16x4x3 cells, which spends 40% of its instructions
+// on the indices of its plus-shaped region and a quarter of its lanes on
+// idle threads; 117x101x89, MP5, TVDLF: 333 us against 669 us (a tile's halo
+// of three left one workgroup per CU).  Loads cost about 36 clocks of the
+// memory pipe each in rows of 16 lanes, so rows of 32 (31x7 cells) beat rows
+// of 16 (15x15) by 6% although fewer of their faces are shared.
+template <int TX, int TY, int REC>
+struct March {
+  static_assert((TX + 1) * (TY + 1) == NT, "one lower x-face and y-face per thread");
+  static constexpr int H = recon_halo(REC), W = TX + 2 * H, NP = W * (TY + 2 * H);
+  static constexpr int WM = TX + 2, NPM = WM * (TY + 2);
+  static constexpr int NHALO = 2 * H * (TX + TY);
+  static_assert(NHALO <= NT, "one halo cell of a plane per thread");
+  static constexpr int NC = TX * TY;
+  static constexpr int LDS = NV * NP + 5 * NPM + NV * NT + (REC == GMUNU_RECON_MC ? 2 : 1) * NV * NC;
+};
+
+// The value of the wavefront's next lane (0 in the last one).
+__device__ __forceinline__ double lane_next(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x130, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x130, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+template <int TX, int TY, int MODE, int REC, int R, int P>
+__device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z0, int z1,
+                                            const double *__restrict__ prim, const double *__restrict__ met,
+                                            const double *qn, const double *qs, double *out,
+                                            const double *__restrict__ dtp, double ca, double cb, double *sF,
+                                            const double *__restrict__ kij) {
+  static_assert(MODE == 0 || MODE == 1, "the right-hand side or a stage with separate recovery");
+  static_assert(P == 0 || MODE == 1, "the limiter needs the stage's Euler step");
+  using M = March<TX, TY, REC>;
+  constexpr int H = M::H, W = M::W, NP = M::NP, WM = M::WM, NPM = M::NPM;
+  const int tid = threadIdx.x, tx = tid % (TX + 1), ty = tid / (TX + 1);
+  constexpr int NC = M::NC;
+  const int i = i0 + tx, j = j0 + ty, own_at = tx < TX && ty < TY ? tx + TX * ty : 0;
+  // SY: the plane's y-fluxes; SZ, SL: the cell's lower z-flux and, with MC,
+  // its half slope along z (own cells only, so no barrier)
+  double *Sm = sF + NV * NP, *SY = Sm + 5 * NPM, *SZ = SY + NV * NT + own_at, *SL = SZ + NV * NC;
+  const bool own = tx < TX && ty < TY, valid = own && i < G.n[0] && j < G.n[1];
+  const bool fx = ty < TY && i <= G.n[0] && j < G.n[1], fy = tx < TX && i < G.n[0] && j <= G.n[1];
+  // loads past the array (ragged columns) repeat its last cell; no valid
+  // face or cell uses them
+  const int ic = i < G.n[0] + G.g[0] ? i : G.n[0] + G.g[0] - 1, jc = j < G.n[1] + G.g[1] ? j : G.n[1] + G.g[1] - 1;
+  // byte offset of the column inside a plane (planes are at most 2^25 cells);
+  // the plane's base address is uniform
+  unsigned col = 8u * (unsigned)(ic + G.g[0] + (jc + G.g[1]) * G.s[1]);
+  const long s2 = G.s[2];
+  const int p = (tx + H) + W * (ty + H), pm = (tx + 1) + WM * (ty + 1);
+  // this thread's cell of the plane's halo
+  int hx, hy;
+  if (tid < 2 * H * TY) {
+    hx = tid % (2 * H);
+    hy = tid / (2 * H);
+    hx = hx < H ? hx - H : TX + hx - H;
+  } else {
+    const int t = tid - 2 * H * TY;
+    hx = t % TX;
+    hy = t / TX;
+    hy = hy < H ? hy - H : TY + hy - H;
+  }
+  const bool halo = tid < M::NHALO && i0 + hx < G.n[0] + G.g[0] && j0 + hy < G.n[1] + G.g[1];
+  const bool hmet = halo && hx >= -1 && hx <= TX && hy >= -1 && hy <= TY;
+  unsigned hcol = halo ? 8u * (unsigned)(i0 + hx + G.g[0] + (j0 + hy + G.g[1]) * G.s[1]) : col;
+  const int hp = (hx + H) + W * (hy + H), hpm = (hx + 1) + WM * (hy + 1);
+
+  PPBase pp{nullptr, 0.0};
+  if constexpr (P) pp = PPBase{ca == 0.0 ? qn : qs, *dtp};
+  double dt = 0.0;
+  if constexpr (MODE == 1) dt = *dtp;
+
+  // the plane below z0: its own cells alone, for the first face along z
+  double u1[NV], sl[NV];
+  {
+    const long o = (z0 - 1 + G.g[2]) * s2;
+    double u0[NV], m0[5];
+#pragma unroll
+    for (int v = 0; v < NV; v++) {
+      u0[v] = ld(prim + o, G.nv, v, col);
+      u1[v] = ld(prim + o + s2, G.nv, v, col);
+      if constexpr (REC == GMUNU_RECON_MC) sl[v] = mc_half_slope(ld(prim + o - s2, G.nv, v, col), u0[v], u1[v]);
+    }
+#pragma unroll
+    for (int w = 0; w < 5; w++) m0[w] = ld(met + o, G.nv, w, col);
+    if (own) {
+#pragma unroll
+      for (int v = 0; v < NV; v++) {
+        sF[v * NP + p] = u0[v];
+        if constexpr (REC == GMUNU_RECON_MC) SL[v * NC] = sl[v];
+      }
+#pragma unroll
+      for (int w = 0; w < 5; w++) Sm[w * NPM + pm] = m0[w];
+    }
+  }
+  bool nfz = false;
+  __syncthreads();
+  for (int z = z0 - 1; z < z1; z++) {
+    const long o = (z + G.g[2]) * s2;
+    // keeps the addresses a uniform base and a lane's offset (else one 64-bit
+    // pointer per variable and lane lives across the loop, in scratch)
+    asm volatile("" : "+v"(col), "+v"(hcol));
+    bool nonflat = false;
+    double u2[NV], ma[5], mb[5], acc[NV];
+    if constexpr (REC == GMUNU_RECON_MC) {
+#pragma unroll
+      for (int v = 0; v < NV; v++) u2[v] = ld(prim + o + 2 * s2, G.nv, v, col);
+    }
+#pragma unroll
+    for (int w = 0; w < 5; w++) mb[w] = ld(met + o + s2, G.nv, w, col);
+#pragma unroll
+    for (int v = 0; v < NV; v++) acc[v] = 0.0;
+    if (z >= z0) {
+      double pl[NV], pr[NV], Fo[NV];
+      if (fx) {
+        const double *S = sF + p - H;
+        double mc[5];
+#pragma unroll
+        for (int w = 0; w < 5; w++) {
+          ma[w] = Sm[w * NPM + pm - 1];
+          mc[w] = Sm[w * NPM + pm];
+        }
+        face_states<REC>([&](int v, int m) { return S[v * NP + m]; }, pl, pr);
+        face_flux<true, 0, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + H - 1 + m]; }, ma, mc, i, j, z, Fo,
+                                 nonflat, pp);
+      } else {
+#pragma unroll
+        for (int v = 0; v < NV; v++) Fo[v] = 0.0;
+      }
+#pragma unroll
+      for (int v = 0; v < NV; v++) acc[v] -= (lane_next(Fo[v]) - Fo[v]) * G.idx[0];
+      if (fy) {
+        const double *S = sF + p - H * W;
+        double mc[5];
+#pragma unroll
+        for (int w = 0; w < 5; w++) {
+          ma[w] = Sm[w * NPM + pm - WM];
+          mc[w] = Sm[w * NPM + pm];
+        }
+        face_states<REC>([&](int v, int m) { return S[v * NP + m * W]; }, pl, pr);
+        face_flux<true, 1, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + (H - 1 + m) * W]; }, ma, mc, i, j,
+                                 z, Fo, nonflat, pp);
+#pragma unroll
+        for (int v = 0; v < NV; v++) SY[v * NT + tid] = Fo[v];
+      }
+    }
+    // MP5, PPM: the rest of the z-face's stencil (in the caches: this column
+    // read it for the planes before, or stages it next)
+    double uz[4][NV];
+    if constexpr (REC != GMUNU_RECON_MC) {
+#pragma unroll
+      for (int v = 0; v < NV; v++) {
+        uz[0][v] = ld(prim + o - 2 * s2, G.nv, v, col);
+        uz[1][v] = ld(prim + o - s2, G.nv, v, col);
+        uz[2][v] = ld(prim + o + 2 * s2, G.nv, v, col);
+        uz[3][v] = ld(prim + o + 3 * s2, G.nv, v, col);
+      }
+    }
+    double hq[NV], hm[5];  // the next plane's halo
+    if (z + 1 < z1) {
+#pragma unroll
+      for (int v = 0; v < NV; v++) hq[v] = ld(prim + o + s2, G.nv, v, hcol);
+#pragma unroll
+      for (int w = 0; w < 5; w++) hm[w] = ld(met + o + s2, G.nv, w, hcol);
+    }
+    // flat: no x- or y-face of the plane and no z-face of the cell joins
+    // cells of different psi or alpha, and none of them has a shift, so every
+    // centred metric derivative is 0
+    bool flat = !__syncthreads_or(nonflat) && !nfz;
+#pragma unroll
+    for (int w = 0; w < 5; w++) ma[w] = Sm[w * NPM + pm];
+    nfz = valid && (ma[0] != mb[0] || ma[1] != mb[1] || ma[2] != 0.0 || mb[2] != 0.0 || ma[3] != 0.0 ||
+                    mb[3] != 0.0 || ma[4] != 0.0 || mb[4] != 0.0);
+    flat = flat && !nfz;
+    if (valid) {
+      double pl[NV], pr[NV], Fo[NV];
+      if constexpr (REC == GMUNU_RECON_MC) {
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+          const double u0 = sF[v * NP + p], s1 = mc_half_slope(u0, u1[v], u2[v]);
+          pl[v] = u0 + SL[v * NC];
+          pr[v] = u1[v] - s1;
+          SL[v * NC] = s1;
+        }
+      } else {
+        face_states<REC>(
+            [&](int v, int m) { return m == 2 ? sF[v * NP + p] : m == 3 ? u1[v] : uz[m < 2 ? m : m - 2][v]; }, pl, pr);
+      }
+      bool nf = false;
+      face_flux<true, 2, R, P>(G, pl, pr, [&](int v, int m) { return m ? u1[v] : sF[v * NP + p]; }, ma, mb, i, j,
+                               z + 1, Fo, nf, pp);
+      if (z >= z0) {
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+          acc[v] -= (SY[v * NT + tid + TX + 1] - SY[v * NT + tid]) * G.idx[1];
+          acc[v] -= (Fo[v] - SZ[v * NC]) * G.idx[2];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < NV; v++) SZ[v * NC] = Fo[v];
+    }
+    if (valid && z >= z0) {
+      double prc[NV];
+#pragma unroll
+      for (int v = 0; v < NV; v++) prc[v] = sF[v * NP + p];
+      auto metv = [&](int w, int a, int d) -> double {
+        if (a < 0) return ma[w];
+        if (a == 2) return d > 0 ? mb[w] : ld(met + o - s2, G.nv, w, col);
+        return Sm[w * NPM + pm + (a == 0 ? d : d * WM)];
+      };
+      cell_sources<true>(G, prc, metv, flat && !kij, kij ? kij + o + (col >> 3) : nullptr, G.nv, i, j, acc);
+      if constexpr (MODE == 1) {
+        double un[NV], us[NV];
+#pragma unroll
+        for (int v = 0; v < NV; v++) {
+          un[v] = ld(qn + o, G.nv, v, col);
+          us[v] = 0.0;
+        }
+        if (ca != 0.0) {  // the first stage has no q_s
+#pragma unroll
+          for (int v = 0; v < NV; v++) us[v] = ld(qs + o, G.nv, v, col);
+        }
+#pragma unroll
+        for (int v = 0; v < NV; v++)
+          acc[v] = ca == 0.0 ? cb * (un[v] + dt * acc[v]) : ca * un[v] + cb * (us[v] + dt * acc[v]);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; v++)
+        *reinterpret_cast<double *>(reinterpret_cast<char *>(out + o + v * G.nv) + col) = acc[v];
+    }
+    __syncthreads();  // every thread has finished with the plane and its fluxes
+    if (z + 1 < z1) {
+      if (own) {
+#pragma unroll
+        for (int v = 0; v < NV; v++) sF[v * NP + p] = u1[v];
+#pragma unroll
+        for (int w = 0; w < 5; w++) Sm[w * NPM + pm] = mb[w];
+      }
+      if (halo) {
+#pragma unroll
+        for (int v = 0; v < NV; v++) sF[v * NP + hp] = hq[v];
+      }
+      if (hmet) {
+#pragma unroll
+        for (int w = 0; w < 5; w++) Sm[w * NPM + hpm] = hm[w];
+      }
+    }
+    __syncthreads();
+    if constexpr (REC == GMUNU_RECON_MC) {
+#pragma unroll
+      for (int v = 0; v < NV; v++) u1[v] = u2[v];
+    } else {
+#pragma unroll
+      for (int v = 0; v < NV; v++) u1[v] = uz[2][v];
+    }
+  }
 }
 
 // The face-adjacent ghosts of the first `axes` axes whose source is interior
