@@ -249,27 +249,33 @@ void launch_list_any(int li, const BlockRec *B, DList L, const double *dts, doub
   }
 }
 
+long ceil_div(long a, long b) { return (a + b - 1) / b; }
+
+long stage_items(const gmunu_grid_desc &d, int v) {
+  return ceil_div(d.n[0], kVar[v].tx) * ceil_div(d.n[1], kVar[v].ty) * ceil_div(d.n[2], kVar[v].tz);
+}
+
 // Default tile for a block before (or without) tuning.
-int default_variant(const gmunu_grid_desc &d) {
+int default_variant(const gmunu_grid_desc &d, bool few) {
   if (d.recon == GMUNU_RECON_MP5) return d.ndim == 1 ? 10 : d.ndim == 2 ? 9 : 8;
   if (d.recon == GMUNU_RECON_PPM) return d.ndim == 1 ? 13 : d.ndim == 2 ? 12 : 11;
   if (d.ndim == 1) return 7;
   if (d.ndim == 2) return 4;
-  return d.n[0] <= 8 ? 0 : 1;
+  // 3D: 8x8x3 for the smallest; else 8x5x5, the shape that fits most sizes,
+  // unless 16x4x3 covers the block with a tenth fewer tiles (a ragged tile
+  // does the work of a full one): 360 blocks of 8^3, 16^3 and 32^3 take 779 us
+  // per stage with 16x4x3 (176 tiles per 32^3 block), 872 us with 8x5x5 (196
+  // tiles).  Not where blocks are few and of mixed sizes (a server's solves):
+  // there a shape of its own is a launch of its own (18 solves: 1% slower)
+  if (d.n[0] <= 8) return 0;
+  return !few && stage_items(d, 2) * 10 <= stage_items(d, 1) * 9 ? 2 : 1;
 }
-
 
 std::tuple<int, int, int, int, int, int> bucket_of(const gmunu_grid_desc &d) {
   return {d.ndim, d.n[0], d.n[1], d.n[2], d.recon, d.riemann};
 }
 
 int list_of(int variant, const gmunu_grid_desc &d) { return variant + NVAR * (d.riemann == GMUNU_RIEMANN_TVDLF); }
-
-long ceil_div(long a, long b) { return (a + b - 1) / b; }
-
-long stage_items(const gmunu_grid_desc &d, int v) {
-  return ceil_div(d.n[0], kVar[v].tx) * ceil_div(d.n[1], kVar[v].ty) * ceil_div(d.n[2], kVar[v].tz);
-}
 
 long cell_items(const gmunu_grid_desc &d) { return ceil_div((long)d.n[0] * d.n[1] * d.n[2], NT); }
 
@@ -334,6 +340,7 @@ bool shape_fits(const Shape &have, const Shape &want) {
 struct gmunu_batch {
   int maxb, maxg;
   long maxi;
+  bool few;  // few blocks of mixed sizes (batch_few_blocks)
   int ncu;
   std::vector<gmunu_block> blk;
   std::vector<char> used;
@@ -512,7 +519,7 @@ namespace gm {
 
 BatchItems batch_items_for(const gmunu_batch *b, const gmunu_grid_desc &d) {
   BatchItems r;
-  int v = default_variant(d);
+  int v = default_variant(d, b ? b->few : true);
   if (b) {
     auto it = b->tuned.find(bucket_of(d));
     if (it != b->tuned.end()) v = it->second;
@@ -525,6 +532,8 @@ BatchItems batch_items_for(const gmunu_batch *b, const gmunu_grid_desc &d) {
 }
 
 long batch_max_items(const gmunu_batch *b) { return b->maxi; }
+
+void batch_few_blocks(gmunu_batch *b) { b->few = true; }
 
 hipStream_t batch_stream(const gmunu_batch *b) { return b->pstream; }
 
@@ -581,6 +590,7 @@ int gmunu_batch_create(int max_blocks, int max_groups, long max_items, gmunu_bat
   b->maxb = max_blocks;
   b->maxg = max_groups;
   b->maxi = max_items;
+  b->few = false;
   b->blk.resize(max_blocks);
   b->used.assign(max_blocks, 0);
   b->rec.resize(max_blocks);
@@ -698,7 +708,7 @@ int gmunu_batch_set_block(gmunu_batch *b, int slot, const gmunu_block *blk) {
   b->used[slot] = 1;
   b->touch(slot);
   auto it = b->tuned.find(bucket_of(blk->desc));
-  b->var[slot] = it != b->tuned.end() ? it->second : default_variant(blk->desc);
+  b->var[slot] = it != b->tuned.end() ? it->second : default_variant(blk->desc, b->few);
   return GMUNU_OK;
 }
 

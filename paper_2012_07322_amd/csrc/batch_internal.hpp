@@ -19,9 +19,13 @@ struct BatchItems {
   long ghosts;  // items in the ghost list
 };
 
-// b may be null: the default tile variant, as for a batch never tuned.
+// b may be null: the default tile variant of an untuned batch of few blocks.
 BatchItems batch_items_for(const gmunu_batch *b, const gmunu_grid_desc &d);
 long batch_max_items(const gmunu_batch *b);
+
+// The batch will hold few blocks of mixed sizes: untuned blocks share tile
+// shapes, hence launches, where they can.  Before the first block.
+void batch_few_blocks(gmunu_batch *b);
 
 // The batch's private stream, on which its captured steps replay.  A caller
 // that issues all of its work for the batch on this stream saves the events

@@ -154,6 +154,7 @@ struct gmunu_server {
       L.b = nullptr;
       return false;
     }
+    batch_few_blocks(L.b);
     L.st = batch_stream(L.b);
     L.steps = kLaneSteps[k % 3];
     L.round = std::max(1, (spsync + L.steps - 1) / L.steps);
