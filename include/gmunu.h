@@ -206,7 +206,8 @@ int gmunu_step(gmunu_ctx *ctx, double *q_n, double *q_s, double *prim, const dou
  * bit for bit, in fewer launches: the last recovery of each step but the last
  * also writes the CFL maxima of the primitives it has just recovered (which
  * nothing changes before the next step's dt, section 2.9), so only the first
- * step launches the CFL kernel.  Time and dt stay on the device as in
+ * step launches the CFL kernel, and the next step's dt launch advances t, so
+ * only the last one launches for it.  Time and dt stay on the device as in
  * gmunu_step (the call is capturable like it).  nsteps >= 1 (GMUNU_EINVAL
  * otherwise). */
 int gmunu_steps(gmunu_ctx *ctx, double *q_n, double *q_s, double *prim, const double *metric, const double *kij,

@@ -168,8 +168,10 @@ __global__ __launch_bounds__(NT) void k_cfl(const Grid G, const double *__restri
 // Eight independent maxima per thread keep eight loads in flight (the
 // partials of gmunu_steps are one per recovery workgroup: 65536 at 256^3);
 // the maximum does not depend on the order.
+// advance: first take the previous step's *tp += *dtp (a step of gmunu_steps
+// followed by another: one launch fewer).
 __global__ __launch_bounds__(NT) void k_cfl_finish(const double *part, int nparts, double cfl, double t_end,
-                                                   const double *tp, double *dtp) {
+                                                   double *tp, double *dtp, int advance) {
   double mu[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int b = threadIdx.x;
   for (; b + 7 * NT < nparts; b += 8 * NT) {
@@ -181,7 +183,11 @@ __global__ __launch_bounds__(NT) void k_cfl_finish(const double *part, int npart
 #pragma unroll
   for (int u = 0; u < 8; u++) m = fmax(m, mu[u]);
   m = block_max(m);
-  if (threadIdx.x == 0) *dtp = dt_from_rate(m, cfl, tp ? *tp : 0.0, t_end);
+  if (threadIdx.x == 0) {
+    double t = tp ? *tp : 0.0;
+    if (advance) *tp = t = t + *dtp;
+    *dtp = dt_from_rate(m, cfl, t, t_end);
+  }
 }
 
 __global__ void k_advance(double *tp, const double *dtp) { *tp += *dtp; }
@@ -481,7 +487,8 @@ int gmunu_cfl_dt(gmunu_ctx *ctx, const double *prim, const double *metric, doubl
   }
   {
     ProfScope ps(ctx, as_stream(stream), GMUNU_K_OTHER);
-    hipLaunchKernelGGL(k_cfl_finish, dim3(1), dim3(NT), 0, as_stream(stream), ctx->acc, nparts, cfl, t_end, t_dev, dt_dev);
+    hipLaunchKernelGGL(k_cfl_finish, dim3(1), dim3(NT), 0, as_stream(stream), ctx->acc, nparts, cfl, t_end,
+                       const_cast<double *>(t_dev), dt_dev, 0);
   }
   return launch_status();
 }
@@ -528,7 +535,7 @@ namespace {
 // and CFL partials are in place.  cfl_from_part: the CFL maxima are those
 // the previous step's last recovery wrote to ctx->c2pmax (no CFL kernel);
 // part_out (nullable): this step's last recovery writes the next step's
-// maxima there.
+// maxima there, and the next step advances t.
 int step_impl(gmunu_ctx *ctx, double *q_n, double *q_s, double *prim, const double *metric, const double *kij,
               double cfl, double t_end, double *t_dev, double *dt_dev, uint8_t *flags, unsigned int *nfatal_dev,
               void *stream, bool cfl_from_part, double *part_out) {
@@ -537,7 +544,7 @@ int step_impl(gmunu_ctx *ctx, double *q_n, double *q_s, double *prim, const doub
     if (!(cfl > 0.0)) return GMUNU_EINVAL;
     ProfScope ps(ctx, as_stream(stream), GMUNU_K_OTHER);
     hipLaunchKernelGGL(k_cfl_finish, dim3(1), dim3(NT), 0, as_stream(stream), ctx->c2pmax,
-                       (int)nblocks(interior_cells(ctx->G)), cfl, t_end, t_dev, dt_dev);
+                       (int)nblocks(interior_cells(ctx->G)), cfl, t_end, t_dev, dt_dev, 1);
     rc = launch_status();
   } else {
     rc = gmunu_cfl_dt(ctx, prim, metric, cfl, t_end, t_dev, dt_dev, stream);
@@ -555,7 +562,7 @@ int step_impl(gmunu_ctx *ctx, double *q_n, double *q_s, double *prim, const doub
                        dt_dev, as_stream(stream), s == nst - 1 ? part_out : nullptr);
     if (rc) return rc;
   }
-  {
+  if (!part_out) {  // else the next step's k_cfl_finish advances t
     ProfScope ps(ctx, as_stream(stream), GMUNU_K_OTHER);
     hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, as_stream(stream), t_dev, dt_dev);
   }
