@@ -295,16 +295,21 @@ __global__ __launch_bounds__(NT) void k_mg_smooth(const MgGeo G, double *u, cons
 // ---- Line relaxation --------------------------------------------------------
 // An alternative to the paper's point smoother for the anisotropic cells on
 // which section 2.7 notes that point smoothers converge slowly (spherical
-// polar grids).  One workgroup per line (up to kLineThreads lanes, one or
-// more cells per lane).  The line's tridiagonal system (couplings toward the
-// lower and upper neighbour along the line, diagonal, right-hand side) is
-// built in LDS by the lanes, cell by cell, and solved by parallel cyclic
-// reduction: at stride s every row eliminates its couplings to the rows s
-// below and s above, so after ceil(log2 n) doublings each row holds one
-// unknown.  Two copies of the four arrays alternate between doublings.
+// polar grids).  One workgroup per line, a lane per cell (lines have at most
+// kMaxLine cells).  The lane builds its row of the line's tridiagonal system
+// (couplings toward the lower and upper neighbour along the line, right-hand
+// side, all over the diagonal) in registers; parallel cyclic reduction then
+// solves it: at stride s every row eliminates its couplings to the rows s
+// below and s above, which it reads from LDS, so after ceil(log2 n)
+// doublings each row holds one unknown.  Two copies of the three arrays
+// alternate between doublings.
+//
+// Bound by latency (a line is a chain of loads and log2 n doublings on a few
+// wavefronts): the diagonal kept at 1 takes one refined reciprocal per
+// doubling where the four-array form took two divisions (scalar lines, 32 of
+// 640 cells: 9.1 us, 13.1 before; 320 of 64: 6.3, 7.4 before).
 
 constexpr int kLineWave = 64;
-constexpr int kLineThreads = 512;
 constexpr int kCoarseLineThreads = 1024;  // one-workgroup coarsest-level line solvers
 constexpr int kMaxLine = 1024;
 
@@ -348,57 +353,70 @@ __device__ __forceinline__ bool mg_line(const MgGeo &G, int a, int colour, long 
   return true;
 }
 
-// Parallel cyclic reduction of the system in sm (A: lower couplings, B:
-// diagonal, C: upper couplings, D: right-hand side, n entries each, A[0] =
-// C[n-1] = 0) by nl lanes (this one: ln); returns the copy (0 or 1)
-// holding the decoupled rows, whose solution is D / B.  The doublings are
-// separated by workgroup barriers, so every thread of the workgroup calls
-// this with the same n.
-__device__ __forceinline__ int mg_pcr(double *sm, int n, int ln, int nl) {
-  int p = 0;
-  for (int s = 1; s < n; s <<= 1) {
-    const double *A = sm + p * 4 * n, *B = A + n, *C = B + n, *D = C + n;
-    double *A2 = sm + (1 - p) * 4 * n, *B2 = A2 + n, *C2 = B2 + n, *D2 = C2 + n;
-    for (int m = ln; m < n; m += nl) {
-      double b = B[m], d = D[m], na = 0.0, nc = 0.0;
-      if (m >= s) {
-        const double al = -A[m] / B[m - s];
-        na = al * A[m - s];
-        b += al * C[m - s];
-        d += al * D[m - s];
-      }
-      if (m + s < n) {
-        const double ga = -C[m] / B[m + s];
-        nc = ga * C[m + s];
-        b += ga * A[m + s];
-        d += ga * D[m + s];
-      }
-      A2[m] = na;
-      B2[m] = b;
-      C2[m] = nc;
-      D2[m] = d;
-    }
-    __syncthreads();
-    p ^= 1;
-  }
-  return p;
+// Order of LDS accesses between the lanes of one wavefront.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One Newton step of the line from cell c along axis ax by nl lanes (this
-// one: ln; LDS sm of 8 n doubles; live = false: lanes with no line that
-// only keep the workgroup's barriers) with the exact Jacobian with
-// respect to the line's cells: the couplings along the line, on the
-// diagonal mg_L's dL/du plus, across each non-periodic boundary face of
-// the cell, the weight toward the ghost times its boundary-rule factor (the
-// ghost follows the cell); right-hand side f - L(u); u += the solution.
+// Orders the LDS accesses of the lanes of a line: those of one wavefront, or
+// of the workgroup.
+__device__ __forceinline__ void mg_line_sync(bool one_wave) {
+  if (one_wave)
+    wave_fence();
+  else
+    __syncthreads();
+}
+
+// Parallel cyclic reduction of NS systems of n rows at once, row m in this
+// lane's registers (a x_{m-s} + x_m + c x_{m+s} = d, s = 1; rows of lanes with
+// !on do not exist): on return d is the solution.  sm: 6 NS n doubles.
+template <int NS>
+__device__ __forceinline__ void mg_pcr(double *sm, int n, int m, bool on, bool one_wave, double *a, double *c,
+                                       double *d) {
+  for (int s = 1, p = 0; s < n; s <<= 1, p ^= 1) {
+    double *R = sm + p * 3 * NS * n;
+    if (on) {
+#pragma unroll
+      for (int q = 0; q < NS; q++) {
+        R[3 * q * n + m] = a[q];
+        R[(3 * q + 1) * n + m] = c[q];
+        R[(3 * q + 2) * n + m] = d[q];
+      }
+    }
+    mg_line_sync(one_wave);
+    if (on) {
+      // (a row without a neighbour s away has no coupling to it)
+      const int lo = m >= s ? m - s : m, hi = m + s < n ? m + s : m;
+#pragma unroll
+      for (int q = 0; q < NS; q++) {
+        const double *A = R + 3 * q * n, *C = A + n, *D = C + n;
+        const double al = -a[q], ga = -c[q];
+        const double ib = rcp(1.0 + al * C[lo] + ga * A[hi]);
+        a[q] = al * A[lo] * ib;
+        c[q] = ga * C[hi] * ib;
+        d[q] = (d[q] + al * D[lo] + ga * D[hi]) * ib;
+      }
+    }
+  }
+}
+
+// One Newton step of the line through cell c along axis ax, cell m of it in
+// this lane (live: the line exists): the residual's derivative on the line
+// from the operator's couplings and diagonal (boundary faces folded in),
+// everything off the line at its current value.  sm: 6 n doubles of the line.
 __device__ __forceinline__ void mg_line_step(const MgGeo &G, double *u, const double *__restrict__ f,
                                              const double *__restrict__ a, const double *__restrict__ a2, int ax,
-                                             const int c[3], bool live, double *sm, int ln, int nl) {
+                                             const int c[3], bool live, double *sm, int m, bool one_wave) {
   const int n = G.n[ax];
-  for (int m = ln; live && m < n; m += nl) {
+  const bool on = live && m < n;
+  double wm = 0.0, wp = 0.0, d = 0.0;
+  long o = 0;
+  if (on) {
     const int cc[3] = {ax == 0 ? m : c[0], ax == 1 ? m : c[1], ax == 2 ? m : c[2]};
-    const long o = mg_off(G, cc[0], cc[1], cc[2]);
-    double dg, wm, wp;
+    o = mg_off(G, cc[0], cc[1], cc[2]);
+    double dg;
     const double Lu = mg_L<false>(G, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, cc[0], cc[1], cc[2], o, &dg);
 #pragma unroll
     for (int b = 0; b < 3; b++) {
@@ -408,29 +426,22 @@ __device__ __forceinline__ void mg_line_step(const MgGeo &G, double *u, const do
       if (cc[b] == G.n[b] - 1) dg += wp * mg_fold(G, cc, b, true);
     }
     mg_w(G, cc[0] + G.g[0], cc[1] + G.g[1], ax, wm, wp);
-    if (m == 0) wm = 0.0;
-    if (m == n - 1) wp = 0.0;
-    sm[m] = wm;
-    sm[n + m] = dg;
-    sm[2 * n + m] = wp;
-    sm[3 * n + m] = f[o] - Lu;
+    const double id = rcp(dg);
+    wm = m == 0 ? 0.0 : wm * id;
+    wp = m == n - 1 ? 0.0 : wp * id;
+    d = (f[o] - Lu) * id;
   }
-  __syncthreads();
-  const double *R = sm + mg_pcr(sm, n, ln, nl) * 4 * n;
-  for (int m = ln; live && m < n; m += nl) {
-    const int cc[3] = {ax == 0 ? m : c[0], ax == 1 ? m : c[1], ax == 2 ? m : c[2]};
-    u[mg_off(G, cc[0], cc[1], cc[2])] += R[3 * n + m] / R[n + m];
-  }
+  mg_pcr<1>(sm, n, m, on, one_wave, &wm, &wp, &d);
+  if (on) u[o] += d;
 }
 
-// Lines of one colour along axis ax, one workgroup per line.
-__global__ __launch_bounds__(kLineThreads) void k_mg_line(const MgGeo G, double *u, const double *__restrict__ f,
-                                                          const double *__restrict__ a,
-                                                          const double *__restrict__ a2, int ax, int colour) {
+__global__ __launch_bounds__(kMaxLine) void k_mg_line(const MgGeo G, double *u, const double *__restrict__ f,
+                                                      const double *__restrict__ a, const double *__restrict__ a2,
+                                                      int ax, int colour) {
   extern __shared__ double sm[];
   int c[3];
   if (!mg_line(G, ax, colour, blockIdx.x, c)) return;
-  mg_line_step(G, u, f, a, a2, ax, c, true, sm, threadIdx.x, blockDim.x);
+  mg_line_step(G, u, f, a, a2, ax, c, true, sm, threadIdx.x, blockDim.x == kLineWave);
 }
 
 // Number of lines of colour `colour` along axis a.
@@ -442,34 +453,36 @@ __host__ __device__ __forceinline__ long mg_line_count(const MgGeo &G, int a, in
 }
 
 // The coarsest-level solver of the line smoother: `sweeps` line sweeps by
-// one workgroup of kCoarseLineThreads threads, its wavefronts taking a
-// colour's lines in rounds, colours and axes separated by barriers.
-// Dynamic LDS: the level's u, f (and the given a, a2) copied in and u
-// copied back, then 8 nmax doubles per wavefront for the line systems.
+// one workgroup, `lanes` lanes to a line, a colour's lines in rounds, colours
+// and axes separated by barriers.  Dynamic LDS: the level's u, f (and the
+// given a, a2) copied in and u copied back, then 6 nmax doubles per line at
+// work.  No more wavefronts than a colour has lines, and no barrier inside a
+// line of one wavefront: 10 wavefronts on 20x2 cells take 54.6 us, 16 meeting
+// at a barrier per doubling took 86.8.
 __global__ __launch_bounds__(kCoarseLineThreads) void k_mg_line_coarse(const MgGeo G, double *u,
                                                                        const double *__restrict__ f,
                                                                        const double *__restrict__ a,
                                                                        const double *__restrict__ a2, int sweeps,
-                                                                       int nmax) {
+                                                                       int nmax, int lanes) {
   extern __shared__ double sm[];
   double *p = sm, *uu = p;
-  for (long e = threadIdx.x; e < G.nt; e += kCoarseLineThreads) p[e] = u[e];
+  for (long e = threadIdx.x; e < G.nt; e += blockDim.x) p[e] = u[e];
   p += G.nt;
-  for (long e = threadIdx.x; e < G.nt; e += kCoarseLineThreads) p[e] = f[e];
+  for (long e = threadIdx.x; e < G.nt; e += blockDim.x) p[e] = f[e];
   const double *ff = p, *aa = nullptr, *aa2 = nullptr;
   p += G.nt;
   if (a) {
-    for (long e = threadIdx.x; e < G.nt; e += kCoarseLineThreads) p[e] = a[e];
+    for (long e = threadIdx.x; e < G.nt; e += blockDim.x) p[e] = a[e];
     aa = p;
     p += G.nt;
   }
   if (a2) {
-    for (long e = threadIdx.x; e < G.nt; e += kCoarseLineThreads) p[e] = a2[e];
+    for (long e = threadIdx.x; e < G.nt; e += blockDim.x) p[e] = a2[e];
     aa2 = p;
     p += G.nt;
   }
   __syncthreads();
-  const int w = threadIdx.x / kLineWave, ln = threadIdx.x % kLineWave, nw = kCoarseLineThreads / kLineWave;
+  const int w = threadIdx.x / lanes, ln = threadIdx.x % lanes, nw = blockDim.x / lanes;
   for (int s = 0; s < sweeps; s++)
     for (int ax = 0; ax < G.ndim; ax++) {
       if (G.bc[ax][0] == GMUNU_MG_PERIODIC) continue;
@@ -478,12 +491,12 @@ __global__ __launch_bounds__(kCoarseLineThreads) void k_mg_line_coarse(const MgG
         for (long t0 = 0; t0 < nl; t0 += nw) {
           int c[3] = {0, 0, 0};
           const bool live = mg_line(G, ax, col, t0 + w, c);
-          mg_line_step(G, uu, ff, aa, aa2, ax, c, live, p + (long)w * 8 * nmax, ln, kLineWave);
+          mg_line_step(G, uu, ff, aa, aa2, ax, c, live, p + (long)w * 6 * nmax, ln, lanes == kLineWave);
           __syncthreads();
         }
       }
     }
-  for (long e = threadIdx.x; e < G.nt; e += kCoarseLineThreads) u[e] = uu[e];
+  for (long e = threadIdx.x; e < G.nt; e += blockDim.x) u[e] = uu[e];
 }
 
 // out = L(u) on the interior.
@@ -799,13 +812,6 @@ __device__ __forceinline__ void mg_tail_cell(const MgLev &V, int t, int &i, int 
   i = t - r * V.n[0];
   k = mg_div(r, V.mn1);
   j = r - k * V.n[1];
-}
-
-// Order of LDS accesses between the lanes of one wavefront.
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Sum over the 2^ndim lanes of one coarse cell.
@@ -2193,6 +2199,27 @@ __global__ __launch_bounds__(NT) void k_mgv_coarse(const MgGeo G, double *u, con
     for (long e = threadIdx.x; e < n3; e += NT) u[e] = uu[e];
 }
 
+// Row of component q's line system at cell cc: diagonal dg of the operator,
+// residual r; over the diagonal with the boundary faces folded in.
+__device__ __forceinline__ void mgv_line_row(const MgGeo &G, int ax, const int cc[3], int q, double dg, double r,
+                                             double &wa, double &wc, double &d) {
+  double wm, wp;
+#pragma unroll
+  for (int b = 0; b < 3; b++) {
+    if (b >= G.ndim || G.bc[b][0] == GMUNU_MG_PERIODIC || (cc[b] > 0 && cc[b] < G.n[b] - 1)) continue;
+    const double kb = b == q ? 4.0 / 3.0 : 1.0;
+    mg_w(G, cc[0] + G.g[0], cc[1] + G.g[1], b, wm, wp);
+    if (cc[b] == 0) dg += (G.vodd[b][0] >> q) & 1 ? -kb * wm : kb * wm;
+    if (cc[b] == G.n[b] - 1) dg += (G.vodd[b][1] >> q) & 1 ? -kb * wp : kb * wp;
+  }
+  const double id = rcp(dg), ki = ax == q && q < G.ndim ? 4.0 / 3.0 * id : id;
+  mg_w(G, cc[0] + G.g[0], cc[1] + G.g[1], ax, wm, wp);
+  const int m = ax == 0 ? cc[0] : ax == 1 ? cc[1] : cc[2];
+  wa = m == 0 ? 0.0 : wm * ki;
+  wc = m == G.n[ax] - 1 ? 0.0 : wp * ki;
+  d = r * id;
+}
+
 // Line relaxation of the vector equations, the line from cell c along
 // axis ax by one wavefront (as mg_line_step): the components one after the
 // other, each a Newton step of its own equation with its exact Jacobian
@@ -2203,64 +2230,212 @@ __global__ __launch_bounds__(NT) void k_mgv_coarse(const MgGeo G, double *u, con
 // mirror ghost times the component's sign there -- and everything else
 // (the other components included) at its current value.
 __device__ __forceinline__ void mgv_line_step(const MgGeo &G, double *u, const double *__restrict__ f, int ax,
-                                              const int c[3], bool live, double *sm, int ln, int nl) {
+                                              const int c[3], bool live, double *sm, int m, bool one_wave) {
   const int n = G.n[ax];
+  const bool on = live && m < n;
+  const int cc[3] = {ax == 0 ? m : c[0], ax == 1 ? m : c[1], ax == 2 ? m : c[2]};
+  const long o = on ? mg_off(G, cc[0], cc[1], cc[2]) : 0;
   for (int q = 0; q < 3; q++) {
-    const double kap = ax == q && q < G.ndim ? 4.0 / 3.0 : 1.0;
-    for (int m = ln; live && m < n; m += nl) {
-      const int cc[3] = {ax == 0 ? m : c[0], ax == 1 ? m : c[1], ax == 2 ? m : c[2]};
-      const long o = mg_off(G, cc[0], cc[1], cc[2]);
-      double L[3], idg[3], wm, wp;
+    double wm = 0.0, wp = 0.0, d = 0.0;
+    if (on) {
+      double L[3], idg[3];
       mgv_L(G, u, o, cc[0], cc[1], cc[2], L, idg);
-      double dg = 1.0 / idg[q];
-#pragma unroll
-      for (int b = 0; b < 3; b++) {
-        if (b >= G.ndim || G.bc[b][0] == GMUNU_MG_PERIODIC || (cc[b] > 0 && cc[b] < G.n[b] - 1)) continue;
-        const double kb = b == q ? 4.0 / 3.0 : 1.0;
-        mg_w(G, cc[0] + G.g[0], cc[1] + G.g[1], b, wm, wp);
-        if (cc[b] == 0) dg += (G.vodd[b][0] >> q) & 1 ? -kb * wm : kb * wm;
-        if (cc[b] == G.n[b] - 1) dg += (G.vodd[b][1] >> q) & 1 ? -kb * wp : kb * wp;
-      }
-      mg_w(G, cc[0] + G.g[0], cc[1] + G.g[1], ax, wm, wp);
-      wm = m == 0 ? 0.0 : kap * wm;
-      wp = m == n - 1 ? 0.0 : kap * wp;
-      sm[m] = wm;
-      sm[n + m] = dg;
-      sm[2 * n + m] = wp;
-      sm[3 * n + m] = f[q * G.nt + o] - L[q];
+      mgv_line_row(G, ax, cc, q, rcp(idg[q]), f[q * G.nt + o] - L[q], wm, wp, d);
     }
-    __syncthreads();
-    const double *R = sm + mg_pcr(sm, n, ln, nl) * 4 * n;
-    for (int m = ln; live && m < n; m += nl) {
-      const int cc[3] = {ax == 0 ? m : c[0], ax == 1 ? m : c[1], ax == 2 ? m : c[2]};
-      u[q * G.nt + mg_off(G, cc[0], cc[1], cc[2])] += R[3 * n + m] / R[n + m];
-    }
-    __syncthreads();
+    mg_pcr<1>(sm, n, m, on, one_wave, &wm, &wp, &d);
+    if (on) u[q * G.nt + o] += d;
+    mg_line_sync(one_wave);
   }
 }
 
-__global__ __launch_bounds__(kLineThreads) void k_mgv_line(const MgGeo G, double *u, const double *__restrict__ f,
-                                                           int ax, int colour) {
+// The same on axisymmetric (2D cylindrical or spherical) levels.  There the
+// third component enters no other's equation nor they its own, so that it is
+// solved beside the first (PAIR; one after the other where the line's LDS
+// would pass 64 KB: the results are the same), and a cell's operands (nine
+// values of the first two components, five of the third) are loaded once and
+// kept in registers: the second component's equation takes the first one's
+// update, its neighbours' along the line from LDS.  A line otherwise waits
+// three times for memory and computes all three operators per component:
+// 320 lines of 64 cells 22.8 us, now 12.6; 32 lines of 640 cells 41.4 us,
+// now 18.8.  sm: (PAIR ? 12 : 7) n doubles.
+template <bool PAIR>
+__device__ __forceinline__ void mgv_line_curv(const MgGeo &G, double *u, const double *__restrict__ f, int ax,
+                                              const int c[3], bool live, double *sm, int m, bool one_wave) {
+  constexpr int NS = PAIR ? 2 : 1;
+  const int n = G.n[ax];
+  const bool on = live && m < n;
+  const int cc[3] = {ax == 0 ? m : c[0], ax == 0 ? c[1] : m, 0};
+  const long nt = G.nt;
+  double U0[3][3], U1[3][3], U2[3][3], fv[3] = {0.0, 0.0, 0.0};
+  bool flip0[3][3];
+  int along[3];           // step along the line of the neighbours m - 1, m, m + 1 (0 where the rule folds it)
+  bool line[3];           // the transverse neighbour is on the line (the line itself, or folded onto it)
+  VStep s;
+  s.neg = 0;
+  long o = 0;
+  if (on) {
+    o = mg_off(G, cc[0], cc[1], cc[2]);
+    s = mgv_steps(G, cc[0], cc[1], 0);
+  }
+  const int d0[3] = {s.dm[0], 0, s.dp[0]}, d1[3] = {s.dm[1], 0, s.dp[1]};
+#pragma unroll
+  for (int e = 0; e < 3; e++) {
+    const int da = ax == 0 ? d0[e] : d1[e], dt = ax == 0 ? d1[e] : d0[e];
+    along[e] = da == 0 ? 0 : e - 1;
+    line[e] = dt == 0;
+  }
+  if (on) {
+#pragma unroll
+    for (int x = 0; x < 3; x++)
+#pragma unroll
+      for (int y = 0; y < 3; y++) {
+        const long at = o + d0[x] + d1[y];
+        // signs of the two steps for components 0, 1, 2 (bit 6 q + a: minus, + 3: plus)
+        const unsigned nx = x == 1 ? 0u : s.neg >> (x == 2 ? 3 : 0), ny = y == 1 ? 0u : s.neg >> (y == 2 ? 4 : 1);
+        const unsigned neg = nx ^ ny;
+        flip0[x][y] = neg & 1;
+        U0[x][y] = mgv_flip(u[at], neg & 1);
+        U1[x][y] = mgv_flip(u[nt + at], (neg >> 6) & 1);
+        if (x == 1 || y == 1) U2[x][y] = mgv_flip(u[2 * nt + at], (neg >> 12) & 1);
+      }
+#pragma unroll
+    for (int q = 0; q < 3; q++) fv[q] = f[q * nt + o];
+  }
+  const int I = cc[0] + G.g[0], J = cc[1] + G.g[1];
+  const bool sph = G.coord == GMUNU_SPH;
+  const double h0 = G.h[0], i2h1 = rcp(2.0 * G.h[1]), i4h = rcp(4.0 * h0 * G.h[1]);
+  double w0m = 0.0, w0p = 0.0, w1m = 0.0, w1p = 0.0, sn = 1.0, sgm = 1.0, sgp = 1.0;
+  if (on) {
+    mg_w(G, I, J, 0, w0m, w0p);
+    mg_w(G, I, J, 1, w1m, w1p);
+    if (sph) {
+      sn = G.sg1[J];
+      sgm = G.sg1[J - 1];
+      sgp = G.sg1[J + 1];
+    }
+  }
+  const double r = G.x0[0] + (cc[0] + 0.5) * h0, ir = rcp(r), ir2 = ir * ir, rm = r - h0, rp = r + h0;
+  const double is = sph ? rcp(sn) : 1.0, is2 = is * is;
+  const double dl0 = -(w0m + w0p), dl1 = -(w1m + w1p), dlap = dl0 + dl1;
+  double wa[NS], wc[NS], d[NS], xq[3];
+  auto second = [&](const double (&U)[3][3], double &l0, double &l1) {
+    l0 = w0p * (U[2][1] - U[1][1]) - w0m * (U[1][1] - U[0][1]);
+    l1 = w1p * (U[1][2] - U[1][1]) - w1m * (U[1][1] - U[1][0]);
+  };
+  auto zero = [&](int k) { wa[k] = wc[k] = d[k] = 0.0; };
+  auto row0 = [&](int k) {
+    double l0, l1, L, dg;
+    second(U0, l0, l1);
+    const double u0 = U0[1][1];
+    if (sph) {
+      const double dth = (sgp * U1[1][2] - sgm * U1[1][0]) * i2h1;
+      // (1/sin) d_r d_th (sin A_th / r) without dividing by a corner radius
+      const double mix = ((sgp * (U1[2][2] - U1[0][2]) - sgm * (U1[2][0] - U1[0][0])) * (i4h * ir) - dth * ir2) * is;
+      L = l0 + l1 - 2.0 * u0 * ir2 - 2.0 * ir2 * is * dth + (l0 - 2.0 * u0 * ir2 + mix) * (1.0 / 3.0);
+      dg = dlap - 2.0 * ir2 + (dl0 - 2.0 * ir2) * (1.0 / 3.0);
+    } else {
+      const double mix = (U1[2][2] - U1[2][0] - U1[0][2] + U1[0][0]) * i4h;
+      L = l0 + l1 - u0 * ir2 + (l0 - u0 * ir2 + mix) * (1.0 / 3.0);
+      dg = dlap - ir2 + (dl0 - ir2) * (1.0 / 3.0);
+    }
+    mgv_line_row(G, ax, cc, 0, dg, fv[0] - L, wa[k], wc[k], d[k]);
+  };
+  auto row1 = [&](int k) {
+    double l0, l1, L, dg;
+    second(U1, l0, l1);
+    const double u1 = U1[1][1];
+    if (sph) {
+      const double dr = (U0[1][2] - U0[1][0]) * i2h1;
+      const double mix = (rp * rp * (U0[2][2] - U0[2][0]) - rm * rm * (U0[0][2] - U0[0][0])) * (i4h * ir2 * ir);
+      L = l0 + l1 - u1 * ir2 * is2 + 2.0 * ir2 * dr + (mix + l1 - u1 * ir2 * is2) * (1.0 / 3.0);
+      dg = dlap - ir2 * is2 + (dl1 - ir2 * is2) * (1.0 / 3.0);
+    } else {
+      const double mix = (rp * (U0[2][2] - U0[2][0]) - rm * (U0[0][2] - U0[0][0])) * (i4h * ir);
+      L = l0 + l1 + (mix + l1) * (1.0 / 3.0);
+      dg = dlap + dl1 * (1.0 / 3.0);
+    }
+    mgv_line_row(G, ax, cc, 1, dg, fv[1] - L, wa[k], wc[k], d[k]);
+  };
+  auto row2 = [&](int k) {
+    double l0, l1;
+    second(U2, l0, l1);
+    mgv_line_row(G, ax, cc, 2, dlap - ir2 * is2, fv[2] - (l0 + l1 - U2[1][1] * ir2 * is2), wa[k], wc[k], d[k]);
+  };
+  if (!PAIR) {
+    on ? row2(0) : zero(0);
+    mg_pcr<NS>(sm, n, m, on, one_wave, wa, wc, d);
+    xq[2] = d[0];
+    mg_line_sync(one_wave);
+  }
+  on ? row0(0) : zero(0);
+  if (PAIR) on ? row2(NS - 1) : zero(NS - 1);
+  mg_pcr<NS>(sm, n, m, on, one_wave, wa, wc, d);
+  xq[0] = d[0];
+  if (PAIR) xq[2] = d[NS - 1];
+  // the first component's update, for the neighbours: beyond the systems, or in
+  // the last sixth of the copy that the last doubling did not read (the second
+  // component's doublings reach it only after a barrier)
+  const int doublings = 32 - __clz(n - 1);
+  double *X = PAIR ? sm + ((doublings & 1) * 6 + 5) * n : sm + 6 * n;
+  if (on) X[m] = xq[0];
+  mg_line_sync(one_wave);
+  double xa[1] = {0.0}, xc[1] = {0.0}, xd[1] = {0.0};
+  if (on) {
+    const double dx[3] = {X[m + along[0]], xq[0], X[m + along[2]]};
+#pragma unroll
+    for (int x = 0; x < 3; x++)
+#pragma unroll
+      for (int y = 0; y < 3; y++)
+        if (line[ax == 0 ? y : x]) U0[x][y] += mgv_flip(dx[ax == 0 ? x : y], flip0[x][y]);
+    row1(0);
+    xa[0] = wa[0];
+    xc[0] = wc[0];
+    xd[0] = d[0];
+  }
+  mg_pcr<1>(sm, n, m, on, one_wave, xa, xc, xd);
+  if (on) {
+    u[o] += xq[0];
+    u[nt + o] = U1[1][1] + xd[0];
+    u[2 * nt + o] = U2[1][1] + xq[2];
+  }
+}
+
+// KIND 0: any level; 1 and 2: axisymmetric levels, the third component
+// apart or paired (mgv_line_curv).
+template <int KIND>
+__device__ __forceinline__ void mgv_line_any(const MgGeo &G, double *u, const double *__restrict__ f, int ax,
+                                             const int c[3], bool live, double *sm, int m, bool one_wave) {
+  if constexpr (KIND == 0)
+    mgv_line_step(G, u, f, ax, c, live, sm, m, one_wave);
+  else
+    mgv_line_curv<KIND == 2>(G, u, f, ax, c, live, sm, m, one_wave);
+}
+
+template <int KIND, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_mgv_line(const MgGeo G, double *u, const double *__restrict__ f, int ax,
+                                                      int colour) {
   extern __shared__ double sm[];
   int c[3];
   if (!mg_line(G, ax, colour, blockIdx.x, c)) return;
-  mgv_line_step(G, u, f, ax, c, true, sm, threadIdx.x, blockDim.x);
+  mgv_line_any<KIND>(G, u, f, ax, c, true, sm, threadIdx.x, blockDim.x == kLineWave);
 }
 
 // Coarsest level of the vector equations (as k_mg_line_coarse): X and f
-// staged in LDS, then 8 nmax doubles per wavefront.
-__global__ __launch_bounds__(kCoarseLineThreads) void k_mgv_line_coarse(const MgGeo G, double *u,
+// staged in LDS, then 12 nmax doubles per line at work (52.9 us on 20x2 cells,
+// 181 with the general step).
+template <int KIND>
+__global__ __launch_bounds__(KIND ? kCoarseLineThreads : 512) void k_mgv_line_coarse(const MgGeo G, double *u,
                                                                         const double *__restrict__ f, int sweeps,
-                                                                        int nmax) {
+                                                                        int nmax, int lanes) {
   extern __shared__ double sm[];
   const long n3 = 3 * G.nt;
-  for (long e = threadIdx.x; e < n3; e += kCoarseLineThreads) {
+  for (long e = threadIdx.x; e < n3; e += blockDim.x) {
     sm[e] = u[e];
     sm[n3 + e] = f[e];
   }
   __syncthreads();
   double *lines = sm + 2 * n3;
-  const int w = threadIdx.x / kLineWave, ln = threadIdx.x % kLineWave, nw = kCoarseLineThreads / kLineWave;
+  const int w = threadIdx.x / lanes, ln = threadIdx.x % lanes, nw = blockDim.x / lanes;
   for (int s = 0; s < sweeps; s++)
     for (int ax = 0; ax < G.ndim; ax++) {
       if (G.bc[ax][0] == GMUNU_MG_PERIODIC) continue;
@@ -2269,11 +2444,12 @@ __global__ __launch_bounds__(kCoarseLineThreads) void k_mgv_line_coarse(const Mg
         for (long t0 = 0; t0 < nl; t0 += nw) {
           int c[3] = {0, 0, 0};
           const bool live = mg_line(G, ax, col, t0 + w, c);
-          mgv_line_step(G, sm, sm + n3, ax, c, live, lines + (long)w * 8 * nmax, ln, kLineWave);
+          mgv_line_any<KIND>(G, sm, sm + n3, ax, c, live, lines + (long)w * 12 * nmax, ln, lanes == kLineWave);
+          __syncthreads();
         }
       }
     }
-  for (long e = threadIdx.x; e < n3; e += kCoarseLineThreads) u[e] = sm[e];
+  for (long e = threadIdx.x; e < n3; e += blockDim.x) u[e] = sm[e];
 }
 
 __global__ __launch_bounds__(NT) void k_mgv_apply(const MgGeo G, const double *__restrict__ u,
@@ -2861,11 +3037,8 @@ void ghosts(const MgGeo &G, double *u, hipStream_t st) {
   if (gc) hipLaunchKernelGGL(k_mg_ghosts<1>, dim3(nblocks(gc)), dim3(NT), 0, st, G, u);
 }
 
-// Threads per line workgroup: a lane per cell up to kLineThreads.
-int line_threads(int n) {
-  const int t = (n + kLineWave - 1) / kLineWave * kLineWave;
-  return t < kLineThreads ? t : kLineThreads;
-}
+// Threads per line workgroup: a lane per cell, whole wavefronts.
+int line_threads(int n) { return (n + kLineWave - 1) / kLineWave * kLineWave; }
 
 // Line sweeps: per sweep every non-periodic axis, per axis its colours.
 void line_sweeps(const MgGeo &G, double *u, const double *f, const double *a, const double *a2, int sweeps,
@@ -2873,7 +3046,7 @@ void line_sweeps(const MgGeo &G, double *u, const double *f, const double *a, co
   for (int s = 0; s < sweeps; s++)
     for (int ax = 0; ax < G.ndim; ax++) {
       if (G.bc[ax][0] == GMUNU_MG_PERIODIC) continue;
-      const size_t lds = 8 * (size_t)G.n[ax] * sizeof(double);
+      const size_t lds = 6 * (size_t)G.n[ax] * sizeof(double);
       for (int c = 0; c < 1 << (G.ndim - 1); c++)
         hipLaunchKernelGGL(k_mg_line, dim3(mg_line_count(G, ax, c)), dim3(line_threads(G.n[ax])), lds, st, G, u, f,
                            a, a2, ax, c);
@@ -2888,12 +3061,28 @@ int line_nmax(const MgGeo &G) {
   return nmax;
 }
 
-// Dynamic LDS of a one-workgroup coarsest line solve staging `arrays`
-// level arrays (0: does not fit).
-size_t line_coarse_lds(const MgGeo &G, int arrays) {
-  const size_t b =
-      ((size_t)arrays * G.nt + (size_t)(kCoarseLineThreads / kLineWave) * 8 * line_nmax(G)) * sizeof(double);
-  return b <= 64 * 1024 ? b : 0;
+// A one-workgroup coarsest line solve staging `arrays` level arrays, with
+// `per` doubles per cell of a line at work: lanes per line (a wavefront, or
+// several for longer lines), as many lines at once as a colour has and as
+// fit; lds = 0: does not fit.
+struct LineCoarse {
+  int lanes, threads;
+  size_t lds;
+};
+LineCoarse line_coarse(const MgGeo &G, int arrays, int per, int max_threads = kCoarseLineThreads) {
+  LineCoarse r{line_threads(line_nmax(G)), 0, 0};
+  long lines = 1;
+  for (int ax = 0; ax < G.ndim; ax++)
+    if (G.bc[ax][0] != GMUNU_MG_PERIODIC) {
+      const long c = mg_line_count(G, ax, 0);
+      lines = c > lines ? c : lines;
+    }
+  const long most = max_threads / r.lanes;
+  lines = lines < most ? lines : most;
+  r.threads = (int)lines * r.lanes;
+  const size_t b = ((size_t)arrays * G.nt + (size_t)lines * per * line_nmax(G)) * sizeof(double);
+  r.lds = lines > 0 && b <= 64 * 1024 ? b : 0;
+  return r;
 }
 
 // Smoothing sweeps in place (boundary rule inline: no ghost fill between
@@ -3091,10 +3280,10 @@ void launch_tail(gmunu_mg *m, bool use_fmg, hipStream_t st) {
 void coarse_solve(gmunu_mg *m, hipStream_t st) {
   const MgGeo &G = m->geo[0];
   if (G.line) {
-    const size_t lds = line_coarse_lds(G, 2 + (m->a[0] ? 1 : 0) + (m->a2[0] ? 1 : 0));
-    if (cells(G) <= 64L * NT && lds)
-      hipLaunchKernelGGL(k_mg_line_coarse, dim3(1), dim3(kCoarseLineThreads), lds, st, G, m->u[0], m->f[0],
-                         m->a[0], m->a2[0], m->d.coarse, line_nmax(G));
+    const LineCoarse p = line_coarse(G, 2 + (m->a[0] ? 1 : 0) + (m->a2[0] ? 1 : 0), 6);
+    if (cells(G) <= 64L * NT && p.lds)
+      hipLaunchKernelGGL(k_mg_line_coarse, dim3(1), dim3(p.threads), p.lds, st, G, m->u[0], m->f[0], m->a[0],
+                         m->a2[0], m->d.coarse, line_nmax(G), p.lanes);
     else
       line_sweeps(G, m->u[0], m->f[0], m->a[0], m->a2[0], m->d.coarse, st);
     return;
@@ -3230,6 +3419,9 @@ long colour_cells(const MgGeo &G, int c) {
   return n;
 }
 
+// Levels whose vector lines take mgv_line_curv.
+bool axisymmetric(const MgGeo &G) { return G.ndim == 2 && G.coord != GMUNU_CART; }
+
 // Sweeps over the 2^ndim colours: two colours per launch (k_mgv_smooth2)
 // when a row's half fits in 4 passes of a workgroup, else one per launch.
 void vsweeps(const MgGeo &G, double *u, const double *f, int sweeps, hipStream_t st) {
@@ -3237,10 +3429,21 @@ void vsweeps(const MgGeo &G, double *u, const double *f, int sweeps, hipStream_t
     for (int s = 0; s < sweeps; s++)
       for (int ax = 0; ax < G.ndim; ax++) {
         if (G.bc[ax][0] == GMUNU_MG_PERIODIC) continue;
-        const size_t lds = 8 * (size_t)G.n[ax] * sizeof(double);
+        // 12 doubles per cell in 64 KB: lines of at most 682 cells pair
+        // two components
+        const int kind = !axisymmetric(G) ? 0 : G.n[ax] <= 682 ? 2 : 1;
+        const size_t lds = (kind == 0 ? 6 : kind == 1 ? 7 : 12) * (size_t)G.n[ax] * sizeof(double);
+        auto run = [&](auto kernel, int c) {
+          hipLaunchKernelGGL(kernel, dim3(mg_line_count(G, ax, c)), dim3(line_threads(G.n[ax])), lds, st, G, u, f, ax,
+                             c);
+        };
         for (int c = 0; c < 1 << (G.ndim - 1); c++)
-          hipLaunchKernelGGL(k_mgv_line, dim3(mg_line_count(G, ax, c)), dim3(line_threads(G.n[ax])), lds, st, G, u,
-                             f, ax, c);
+          if (kind == 2)
+            run(k_mgv_line<2, 704>, c);
+          else if (kind == 1)
+            run(k_mgv_line<1, kMaxLine>, c);
+          else  // (the general operator's registers spill under the longest lines' bound)
+            G.n[ax] <= 512 ? run(k_mgv_line<0, 512>, c) : run(k_mgv_line<0, kMaxLine>, c);
       }
     return;
   }
@@ -3307,10 +3510,13 @@ void vcorrect(gmunu_mg *m, int l, hipStream_t st) {
 void vcoarse_solve(gmunu_mg *m, hipStream_t st) {
   const MgGeo &G = m->geo[0];
   if (G.line) {
-    const size_t lds = line_coarse_lds(G, 6);
-    if (cells(G) <= 64L * NT && lds)
-      hipLaunchKernelGGL(k_mgv_line_coarse, dim3(1), dim3(kCoarseLineThreads), lds, st, G, m->vu[0], m->vf[0],
-                         m->d.coarse, line_nmax(G));
+    const LineCoarse p = line_coarse(G, 6, 12, axisymmetric(G) ? kCoarseLineThreads : 512);
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(p.threads), p.lds, st, G, m->vu[0], m->vf[0], m->d.coarse,
+                         line_nmax(G), p.lanes);
+    };
+    if (cells(G) <= 64L * NT && p.lds)
+      axisymmetric(G) ? run(k_mgv_line_coarse<2>) : run(k_mgv_line_coarse<0>);
     else
       vsweeps(G, m->vu[0], m->vf[0], m->d.coarse, st);
     return;

@@ -90,3 +90,26 @@ def test_one_vector_cycle(name, fmg):
     for c in range(3):
         a, b = mg.interior(p, g[c]), mg.interior(p, Xo[c])
         assert np.abs(a - b).max() <= 1e-12 * np.abs(Xo).max(), c
+
+
+@pytest.mark.parametrize("coord", [SPH, CYL])
+@pytest.mark.parametrize("n", [(2, 65), (64, 64), (65, 3), (682, 2), (683, 4)], ids=lambda n: "x".join(map(str, n)))
+def test_line_sweeps_where_the_kernels_change(coord, n):
+    """Lines of one and two wavefronts, the longest whose two components are
+    solved together and the first that are not, along both axes of
+    axisymmetric grids.  Two sweeps against the oracle's elimination: the
+    line systems' condition number is about n^2 in units of eps, each
+    sweep's two axes and the second component on top of the first: 4 n^2 eps,
+    at least 1e-12."""
+    lo, hi, bc = ((0.0, 0.0), (4.0, np.pi / 2), [[N, D], [N, N]]) if coord == SPH else (
+        (0.0, -1.0), (4.0, 1.5), [[N, D], [N, D]])
+    p = prob(2, coord, n, lo, hi, bc, smoother=gmu.MG_LINE)
+    rng = np.random.default_rng(13)
+    X, f = rng.uniform(-1, 1, (3,) + mg.shape(p)), rng.uniform(-1, 1, (3,) + mg.shape(p))
+    Xg = dev(X)
+    gmu.Multigrid(p).vsmooth(Xg, dev(f), sweeps=2)
+    Xo = mg.vline_smooth(p, X.copy(), f, sweeps=2)
+    tol = max(1e-12, 4.0 * max(n) ** 2 * np.finfo(float).eps)
+    g = host(Xg)
+    for c in range(3):
+        assert np.abs(mg.interior(p, g[c]) - mg.interior(p, Xo[c])).max() <= tol * np.abs(Xo).max(), c
