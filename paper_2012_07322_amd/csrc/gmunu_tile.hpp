@@ -1096,10 +1096,13 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
 // The face-adjacent ghosts of the first `axes` axes whose source is interior
 // cell (i, j, k), written from that cell's primitives pr by ghost_one's
 // rules: an outflow face copies its end cell into every layer, a periodic
-// face takes layer l from the cell l in from the other end, a reflecting
-// face from the cell l in from its own end with the axis's components of
-// velocity and field negated.  Only for axes whose faces are periodic,
-// outflow or reflecting and that hold at least ng cells (every source
+// face takes layer l from the cell l in from the other end, a reflecting,
+// axis or centre face from the cell l in from its own end with components of
+// velocity and field negated (the axis's; at the centre the first two), the
+// axis and the centre from the other side of the domain (half a turn in phi,
+// at the centre the mirror theta: each its own inverse, so the ghost's place
+// follows from the source's as the source's from the ghost's).  Only for axes
+// whose faces have such rules and that hold at least ng cells (every source
 // interior); each ghost has one source, so one thread writes it.
 __device__ __forceinline__ void face_ghosts_from(const Grid &G, double *prim, const double *pr, int i, int j, int k,
                                                  int axes) {
@@ -1109,7 +1112,7 @@ __device__ __forceinline__ void face_ghosts_from(const Grid &G, double *prim, co
     const int na = G.n[a], ng = G.g[a], ca = cell[a];
     for (int side = 0; side < 2; side++) {
       const int bc = G.bc[a][side];
-      if (bc != BC_OUTFLOW && bc != BC_PERIODIC && bc != BC_REFLECT) continue;
+      if (bc == BC_NONE) continue;
       int l0, l1;  // layers [l0, l1) of this side sourced by the cell
       if (bc == BC_OUTFLOW) {
         if (ca != (side == 0 ? 0 : na - 1)) continue;
@@ -1120,16 +1123,23 @@ __device__ __forceinline__ void face_ghosts_from(const Grid &G, double *prim, co
         if (l0 >= ng) continue;
         l1 = l0 + 1;
       }
-      const double s = bc == BC_REFLECT ? -1.0 : 1.0;
+      const bool odd = bc == BC_REFLECT || bc == BC_AXIS, centre = bc == BC_CENTER;
+      const int gj = centre && G.ndim > 1 ? G.n[1] - 1 - j : j;
+      int gk = k;
+      if ((centre || bc == BC_AXIS) && G.ndim > 2) {
+        gk = k + G.n[2] / 2;
+        gk = gk >= G.n[2] ? gk - G.n[2] : gk;
+      }
       for (int l = l0; l < l1; l++) {
         const int gi = side == 0 ? -1 - l : na + l;
-        const long cd = cell_offset(G, a == 0 ? gi : i, a == 1 ? gi : j, a == 2 ? gi : k);
+        const long cd = cell_offset(G, a == 0 ? gi : i, a == 1 ? gi : gj, a == 2 ? gi : gk);
         prim[cd] = pr[0];
         prim[4 * nv + cd] = pr[4];
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          prim[(1 + m) * nv + cd] = m == a ? s * pr[1 + m] : pr[1 + m];
-          prim[(5 + m) * nv + cd] = m == a ? s * pr[5 + m] : pr[5 + m];
+          const double s = (odd && m == a) || (centre && m < 2) ? -1.0 : 1.0;
+          prim[(1 + m) * nv + cd] = s * pr[1 + m];
+          prim[(5 + m) * nv + cd] = s * pr[5 + m];
         }
       }
     }
