@@ -13,7 +13,7 @@
 //             combination;
 //   k_c2p     per interior cell: primitive recovery with error handling,
 //             writing the face ghosts its cell is the source of on the axes
-//             whose boundary rules copy a cell of the line;
+//             whose boundary rules copy one cell;
 //   k_ghosts  per remaining face-adjacent ghost cell: boundary fill.
 // The time step is a per-cell rate reduced by wavefront shuffles to one
 // maximum per workgroup (a fixed number of grid-stride workgroups, or in
