@@ -35,9 +35,9 @@ namespace {
 
 struct BlockRec {
   Grid G;
-  double *qn, *qs, *prim;
-  const double *met;
-  uint8_t *flags;
+  double GM_GLOBAL *qn, *qs, *prim;
+  const double GM_GLOBAL *met;
+  uint8_t GM_GLOBAL *flags;
   int group;
   int active;
   // face ghosts of the first raxes axes (the first rghosts in ghost_one's
@@ -123,8 +123,10 @@ __global__ __launch_bounds__(NT, (stage_occupancy<TX, TY, TZ, ND, recon_halo(REC
     const int l = it - L.start[e];
     const int gx = (b.G.n[0] + TX - 1) / TX, gy = (b.G.n[1] + TY - 1) / TY;
     const int i0 = (l % gx) * TX, j0 = ((l / gx) % gy) * TY, k0 = (l / (gx * gy)) * TZ;
-    double *out = (MODE == 0 || !out_qn) ? b.qs : b.qn;
-    stage_tile<TX, TY, TZ, ND, MODE, REC, R>(b.G, i0, j0, k0, b.prim, b.met, b.qn, b.qs, out, dtp, ca, cb, sF);
+    double GM_GLOBAL *out = (MODE == 0 || !out_qn) ? b.qs : b.qn;
+    stage_tile<TX, TY, TZ, ND, MODE, REC, R>(b.G, i0, j0, k0, (const double *)b.prim, (const double *)b.met,
+                                             (const double *)b.qn, (const double *)b.qs, (double *)out, dtp, ca, cb,
+                                             sF);
   }
 }
 
@@ -147,10 +149,10 @@ __global__ __launch_bounds__(NT) void k_bc2p(const BlockRec *__restrict__ B, DLi
     if (!force && dts[b.group] == 0.0) continue;  // the same for the whole item
     const long t = (long)(it - L.start[e]) * NT + threadIdx.x;
     if (t < interior_count(b.G))
-      c2p_one(b.G, use_qn ? b.qn : b.qs, b.met, b.prim, b.flags, nfatal, t, gfatal ? gfatal + b.group : nullptr,
-              gfill ? b.raxes : 0);
+      c2p_one(b.G, (double *)(use_qn ? b.qn : b.qs), (const double *)b.met, (double *)b.prim, (uint8_t *)b.flags,
+              nfatal, t, gfatal ? gfatal + b.group : nullptr, gfill ? b.raxes : 0);
     if (part) {
-      const double r = t < interior_count(b.G) ? cfl_one(b.G, b.prim, b.met, t) : 0.0;
+      const double r = t < interior_count(b.G) ? cfl_one(b.G, (const double *)b.prim, (const double *)b.met, t) : 0.0;
       const double m = block_max(r);
       if (threadIdx.x == 0) part[b.cfl_start + (it - L.start[e])] = m;
     }
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(NT) void k_bprim2con(const BlockRec *__restrict__ B
     if (t < interior_count(b.G)) {
       int i, j, k;
       interior_cell(b.G, t, i, j, k);
-      prim2con_one(b.G, b.prim, b.met, b.qn, cell_offset(b.G, i, j, k));
+      prim2con_one(b.G, (const double *)b.prim, (const double *)b.met, (double *)b.qn, cell_offset(b.G, i, j, k));
     }
   }
 }
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(NT) void k_bghosts(const BlockRec *__restrict__ B, 
     const BlockRec &b = B[L.blk[e]];
     if (!force && dts[b.group] == 0.0) continue;
     const long t = (long)(it - L.start[e]) * NT + threadIdx.x + (force ? 0 : b.rghosts);
-    if (t < ghost_count(b.G)) ghost_one(b.G, b.prim, t);
+    if (t < ghost_count(b.G)) ghost_one(b.G, (double *)b.prim, t);
   }
 }
 
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(NT) void k_bcfl(const BlockRec *__restrict__ B, DLi
     e = find_entry(L.start, nent, it, e);
     const BlockRec &b = B[L.blk[e]];
     const long t = (long)(it - L.start[e]) * NT + threadIdx.x;
-    const double r = t < interior_count(b.G) ? cfl_one(b.G, b.prim, b.met, t) : 0.0;
+    const double r = t < interior_count(b.G) ? cfl_one(b.G, (const double *)b.prim, (const double *)b.met, t) : 0.0;
     const double m = block_max(r);
     if (threadIdx.x == 0) part[it] = m;
   }
@@ -702,11 +704,11 @@ int gmunu_batch_set_block(gmunu_batch *b, int slot, const gmunu_block *blk) {
   double *g = b->geo[slot];
   if (hipMemcpy(g, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) return GMUNU_EHIP;
   bind_geo(r.G, g, off);
-  r.qn = blk->q_n;
-  r.qs = blk->q_s;
-  r.prim = blk->prim;
-  r.met = blk->metric;
-  r.flags = blk->flags;
+  r.qn = (double GM_GLOBAL *)blk->q_n;
+  r.qs = (double GM_GLOBAL *)blk->q_s;
+  r.prim = (double GM_GLOBAL *)blk->prim;
+  r.met = (const double GM_GLOBAL *)blk->metric;
+  r.flags = (uint8_t GM_GLOBAL *)blk->flags;
   r.group = blk->group;
   r.active = 1;
   r.rghosts = recovery_ghosts(blk->desc, &r.raxes);

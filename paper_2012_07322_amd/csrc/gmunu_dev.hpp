@@ -28,18 +28,25 @@ enum {
 // axis-a face is fa_a * prod_{b != a} cv_b, so (F dA)_+ - (F dA)_-) / dV
 // reduces to (F fa)_+ - (F fa)_-) / cv_a.  Indices include ghosts: cell I in
 // [0, nt), face F in [0, nt] between cells F-1 and F.
+//
+// Pointers that kernels read from records in memory name the global address
+// space: through a generic one every access is a flat load, which an LDS wait
+// waits for too (a kernel's own pointer arguments are known to be global).
+#define GM_GLOBAL __attribute__((address_space(1)))
+typedef const double GM_GLOBAL *GeoTab;
+
 struct Geo {
-  const double *icv[3];  // 1 / cv per cell
-  const double *fa[3];   // face factor per face
-  const double *r2c;     // axis-0 coordinate squared at centres
-  const double *r2f;     // ... at faces
-  const double *s2c;     // sin^2 of axis-1 coordinate at centres (spherical)
-  const double *s2f;     // ... at faces
-  const double *xc0;     // axis-0 centre coordinate
-  const double *sc1, *cc1;  // sin, cos of axis-1 centre coordinate
-  const double *gA;      // per axis-0 cell: sph <G^th_r th> = <G^ph_r ph>, cyl <G^ph_R ph>
-  const double *gB;      // per axis-0 cell: sph <G^r_th th>
-  const double *gC;      // per axis-1 cell: sph <G^ph_th ph>
+  GeoTab icv[3];    // 1 / cv per cell
+  GeoTab fa[3];     // face factor per face
+  GeoTab r2c;       // axis-0 coordinate squared at centres
+  GeoTab r2f;       // ... at faces
+  GeoTab s2c;       // sin^2 of axis-1 coordinate at centres (spherical)
+  GeoTab s2f;       // ... at faces
+  GeoTab xc0;       // axis-0 centre coordinate
+  GeoTab sc1, cc1;  // sin, cos of axis-1 centre coordinate
+  GeoTab gA;        // per axis-0 cell: sph <G^th_r th> = <G^ph_r ph>, cyl <G^ph_R ph>
+  GeoTab gB;        // per axis-0 cell: sph <G^r_th th>
+  GeoTab gC;        // per axis-1 cell: sph <G^ph_th ph>
 };
 
 struct Grid {

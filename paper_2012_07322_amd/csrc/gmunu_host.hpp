@@ -198,7 +198,8 @@ inline GeoOffsets setup_grid(const gmunu_grid_desc &d, Grid &G, std::vector<doub
 }
 
 // Point G's geometry tables into the device copy of the packed table.
-inline void bind_geo(Grid &G, const double *g, const GeoOffsets &o) {
+inline void bind_geo(Grid &G, const double *tab, const GeoOffsets &o) {
+  const GeoTab g = (GeoTab)tab;
   for (int a = 0; a < 3; a++) {
     G.geo.icv[a] = g + o.icv[a];
     G.geo.fa[a] = g + o.fa[a];
