@@ -209,15 +209,18 @@ void launch_stage_t(const gmunu_ctx *ctx, const double *prim, const double *met,
 // planes 1.0 L + 1.8 (31x7 cells, MC), 1.1 L + 1.8 (15x15, MC) and 3.1 L + 3.0
 // (15x15, MP5 or PPM) times 10 us, the constant for the planes below the
 // first.  So 64^3 stays on tiles (43 against 58 us), 96^3 (132 against 140 us)
-// and larger grids march; the shape follows the grid's remainders.
+// and larger grids march; the shape follows the grid's remainders.  A stage
+// with the limiter (pp) marches with MP5 alone: its second pair of states per
+// face spills in the marched kernel (a step of 128^3 cells: MC 2.72 ms marched,
+// 1.75 on tiles; PPM 3.56 and 3.25; MP5 4.11 and 4.63).
 struct March3 {
   int zlen;
   bool wide;
 };
 
-March3 march_plan(const Grid &G) {
+March3 march_plan(const Grid &G, bool pp) {
   March3 m{0, false};
-  if (G.ndim < 3 || G.coord != CART) return m;
+  if (G.ndim < 3 || G.coord != CART || (pp && G.recon != GMUNU_RECON_MP5)) return m;
   const bool mc = G.recon == GMUNU_RECON_MC;
   auto up = [](long a, long b) { return (a + b - 1) / b; };
   const long tiles = up(G.n[0], 16) * up(G.n[1], 4) * up(G.n[2], 3);
@@ -254,7 +257,7 @@ void launch_stage(const gmunu_ctx *ctx, const double *prim, const double *met, c
   // the limiter acts on the stage's Euler step, so the RHS alone (MODE 0) is unlimited
   const int pp = MODE != 0 && ctx->G.pp;
   if constexpr (MODE != 2) {
-    const March3 m = march_plan(ctx->G);
+    const March3 m = march_plan(ctx->G, pp);
     if (m.zlen) {
       switch (m.wide * 16 + rec * 4 + lf * 2 + pp) {
 #define GM_CASE(W, TX, TY, M, L, P)                                                                          \
@@ -263,11 +266,14 @@ void launch_stage(const gmunu_ctx *ctx, const double *prim, const double *met, c
                                                        skipp, st);                                           \
     break;
 #define GM_CASES(W, TX, TY, M) \
-  GM_CASE(W, TX, TY, M, 0, 0) GM_CASE(W, TX, TY, M, 0, 1) GM_CASE(W, TX, TY, M, 1, 0) GM_CASE(W, TX, TY, M, 1, 1)
+  GM_CASE(W, TX, TY, M, 0, 0)  \
+  GM_CASE(W, TX, TY, M, 1, 0)
         GM_CASES(1, 31, 7, GMUNU_RECON_MC)
         GM_CASES(0, 15, 15, GMUNU_RECON_MC)
         GM_CASES(0, 15, 15, GMUNU_RECON_MP5)
         GM_CASES(0, 15, 15, GMUNU_RECON_PPM)
+        GM_CASE(0, 15, 15, GMUNU_RECON_MP5, 0, 1)
+        GM_CASE(0, 15, 15, GMUNU_RECON_MP5, 1, 1)
 #undef GM_CASES
 #undef GM_CASE
         default:
@@ -344,7 +350,7 @@ int rk_stage_impl(gmunu_ctx *ctx, int stage, const double *dt_dev, const double 
   // own kernel after the stage
   // (separate on grids that march: the marched stage and a recovery at the
   // copy rate are faster than a fused tile)
-  const bool fuse = prim_out != prim_in && !ctx->G.pp && !march_plan(ctx->G).zlen;
+  const bool fuse = prim_out != prim_in && !ctx->G.pp && !march_plan(ctx->G, false).zlen;
   {
     ProfScope ps(ctx, st, GMUNU_K_STAGE);
     if (fuse)

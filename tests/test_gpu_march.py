@@ -82,6 +82,9 @@ def test_steps_agree_with_a_batch_block(n, opt, beta):
             assert np.abs(a[grp] - b[grp]).max() <= 1e-12 * np.abs(b[grp]).max(), grp
 
 
-@pytest.mark.parametrize("n,axis,riemann", [((62, 49, 129), 2, 0), ((75, 45, 113), 0, 1)])
-def test_limited_stage_parity(n, axis, riemann):
-    test_gpu_pp.test_limited_stage_parity(W.CART, 3, axis, None, n, riemann)
+@pytest.mark.parametrize("axis,riemann", [(2, 0), (0, 1)])
+def test_limited_stage_parity(monkeypatch, axis, riemann):
+    """MP5 (the other reconstructions' limited stages stay on tiles)."""
+    flow = test_gpu_pp._flow
+    monkeypatch.setattr(test_gpu_pp, "_flow", lambda *a, **k: flow(*a, ng=3, recon=1, **k))
+    test_gpu_pp.test_limited_stage_parity(W.CART, 3, axis, None, (62, 57, 73), riemann)
