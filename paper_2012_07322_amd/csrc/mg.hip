@@ -1141,7 +1141,7 @@ __device__ __forceinline__ RbCell<CA> mg_rb_cell(const MgGeo &G, int i0, int j0,
 // Newton update of cell c on the plane at sm + zc (neighbour planes at zm and
 // zp; on a face of axis 2 the plane itself), zs: s - 1 of that face (0 off the
 // faces), zr: bits of a face of axis 2 whose s depends on the position, k the
-// index along axis 2.  M: the terms (0: none, 1: a (u + c), 2: general).
+// index along axis 2 (of the cell itself where the plane is a periodic image).  M: the terms (0: none, 1: a (u + c), 2: general).
 // Returns the new value.
 template <int ND, bool CA, int M, bool ROB>
 __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm, const RbCell<CA> &c, int zc, int zm,
@@ -1303,8 +1303,10 @@ __device__ __forceinline__ void mg_rb_march(const MgGeo &G, const double *__rest
       const int q = p - (2 * s - 1), m = 2 * s + 1;
       const bool zlo = face && q == 0, zhi = face && q == n2 - 1;
       const RbSrc &r = s & 1 ? qo[2 * s] : qe[2 * s];
+      // a periodic image is relaxed with its cell's position in the Robin factor
+      const int k = ROB && pz ? mg_wrap(q, n2) : q;
       w[s] = mg_rb_update<3, CA, M, ROB>(G, sm, s & 1 ? X : Y, sl[m], zlo ? sl[m] : sl[m + 1], zhi ? sl[m] : sl[m - 1],
-                                         zlo ? zs0 : zhi ? zs1 : 0.0, (zlo ? zr0 : 0u) | (zhi ? zr1 : 0u), q, r.f, r.a,
+                                         zlo ? zs0 : zhi ? zs1 : 0.0, (zlo ? zr0 : 0u) | (zhi ? zr1 : 0u), k, r.f, r.a,
                                          r.a2);
     }
 #pragma unroll
