@@ -89,7 +89,7 @@ typedef struct gmunu_mg gmunu_mg;
  * fewer than 2^31 entries per array),
  * build the level hierarchy on the current device and allocate its arrays
  * (5 arrays per coarse level, 6 with power2 != 0; 1 on the finest; the
- * vector equations add 12 per coarse level on their first use, and on
+ * vector equations add 12 per coarse level on their first solve, and on
  * Cartesian grids of two or three axes 3 per level, the finest included, for
  * the out-of-place point smoother; without memory for those the level is
  * relaxed in place).
@@ -120,9 +120,10 @@ int gmunu_mg_residual_norm(gmunu_mg *mg, double *u, const double *f, const doubl
 
 /* Building blocks (finest level unless a level is given), for checking:
  * out = L(u) on the interior with u's ghosts as given; ghost fill; `sweeps`
- * sweeps of the descriptor's smoother (red-black: on a large finest level
- * by way of the hierarchy's second u, as in the solve; line relaxation),
- * then the ghost fill; restriction
+ * sweeps of the descriptor's smoother (red-black: on a finest level of at
+ * least 32768 cells, 16 or more along axis 0, by way of the hierarchy's second
+ * u, as in the solve, so that there calls on one hierarchy must not overlap
+ * on the device; line relaxation), then the ghost fill; restriction
  * of level l into level l - 1 (volume-weighted mean of children); Kwak
  * prolongation of level l - 1 (ghosts as given) into level l. */
 int gmunu_mg_apply(gmunu_mg *mg, const double *u, const double *a, const double *a2, double *out, void *stream);
@@ -184,10 +185,11 @@ int gmunu_mg_cfc_solve(gmunu_mg *mpsi, gmunu_mg *malpha, const gmunu_grid_desc *
  * also the phi component, the spherical centre every component; ghost
  * entries of X are not read.  vapply: out = L(X) on the interior.
  * vsmooth: `sweeps` sweeps of the descriptor's smoother (the 2^ndim
- * colours, or line relaxation), then X's ghosts filled.  vsolve: as
- * gmunu_mg_solve (per-component maximum norm); X's ghosts filled on
- * return.  The first vector call allocates the coarse levels' vector
- * arrays. */
+ * colours, or line relaxation) in place, then X's ghosts filled.  vapply and
+ * vsmooth use the caller's arrays alone, so that calls on different arrays may
+ * overlap.  vsolve: as gmunu_mg_solve (per-component maximum norm); X's
+ * ghosts filled on return.  The first vector solve allocates the levels'
+ * vector arrays. */
 int gmunu_mg_vapply(gmunu_mg *mg, const double *X, double *out, void *stream);
 int gmunu_mg_vsmooth(gmunu_mg *mg, double *X, const double *f, int sweeps, void *stream);
 int gmunu_mg_vsolve(gmunu_mg *mg, double *X, const double *f, double tol, int max_cycles, int fmg, double *res_host,

@@ -4039,8 +4039,11 @@ int gmunu_mg_smooth(gmunu_mg *m, double *u, const double *f, const double *a, co
   if (sweeps < 0 || !a2_ok(m, a2)) return GMUNU_EINVAL;
   hipStream_t st = as_stream(stream);
   const MgGeo &G = m->geo[m->levels - 1];
-  second_field(m);
-  rb_sweeps_back(G, u, m->us[m->levels - 1], f, a, a2, sweeps, st);
+  // out of place only on large levels: smaller ones are relaxed on the caller's
+  // arrays alone, so that calls on different arrays may overlap
+  const bool large = cells(G) >= 32768 && G.n[0] >= 16;
+  if (large) second_field(m);
+  rb_sweeps_back(G, u, large ? m->us[m->levels - 1] : nullptr, f, a, a2, sweeps, st);
   ghosts(G, u, st);
   return launch_status();
 }
@@ -4112,13 +4115,9 @@ int gmunu_mg_vsmooth(gmunu_mg *m, double *X, const double *f, int sweeps, void *
   if (!m || !X || !f) return GMUNU_ENULL;
   if (!ok_ptr(X) || !ok_ptr(f)) return GMUNU_EALIGN;
   if (!vector_ok(m) || sweeps < 0) return GMUNU_EINVAL;
-  (void)vector_storage(m);  // without memory: in place
   const MgGeo &G = m->geo[m->levels - 1];
   hipStream_t st = as_stream(stream);
-  double *s = m->vs[m->levels - 1], *cur = X;
-  const int odd = s ? sweeps & 1 : 0;  // in place, so that X holds the result
-  vsweeps(G, X, f, odd, st);
-  vsweeps_alt(G, X, s, &cur, f, sweeps - odd, st);
+  vsweeps(G, X, f, sweeps, st);
   vghosts(G, X, st);
   return launch_status();
 }
