@@ -3389,14 +3389,22 @@ void bind(gmunu_mg *m, double *u, const double *f, const double *a, const double
   }
 }
 
+// n doubles of device memory.  A refusal is the caller's to answer: it does not
+// stay behind as the error that the next launch_status reports.
+bool try_alloc(size_t n, double **out) {
+  if (hipMalloc(out, n * sizeof(double)) == hipSuccess) return true;
+  (void)hipGetLastError();
+  *out = nullptr;
+  return false;
+}
+
 // The second field of the finest level (without memory for it the level is
 // relaxed in place).
 void second_field(gmunu_mg *m) {
   const int top = m->levels - 1;
   const MgGeo &G = m->geo[top];
-  if (m->us[top] || !rb_level(G)) return;
   double *p = nullptr;
-  if (hipMalloc(&p, (size_t)G.nt * sizeof(double)) != hipSuccess) return;
+  if (m->us[top] || !rb_level(G) || !try_alloc(G.nt, &p)) return;
   m->owned.push_back(p);
   m->us[top] = p;
 }
@@ -3597,7 +3605,7 @@ int vnorm(gmunu_mg *m, double *out, hipStream_t st) {
 
 bool alloc_zeroed(gmunu_mg *m, size_t n, double **out) {
   double *p = nullptr;
-  if (hipMalloc(&p, n * sizeof(double)) != hipSuccess) return false;
+  if (!try_alloc(n, &p)) return false;
   if (hipMemset(p, 0, n * sizeof(double)) != hipSuccess) {
     (void)hipFree(p);
     return false;
@@ -3611,9 +3619,9 @@ bool vector_storage(gmunu_mg *m) {
   if (m->vready) return true;
   for (int l = 0; l < m->levels - 1; l++) {
     const size_t n = 3 * (size_t)m->geo[l].nt;
-    if (!alloc_zeroed(m, n, &m->vu[l]) || !alloc_zeroed(m, n, &m->vf[l]) || !alloc_zeroed(m, n, &m->vr[l]) ||
-        !alloc_zeroed(m, n, &m->vuo[l]))
-      return false;
+    // (after a failure the next call goes on where this one stopped)
+    for (double **p : {&m->vu[l], &m->vf[l], &m->vr[l], &m->vuo[l]})
+      if (!*p && !alloc_zeroed(m, n, p)) return false;
   }
   // second fields of the levels above the tail; without memory for one the
   // level is relaxed in place
@@ -3882,6 +3890,8 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   for (int l = 0; l < levels; l++) level_tables(*desc, levels - 1 - l, tab, off[l], m->geo[l]);
   m->br = nullptr;
   m->xs = nullptr;
+  for (auto v : {m->vu, m->vf, m->vr, m->vuo})
+    for (int l = 0; l < kMaxLevels; l++) v[l] = nullptr;
   for (int &t : m->ttop) t = -1;
   m->tplan = nullptr;
   m->tgeo = nullptr;
@@ -3908,15 +3918,22 @@ int gmunu_mg_create(const gmunu_mg_desc *desc, gmunu_mg **out) {
   const size_t tab_at = take(tab.size()), part_at = take(kNormParts + 1 + kGateSlots), zero_at = take(0);
   size_t arr_at[kMaxLevels][7];
   for (int l = 0; l < levels; l++)
-    for (int q = 0; q < 7; q++) {
-      const bool second = rb_level(m->geo[l]);
-      if (q == 0 || (l < levels - 1 && (q < 5 || (q == 5 ? desc->power2 != 0 : second))))
+    for (int q = 0; q < 6; q++) {
+      if (q == 0 || (l < levels - 1 && (q < 5 || desc->power2 != 0)))
         arr_at[l][q] = take(m->geo[l].nt);
       else
         arr_at[l][q] = SIZE_MAX;
     }
+  const size_t without = at;
+  for (int l = 0; l < levels; l++)
+    arr_at[l][6] = l < levels - 1 && rb_level(m->geo[l]) ? take(m->geo[l].nt) : SIZE_MAX;
   double *p = nullptr;
-  bool ok = hipMalloc(&p, at * sizeof(double)) == hipSuccess;
+  bool ok = try_alloc(at, &p);
+  if (!ok && at > without) {  // without memory for the second fields their levels are relaxed in place
+    at = without;
+    for (int l = 0; l < levels; l++) arr_at[l][6] = SIZE_MAX;
+    ok = try_alloc(at, &p);
+  }
   if (ok) m->owned.push_back(p);
   m->tab = p + tab_at;
   m->part = p + part_at;
