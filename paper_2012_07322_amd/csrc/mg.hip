@@ -69,10 +69,11 @@ __device__ __forceinline__ long mg_off(const MgGeo &G, int i, int j, int k) {
   return (long)(k + G.g[2]) * G.s2 + (long)(j + G.g[1]) * G.s1 + (i + G.g[0]);
 }
 
+// w^q, q >= 0.
 __device__ __forceinline__ double mg_ipow(double w, int q) {
   double r = 1.0;
-  for (int e = q < 0 ? -q : q; e > 0; e--) r *= w;
-  return q < 0 ? 1.0 / r : r;
+  for (; q > 0; q--) r *= w;
+  return r;
 }
 
 // a (u + c)^p + a2 (u + c)^q and its derivative in u.
@@ -90,16 +91,22 @@ __device__ __forceinline__ double mg_nl_both(int power, int power2, double offse
     du = -nl * rw;
   }
   if (a2 != 0.0) {
-    if (power != -1) rw = rcp(w);
-    double t;
-    if (power2 == -7) {
-      const double r2 = rw * rw;
-      t = a2 * (r2 * r2) * (r2 * rw);
+    if (power2 > 0) {  // (without a reciprocal: u + c may be 0)
+      const double v = a2 * mg_ipow(w, power2 - 1);
+      nl += v * w;
+      du += power2 * v;
     } else {
-      t = a2 * mg_ipow(power2 < 0 ? rw : w, power2 < 0 ? -power2 : power2);
+      if (power != -1) rw = rcp(w);
+      double t;
+      if (power2 == -7) {
+        const double r2 = rw * rw;
+        t = a2 * (r2 * r2) * (r2 * rw);
+      } else {
+        t = a2 * mg_ipow(rw, -power2);
+      }
+      nl += t;
+      du += power2 * t * rw;
     }
-    nl += t;
-    du += power2 * t * rw;
   }
   return nl;
 }
