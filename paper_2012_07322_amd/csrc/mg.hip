@@ -69,6 +69,17 @@ __device__ __forceinline__ long mg_off(const MgGeo &G, int i, int j, int k) {
   return (long)(k + G.g[2]) * G.s2 + (long)(j + G.g[1]) * G.s1 + (i + G.g[0]);
 }
 
+// 1 / x with a division's results where the refinement would give NaN (0 and
+// infinity).
+__device__ __forceinline__ double mg_rcp(double x) { return __builtin_amdgcn_div_fixup(rcp(x), x, 1.0); }
+
+// sqrt(ri / rg): the ratio of two distances from the origin from their squares,
+// as one refined root of their product; 0 and infinity where the one or the
+// other is the origin.
+__device__ __forceinline__ double mg_dist_ratio(double ri, double rg) {
+  return __builtin_amdgcn_div_fixup(ri * rsq(ri * rg), rg, ri);
+}
+
 // w^q, q >= 0.
 __device__ __forceinline__ double mg_ipow(double w, int q) {
   double r = 1.0;
@@ -86,7 +97,7 @@ __device__ __forceinline__ double mg_nl_both(int power, int power2, double offse
     nl = a * w;
     du = a;
   } else if (power == -1) {
-    rw = rcp(w);
+    rw = mg_rcp(w);
     nl = a * rw;
     du = -nl * rw;
   }
@@ -96,7 +107,7 @@ __device__ __forceinline__ double mg_nl_both(int power, int power2, double offse
       nl += v * w;
       du += power2 * v;
     } else {
-      if (power != -1) rw = rcp(w);
+      if (power != -1) rw = mg_rcp(w);
       double t;
       if (power2 == -7) {
         const double r2 = rw * rw;
@@ -130,7 +141,7 @@ __device__ __forceinline__ double mg_rob(const MgGeo &G, int i, int j, int k, in
     ri += xi * xi;
     rg += xg * xg;
   }
-  return ri * rsq(ri * rg);  // sqrt(ri) / sqrt(rg)
+  return mg_dist_ratio(ri, rg);
 }
 
 // Neighbour of interior cell (i, j, k) along axis a (stride S) on the side
@@ -296,7 +307,7 @@ __global__ __launch_bounds__(NT) void k_mg_smooth(const MgGeo G, double *u, cons
   const long o = mg_off(G, i, j, k);
   double dg;
   const double Lu = mg_L<false>(G, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, i, j, k, o, &dg);
-  u[o] -= (Lu - f[o]) * rcp(dg);
+  u[o] -= (Lu - f[o]) * mg_rcp(dg);
 }
 
 // ---- Line relaxation --------------------------------------------------------
@@ -763,7 +774,7 @@ __device__ __forceinline__ MgCell mg_tail_stencil(const MgTail &T, const MgLev &
     c.fac[a] = hi ? V.fac[a][1] : V.fac[a][0];
   }
   if (ROB && (c.edge & V.rob)) {
-    // r_in / r_ghost = r_in^2 / sqrt(r_in^2 r_ghost^2)
+    // r_in / r_ghost
     double y[3], rr = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; a++) {
@@ -774,7 +785,7 @@ __device__ __forceinline__ MgCell mg_tail_stencil(const MgTail &T, const MgLev &
     for (int a = 0; a < 3; a++) {
       if (!((c.edge & V.rob) >> (2 * a) & 3)) continue;
       const double g = (c.edge >> (2 * a)) & 2 ? y[a] + V.h[a] : y[a] - V.h[a];
-      c.fac[a] = rr * rsq(rr * (rr - y[a] * y[a] + g * g));
+      c.fac[a] = mg_dist_ratio(rr, rr - y[a] * y[a] + g * g);
     }
   }
   return c;
@@ -869,7 +880,7 @@ __device__ __forceinline__ void mg_tail_sweeps(const MgTail &T, const MgLev &Vg,
           if (!on[m][s]) continue;
           double dg;
           const double L = mg_tail_L<CA, NL>(T, V, sm, c[m][s], av[m][s], a2v[m][s], dg);
-          sm[V.u + c[m][s].o] -= (L - f[m][s]) * rcp(dg);
+          sm[V.u + c[m][s].o] -= (L - f[m][s]) * mg_rcp(dg);
         }
         if (one_wave)
           wave_fence();
@@ -956,7 +967,7 @@ __device__ __forceinline__ void mg_tail_correct(const MgTail &T, const MgLev &F,
             ri += x * x;
             rg += g * g;
           }
-          fac = ri * rsq(ri * rg);
+          fac = mg_dist_ratio(ri, rg);
         }
         e = fac * e0;
       }
@@ -1099,10 +1110,10 @@ __device__ __forceinline__ double mg_fold1(const MgGeo &G, int a, int side) {
 __device__ __forceinline__ bool mg_robin(const MgGeo &G, int a, int side) {
   return G.coord != GMUNU_SPH && G.bc[a][side] == GMUNU_MG_ROBIN;
 }
-// r_in / r_ghost - 1 = r_in^2 / sqrt(r_in^2 r_ghost^2) - 1 for a cell at x
-// along the face's axis (its ghost at g), rr its squared distance.
+// r_in / r_ghost - 1 for a cell at x along the face's axis (its ghost at g), rr
+// its squared distance.
 __device__ __forceinline__ double mg_robin1(double rr, double x, double g) {
-  return rr * rsq(rr * (rr - x * x + g * g)) - 1.0;
+  return mg_dist_ratio(rr, rr - x * x + g * g) - 1.0;
 }
 
 template <int ND, int NS, bool CA>
@@ -1194,7 +1205,7 @@ __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm,
     lap -= av * (uc + G.offset);
     d -= av;
   }
-  return uc - (lap - fv) * rcp(d);
+  return uc - (lap - fv) * mg_rcp(d);
 }
 
 // f, a and a2 of one update.
