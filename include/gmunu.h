@@ -264,7 +264,8 @@ typedef struct gmunu_block {
 } gmunu_block;
 
 /* Capacities: slots, groups, and work items per list (one item = one tile of
- * at most 256 cells, or 256 cells / ghosts).  Allocates device tables.
+ * at most 256 cells, or 256 cells / ghosts; a block that marches counts as its
+ * tiles).  Allocates device tables.
  * set_block, clear_block, set_group, commit, init and autotune must not be
  * called while a step of this batch may still run on the device (a slot's
  * geometry table is rewritten in place by set_block). */
@@ -283,7 +284,9 @@ int gmunu_batch_set_group(gmunu_batch *b, int group, double t, double t_end, int
 int gmunu_batch_commit(gmunu_batch *b, void *stream);
 /* Time the compiled tile shapes per block-size class on the committed
  * blocks and keep the fastest (writes q_s of the blocks as scratch);
- * recommits.  Results do not depend on the choice. */
+ * recommits.  Results do not depend on the choice.  (Blocks of large
+ * Cartesian 3D grids, whose stage marches along z when they are advanced alone,
+ * march in a batch too, with the same bits: they take no tile shape.) */
 int gmunu_batch_autotune(gmunu_batch *b, void *stream);
 /* Pin the tile shape of the stage kernel for the class of blocks of
  * descriptor d (same ndim, n, recon and riemann), as the autotuner would:
@@ -292,6 +295,7 @@ int gmunu_batch_autotune(gmunu_batch *b, void *stream);
  * 8x5x5, 16x4x3, 8x6x4, in 2D 16x15x1, 32x7x1, 8x28x1, in 1D 255x1x1; MP5
  * and PPM 8x5x5, 16x15x1, 255x1x1.  For reproducible timings and tests
  * (a tuning control, not in the paper); results do not depend on the shape.
+ * Blocks that march (gmunu_batch_autotune) go on marching.
  * GMUNU_EINVAL for a shape not compiled for d's ndim and reconstruction. */
 int gmunu_batch_set_tile(gmunu_batch *b, const gmunu_grid_desc *d, int tx, int ty, int tz);
 /* Initial data of the given committed slots (all if slots is NULL): fill the
@@ -321,7 +325,10 @@ int gmunu_batch_times(gmunu_batch *b, double *t_host, double *dt_host, int *nste
                       void *stream);
 /* Number of committed items per list: [stage, c2p, ghosts] (ghosts of a
  * step: the ghosts that the recovery kernel writes are not counted);
- * tile variant chosen per block (out_variant[slot], -1 for empty slots). */
+ * tile variant chosen per block (out_variant[slot], 0 to 13 in the order of
+ * gmunu_batch_set_tile's shapes, 3D, 2D and 1D of MC, then of MP5 and of PPM;
+ * 14 to 17 for a block that marches, by its columns: 31x7 and 15x15 cells
+ * with MC, 15x15 with MP5, 15x15 with PPM; -1 for empty slots). */
 int gmunu_batch_info(gmunu_batch *b, long *items_out, int *out_variant);
 
 /* Kernel timing, for measurement only (not for use under graph capture).

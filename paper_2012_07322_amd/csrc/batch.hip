@@ -1,7 +1,8 @@
 // Batched stage for many independent grids ("blocks") on one GPU.
 //
 // Work is cut into uniform items: a stage item is one tile (at most 256
-// cells) of one block, a recovery / CFL item is 256 interior cells of one
+// cells) of one block, or one column and chunk of planes of a block whose grid
+// marches (march_plan), a recovery / CFL item is 256 interior cells of one
 // block, a ghost item 256 ghost cells.  Each work list is stored as a table
 // of entries, one per block (the block's slot and the index of its first
 // item); a workgroup finds the block of an item by search in that table and
@@ -12,8 +13,9 @@
 // one contiguous run of items so that the tiles of a block share that XCD's
 // L2.  Per-cell arithmetic is the single-grid path's (gmunu_tile.hpp): a
 // block advanced here is bitwise equal to the same block advanced alone,
-// whatever tile shape is used (and equal to rounding where the grid alone is
-// large enough for the marched stage, march_plan in gmunu.hip).
+// whatever tile shape is used.  (Tile and marched stage agree to rounding, so a
+// block whose grid marches alone marches here too, by the same rule and with
+// the same columns.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,6 +48,7 @@ struct BlockRec {
   long rghosts;
   int raxes;
   int cfl_start;  // the block's first item in the CFL list (set at commit)
+  int zlen;       // planes per item of the marched stage
 };
 
 // Compiled tile shapes (256 threads; each pass has at most 256 faces) and
@@ -58,14 +61,20 @@ constexpr Variant kVar[NVAR] = {{8, 8, 3, 3, 0},   {8, 5, 5, 3, 0},   {16, 4, 3,
                                 {16, 15, 1, 2, 0}, {32, 7, 1, 2, 0},  {8, 28, 1, 2, 0}, {255, 1, 1, 1, 0},
                                 {8, 5, 5, 3, 1},   {16, 15, 1, 2, 1}, {255, 1, 1, 1, 1}, {8, 5, 5, 3, 2},
                                 {16, 15, 1, 2, 2}, {255, 1, 1, 1, 2}};
-// Work lists: one per tile variant, then recovery, ghosts, CFL (entries
-// ordered by group), and the recovery / ghost lists of an init.
-// Stage lists: one per (tile variant, Riemann solver), list = variant +
-// NVAR * riemann; then recovery, ghosts, CFL (entries ordered by group), and
-// the recovery / ghost lists of an init.
-constexpr int NSL = 2 * NVAR;
+// Columns of the marched stage (the shapes that march_plan chooses from).
+struct Column {
+  int tx, ty, rec;
+};
+constexpr int NCOL = 4;
+constexpr Column kCol[NCOL] = {{31, 7, 0}, {15, 15, 0}, {15, 15, 1}, {15, 15, 2}};
+// Stage lists: one per (tile variant, Riemann solver), list = variant + NVAR *
+// riemann, and one per (column, Riemann solver), list = NTL + column + NCOL *
+// riemann; then recovery, ghosts, CFL (entries ordered by group), and the
+// recovery / ghost lists of an init.
+constexpr int NTL = 2 * NVAR, NSL = NTL + 2 * NCOL;
 enum { L_C2P = NSL, L_GH, L_CFL, L_IC2P, L_IGH, NLIST };
-static_assert(NSL <= kMaxVariants && NSL <= 32, "stage lists are counted in 32-bit masks and server counters");
+typedef unsigned long long ListMask;  // a bit per stage list
+static_assert(NTL <= kMaxVariants && NSL <= 64, "stage lists are counted in server counters and 64-bit masks");
 
 // Entry table of one list on the device: blk[e] is the slot of entry e,
 // start[e] the index of its first item (start[nent] = total), meta = {nent,
@@ -127,6 +136,32 @@ __global__ __launch_bounds__(NT, (stage_occupancy<TX, TY, TZ, ND, recon_halo(REC
     stage_tile<TX, TY, TZ, ND, MODE, REC, R>(b.G, i0, j0, k0, (const double *)b.prim, (const double *)b.met,
                                              (const double *)b.qn, (const double *)b.qs, (double *)out, dtp, ca, cb,
                                              sF);
+  }
+}
+
+// The marched stage of the blocks of a list of columns (k_stage_march's
+// body).  The slot is made uniform for the compiler, so that the block's record
+// is read by scalar loads: the marched stage has no vector registers left.
+template <int TX, int TY, int REC, int R>
+__global__ __launch_bounds__(NT, 2) void k_bstage_march(const BlockRec *__restrict__ B, DList L, const double *dts,
+                                                        double ca, double cb, int out_qn) {
+  __shared__ double sF[March<TX, TY, REC>::LDS];
+  const int nent = L.meta[0];
+  int it, end, stride;
+  xcd_range(L.meta[1], it, end, stride);
+  int e = -1;
+  for (; it < end; it += stride) {
+    e = __builtin_amdgcn_readfirstlane(find_entry(L.start, nent, it, e));
+    const BlockRec &b = B[__builtin_amdgcn_readfirstlane(L.blk[e])];
+    const double *dtp = dts + b.group;
+    if (*dtp == 0.0) continue;
+    const int l = it - __builtin_amdgcn_readfirstlane(L.start[e]);
+    const int gx = (b.G.n[0] + TX - 1) / TX, gy = (b.G.n[1] + TY - 1) / TY;
+    const int z0 = l / (gx * gy) * b.zlen, z1 = z0 + b.zlen < b.G.n[2] ? z0 + b.zlen : b.G.n[2];
+    double GM_GLOBAL *out = out_qn ? b.qn : b.qs;
+    stage_march<TX, TY, 1, REC, R, 0>(b.G, l % gx * TX, l / gx % gy * TY, z0, z1, (const double *)b.prim,
+                                      (const double *)b.met, (const double *)b.qn, (const double *)b.qs, (double *)out,
+                                      dtp, ca, cb, sF, nullptr);
   }
 }
 
@@ -237,14 +272,20 @@ __global__ __launch_bounds__(NT) void k_bcfl_finish(const int *__restrict__ gfir
   }
 }
 
-// Launch the stage kernel of list LI (variant LI % NVAR, Riemann solver
-// LI / NVAR), or of the run-time list li by recursion over the lists.
+// Launch the stage kernel of list LI, or of the run-time list li by recursion
+// over the lists (MODE 0: tiles only).
 template <int LI, int MODE>
 void launch_list(const BlockRec *B, DList L, const double *dts, double ca, double cb, int out_qn, int grid,
                  hipStream_t st) {
-  constexpr Variant v = kVar[LI % NVAR];
-  hipLaunchKernelGGL((k_bstage<v.tx, v.ty, v.tz, v.nd, MODE, v.rec, LI / NVAR>), dim3(grid), dim3(NT), 0, st, B, L,
-                     dts, ca, cb, out_qn);
+  if constexpr (LI < NTL) {
+    constexpr Variant v = kVar[LI % NVAR];
+    hipLaunchKernelGGL((k_bstage<v.tx, v.ty, v.tz, v.nd, MODE, v.rec, LI / NVAR>), dim3(grid), dim3(NT), 0, st, B, L,
+                       dts, ca, cb, out_qn);
+  } else if constexpr (MODE == 1) {
+    constexpr Column c = kCol[(LI - NTL) % NCOL];
+    hipLaunchKernelGGL((k_bstage_march<c.tx, c.ty, c.rec, (LI - NTL) / NCOL>), dim3(grid), dim3(NT), 0, st, B, L, dts,
+                       ca, cb, out_qn);
+  }
 }
 
 template <int MODE, int LI = 0>
@@ -262,6 +303,18 @@ long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
 long stage_items(const gmunu_grid_desc &d, int v) {
   return ceil_div(d.n[0], kVar[v].tx) * ceil_div(d.n[1], kVar[v].ty) * ceil_div(d.n[2], kVar[v].tz);
+}
+
+// Column of the marched stage that a grid takes (index into kCol), -1: tiles.
+int column_of(const Grid &G, int &zlen) {
+  const March3 m = march_plan(G, false);
+  zlen = m.zlen;
+  if (!zlen) return -1;
+  return G.recon == GMUNU_RECON_MP5 ? 2 : G.recon == GMUNU_RECON_PPM ? 3 : m.wide ? 0 : 1;
+}
+
+long column_items(const gmunu_grid_desc &d, int c, int zlen) {
+  return ceil_div(d.n[0], kCol[c].tx) * ceil_div(d.n[1], kCol[c].ty) * ceil_div(d.n[2], zlen);
 }
 
 // Default tile for a block before (or without) tuning.
@@ -356,7 +409,8 @@ struct gmunu_batch {
   std::vector<BlockRec> rec;
   std::vector<double *> geo;  // per-slot geometry tables, grown, never shrunk
   std::vector<size_t> geo_cap;
-  std::vector<int> var;
+  std::vector<int> var;  // tile variant
+  std::vector<int> col;  // column of the marched stage, which then takes the tiles' place (-1: tiles)
   std::map<std::tuple<int, int, int, int, int, int>, int> tuned;
   struct TimeSet {
     int group;
@@ -365,7 +419,7 @@ struct gmunu_batch {
   };
   std::vector<TimeSet> time_set;
   long counts[NLIST];
-  unsigned var_mask;
+  ListMask var_mask;
   int rec_lo, rec_hi;  // slots whose records changed since the last upload
   // device tables
   BlockRec *d_rec;
@@ -382,7 +436,7 @@ struct gmunu_batch {
   hipGraphExec_t exec;
   bool have_graph;
   double graph_cfl;
-  unsigned graph_mask;
+  ListMask graph_mask;
   unsigned int *graph_nfatal;
   int graph_steps;
   Shape graph_shape;
@@ -479,7 +533,7 @@ Shape with_headroom(const gmunu_batch *b, const Shape &w) {
 
 // Enqueue `steps` full steps (CFL and advance, stages) on st, with the stage
 // kernels of the lists in `mask` and the grids of `sh`.
-int enqueue_step(gmunu_batch *b, double cfl, unsigned int *nfatal, unsigned mask, const Shape &sh, int steps,
+int enqueue_step(gmunu_batch *b, double cfl, unsigned int *nfatal, ListMask mask, const Shape &sh, int steps,
                  hipStream_t st) {
   // RK stages (same coefficients as gmunu_rk_stage); a batch holds one
   // integrator (checked at commit)
@@ -512,7 +566,7 @@ int enqueue_step(gmunu_batch *b, double cfl, unsigned int *nfatal, unsigned mask
       }
       const int last = s == nst - 1;
       for (int l = 0; l < NSL; l++)
-        if (mask & (1u << l)) launch_list_any<1>(l, b->d_rec, b->list(l), b->d_dt, ca, cb, last, sh.st[l], st);
+        if (mask >> l & 1) launch_list_any<1>(l, b->d_rec, b->list(l), b->d_dt, ca, cb, last, sh.st[l], st);
       double *part = last && k + 1 < steps ? b->d_part : nullptr;
       hipLaunchKernelGGL(k_bc2p, dim3(sh.c2p), dim3(NT), 0, st, b->d_rec, b->list(L_C2P), b->d_dt, last, 0, nfatal,
                          b->d_gfatal, 1, part);
@@ -552,7 +606,7 @@ int batch_step_graph(gmunu_batch *b, double cfl, unsigned int *nfatal_dev, int s
   // the captured step keeps the kernels of every variant used since the
   // capture (an empty list costs one short launch), so blocks of new shapes
   // coming and going do not force a capture each time
-  const unsigned mask = b->var_mask | (b->have_graph ? b->graph_mask : 0u);
+  const ListMask mask = b->var_mask | (b->have_graph ? b->graph_mask : 0);
   const Shape want = step_shape(b);
   if (!b->have_graph || b->graph_cfl != cfl || b->graph_mask != mask || b->graph_nfatal != nfatal_dev ||
       b->graph_steps != steps || !shape_fits(b->graph_shape, want)) {
@@ -607,6 +661,7 @@ int gmunu_batch_create(int max_blocks, int max_groups, long max_items, gmunu_bat
   b->geo.assign(max_blocks, nullptr);
   b->geo_cap.assign(max_blocks, 0);
   b->var.assign(max_blocks, -1);
+  b->col.assign(max_blocks, -1);
   for (long &c : b->counts) c = 0;
   b->var_mask = 0;
   b->rec_lo = INT_MAX;
@@ -712,6 +767,7 @@ int gmunu_batch_set_block(gmunu_batch *b, int slot, const gmunu_block *blk) {
   r.group = blk->group;
   r.active = 1;
   r.rghosts = recovery_ghosts(blk->desc, &r.raxes);
+  b->col[slot] = column_of(r.G, r.zlen);
   b->rec[slot] = r;
   b->blk[slot] = *blk;
   b->used[slot] = 1;
@@ -727,6 +783,7 @@ int gmunu_batch_clear_block(gmunu_batch *b, int slot) {
   b->used[slot] = 0;
   b->rec[slot].active = 0;
   b->var[slot] = -1;
+  b->col[slot] = -1;
   b->touch(slot);
   return GMUNU_OK;
 }
@@ -766,11 +823,18 @@ int gmunu_batch_commit(gmunu_batch *b, void *stream) {
       rk = b->blk[s].desc.rk;
     }
   HList h[L_IC2P];
+  long tiles[NTL] = {};  // the capacity is in tiles, also where a block's columns are fewer
   std::vector<std::vector<int>> by_group(b->maxg);
   for (int s = 0; s < b->maxb; s++) {
     if (!b->used[s]) continue;
     const gmunu_grid_desc &d = b->blk[s].desc;
-    h[list_of(b->var[s], d)].add(s, stage_items(d, b->var[s]));
+    const int tl = list_of(b->var[s], d);
+    const long items = stage_items(d, b->var[s]);
+    tiles[tl] += items;
+    if (b->col[s] < 0)
+      h[tl].add(s, items);
+    else
+      h[NTL + b->col[s] + NCOL * (tl / NVAR)].add(s, column_items(d, b->col[s], b->rec[s].zlen));
     h[L_C2P].add(s, cell_items(d));
     h[L_GH].add(s, ghost_items(d));
     by_group[b->rec[s].group].push_back(s);
@@ -787,11 +851,13 @@ int gmunu_batch_commit(gmunu_batch *b, void *stream) {
     }
     gcount[g] = (int)(h[L_CFL].total - gfirst[g]);
   }
-  unsigned mask = 0;
-  for (int l = 0; l < L_IC2P; l++)
+  ListMask mask = 0;
+  for (long t : tiles)
+    if (t > b->maxi) return GMUNU_EINVAL;
+  for (int l = NSL; l < L_IC2P; l++)
     if (h[l].total > b->maxi) return GMUNU_EINVAL;
   for (int l = 0; l < NSL; l++)
-    if (h[l].total) mask |= 1u << l;
+    if (h[l].total) mask |= (ListMask)1 << l;
   int meta[2 * L_IC2P];
   bool ok = upload_records(b, st);
   for (int l = 0; l < L_IC2P; l++) ok = ok && upload_list(b, l, h[l], meta + 2 * l, st);
@@ -851,7 +917,7 @@ int gmunu_batch_autotune(gmunu_batch *b, void *stream) {
   hipStream_t st = as_stream(stream);
   std::map<std::tuple<int, int, int, int, int, int>, std::vector<int>> buckets;
   for (int s = 0; s < b->maxb; s++)
-    if (b->used[s]) buckets[bucket_of(b->blk[s].desc)].push_back(s);
+    if (b->used[s] && b->col[s] < 0) buckets[bucket_of(b->blk[s].desc)].push_back(s);
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return GMUNU_EHIP;
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -949,7 +1015,8 @@ int gmunu_batch_info(gmunu_batch *b, long *items_out, int *out_variant) {
     items_out[2] = b->counts[L_GH];
   }
   if (out_variant)
-    for (int s = 0; s < b->maxb; s++) out_variant[s] = b->used[s] ? b->var[s] : -1;
+    for (int s = 0; s < b->maxb; s++)
+      out_variant[s] = !b->used[s] ? -1 : b->col[s] < 0 ? b->var[s] : NVAR + b->col[s];
   return GMUNU_OK;
 }
 

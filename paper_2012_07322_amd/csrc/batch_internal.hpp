@@ -10,11 +10,11 @@
 
 namespace gm {
 
-constexpr int kMaxVariants = 32;  // bound on the number of stage work lists
+constexpr int kMaxVariants = 32;  // bound on the number of tile stage work lists
 
 struct BatchItems {
-  int variant;  // stage list the block would join (tile variant and Riemann solver)
-  long stage;   // items in that stage list
+  int variant;  // tile stage list the block would join (tile variant and Riemann solver)
+  long stage;   // items in that stage list (more than its columns, where the block's stage marches)
   long cells;   // items in the recovery and CFL lists (256 interior cells each)
   long ghosts;  // items in the ghost list
 };

@@ -202,43 +202,6 @@ void launch_stage_t(const gmunu_ctx *ctx, const double *prim, const double *met,
                      dtp, ca, cb, skipp, kij, fc);
 }
 
-// Which 3D stage kernel a grid takes: planes per workgroup of the marched
-// one, 0 for the tiles, and its column's shape.  The least of the times that
-// rounds of resident workgroups take (in 0.1 us, measured on full rounds): 512
-// tiles 14.5 us with MC, 256 tiles 26.7 us with MP5 or PPM; 512 columns of L
-// planes 1.0 L + 1.8 (31x7 cells, MC), 1.1 L + 1.8 (15x15, MC) and 3.1 L + 3.0
-// (15x15, MP5 or PPM) times 10 us, the constant for the planes below the
-// first.  So 64^3 stays on tiles (43 against 58 us), 96^3 (132 against 140 us)
-// and larger grids march; the shape follows the grid's remainders.  A stage
-// with the limiter (pp) marches with MP5 alone: its second pair of states per
-// face spills in the marched kernel (a step of 128^3 cells: MC 2.72 ms marched,
-// 1.75 on tiles; PPM 3.56 and 3.25; MP5 4.11 and 4.63).
-struct March3 {
-  int zlen;
-  bool wide;
-};
-
-March3 march_plan(const Grid &G, bool pp) {
-  March3 m{0, false};
-  if (G.ndim < 3 || G.coord != CART || (pp && G.recon != GMUNU_RECON_MP5)) return m;
-  const bool mc = G.recon == GMUNU_RECON_MC;
-  auto up = [](long a, long b) { return (a + b - 1) / b; };
-  const long tiles = up(G.n[0], 16) * up(G.n[1], 4) * up(G.n[2], 3);
-  if (tiles <= 512) return m;
-  long best = mc ? up(tiles, 512) * 145 : up(tiles, 256) * 267;
-  for (int wide = 0; wide < (mc ? 2 : 1); wide++) {
-    const long cols = wide ? up(G.n[0], 31) * up(G.n[1], 7) : up(G.n[0], 15) * up(G.n[1], 15);
-    for (int len = 4; len <= 16; len++) {
-      const long t = up(cols * up(G.n[2], len), 512) * (wide ? 100 * len + 180 : mc ? 110 * len + 180 : 310 * len + 300);
-      if (t < best) {
-        best = t;
-        m = March3{len, wide == 1};
-      }
-    }
-  }
-  return m;
-}
-
 template <int TX, int TY, int MODE, int REC, int R, int P>
 void launch_march_t(const gmunu_ctx *ctx, int zlen, const double *prim, const double *met, const double *kij,
                     const double *qn, const double *qs, double *out, const double *dtp, double ca, double cb,
