@@ -577,10 +577,13 @@ __global__ __launch_bounds__(NT) void k_mg_restrict(const MgGeo F, const MgGeo C
   coarse[mg_off(C, i, j, k)] = s / w;
 }
 
-// FAS coarse problem: f_c = L_c(u_c) + r_c, and uo_c = u_c, at cell t (r and
-// f may be the same array).
-__device__ __forceinline__ void mg_fas_one(const MgGeo &C, const double *u, const double *a, const double *a2,
-                                           const double *r, double *f, double *uo, long t) {
+// FAS coarse problem: f_c = L_c(u_c) + r_c, and uo_c = u_c.
+__global__ __launch_bounds__(NT) void k_mg_fas_rhs(const MgGeo C, const double *__restrict__ u,
+                                                   const double *__restrict__ a, const double *__restrict__ a2,
+                                                   const double *__restrict__ r, double *__restrict__ f,
+                                                   double *__restrict__ uo) {
+  const long t = (long)blockIdx.x * NT + threadIdx.x;
+  if (t >= mg_cells(C)) return;
   int i, j, k;
   mg_cell(C, t, i, j, k);
   const long o = mg_off(C, i, j, k);
@@ -588,46 +591,29 @@ __device__ __forceinline__ void mg_fas_one(const MgGeo &C, const double *u, cons
   uo[o] = u[o];
 }
 
-__global__ __launch_bounds__(NT) void k_mg_fas_rhs(const MgGeo C, const double *__restrict__ u,
-                                                   const double *__restrict__ a, const double *__restrict__ a2,
-                                                   const double *__restrict__ r, double *__restrict__ f,
-                                                   double *__restrict__ uo) {
-  const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t < mg_cells(C)) mg_fas_one(C, u, a, a2, r, f, uo, t);
-}
-
-// Coarse problem of a fine level in one pass over the coarse cells: the
-// residual f - L(u) of each child (boundary rule inline) and the
-// volume-weighted means of u and of the residual into the coarse u and r,
-// at coarse cell t.
-__device__ __forceinline__ void mg_restrict_res_one(const MgGeo &F, const MgGeo &C, const double *u, const double *f,
-                                                    const double *a, const double *a2, double *uc, double *rc,
-                                                    long t) {
-  int i, j, k;
-  mg_cell(C, t, i, j, k);
-  double su = 0.0, sr = 0.0, w = 0.0;
-  const int nch = 1 << F.ndim;
-  for (int ch = 0; ch < nch; ch++) {
-    const int fi = 2 * i + (ch & 1);
-    const int fj = F.ndim > 1 ? 2 * j + ((ch >> 1) & 1) : j;
-    const int fk = F.ndim > 2 ? 2 * k + ((ch >> 2) & 1) : k;
-    const double v = F.vol0[fi + F.g[0]] * F.vol1[fj + F.g[1]];
-    const long o = mg_off(F, fi, fj, fk);
-    su += v * u[o];
-    sr += v * (f[o] - mg_L<false>(F, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, fi, fj, fk, o, nullptr));
-    w += v;
-  }
-  const long oc = mg_off(C, i, j, k);
-  uc[oc] = su / w;
-  rc[oc] = sr / w;
-}
-
+// Coarse problem of a fine 1D level in one pass over the coarse cells: the
+// residual f - L(u) of both children (boundary rule inline) and the
+// volume-weighted means of u and of the residual into the coarse u and r.
+// (Of 2D and 3D levels: k_mg_res.)
 __global__ __launch_bounds__(NT) void k_mg_restrict_res(const MgGeo F, const MgGeo C, const double *__restrict__ u,
                                                         const double *__restrict__ f, const double *__restrict__ a,
                                                         const double *__restrict__ a2, double *__restrict__ uc,
                                                         double *__restrict__ rc) {
   const long t = (long)blockIdx.x * NT + threadIdx.x;
-  if (t < mg_cells(C)) mg_restrict_res_one(F, C, u, f, a, a2, uc, rc, t);
+  if (t >= mg_cells(C)) return;
+  double su = 0.0, sr = 0.0, w = 0.0;
+#pragma unroll
+  for (int ch = 0; ch < 2; ch++) {
+    const int i = 2 * (int)t + ch;
+    const double v = F.vol0[i + 1];
+    const long o = mg_off(F, i, 0, 0);
+    su += v * u[o];
+    sr += v * (f[o] - mg_L<false>(F, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, i, 0, 0, o, nullptr));
+    w += v;
+  }
+  const long oc = mg_off(C, (int)t, 0, 0);
+  uc[oc] = su / w;
+  rc[oc] = sr / w;
 }
 
 // u_F += P (u_C - uo_C): Kwak prolongation of the coarse correction, whose
