@@ -722,8 +722,9 @@ struct MgTail {
   MgLev lev[kTailLevels];
   int ndim, coord, power, power2, top;
   double offset;
+  int sweeps[3];                // pre, post, coarse
   int nprog[2];                 // V-cycle, FMG cycle
-  int prog[2][512];             // op + 4 level + 64 sweeps
+  int prog[2][512];             // op + 4 level + 64 (which of sweeps)
 };
 
 // u / d with the magic multiplier m of d (0: d = 1); exact for u d < 2^32.
@@ -1023,7 +1024,7 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(const MgTail *__restri
   for (int pc = 0; pc < np; pc++) {
     const int op = T.prog[use_fmg][pc], l = (op >> 2) & 15;
     if ((op & 3) == kOpSweep)
-      mg_tail_sweeps<CA, ROB, NL>(T, T.lev[l], sm, op >> 6);
+      mg_tail_sweeps<CA, ROB, NL>(T, T.lev[l], sm, T.sweeps[op >> 6]);
     else if ((op & 3) == kOpCoarse)
       mg_tail_coarse_problem<CA, ROB, NL>(T, T.lev[l], T.lev[l - 1], sm);
     else
@@ -2007,6 +2008,7 @@ struct MgvLev {
 struct MgvTail {
   MgvLev lev[kTailLevels];
   int ndim, top;
+  int sweeps[3];
   int nprog[2];
   int prog[2][512];
 };
@@ -2176,7 +2178,7 @@ __global__ __launch_bounds__(kTailThreads) void k_mgv_tail(const MgvTail *__rest
   for (int pc = 0; pc < np; pc++) {
     const int op = T.prog[use_fmg][pc], l = (op >> 2) & 15;
     if ((op & 3) == kOpSweep)
-      mgv_tail_sweeps(T, T.lev[l], sm, op >> 6);
+      mgv_tail_sweeps(T, T.lev[l], sm, T.sweeps[op >> 6]);
     else if ((op & 3) == kOpCoarse)
       mgv_tail_coarse_problem(T, T.lev[l], T.lev[l - 1], sm);
     else
@@ -3640,25 +3642,30 @@ bool vector_storage(gmunu_mg *m) {
 unsigned magic_of(int v) { return v == 1 ? 0u : (unsigned)(0x100000000ull / (unsigned)v) + 1u; }
 
 // The programs of a tail up to level `top`: a V-cycle, and the FMG cycle.
-void tail_program(const gmunu_mg_desc &d, int top, int prog[2][512], int nprog[2]) {
-  auto put = [&](int f, int op, int l, int sweeps) {
-    if (op != kOpSweep || sweeps) prog[f][nprog[f]++] = op + 4 * l + 64 * sweeps;
+template <typename Tail>
+void tail_program(const gmunu_mg_desc &d, Tail &T) {
+  enum { kPre, kPost, kCoarse };
+  T.sweeps[kPre] = d.pre;
+  T.sweeps[kPost] = d.post;
+  T.sweeps[kCoarse] = d.coarse;
+  auto put = [&](int f, int op, int l, int which) {
+    if (op != kOpSweep || T.sweeps[which]) T.prog[f][T.nprog[f]++] = op + 4 * l + 64 * which;
   };
   auto vcycle_at = [&](int f, int lt) {
     for (int l = lt; l > 0; l--) {
-      put(f, kOpSweep, l, d.pre);
+      put(f, kOpSweep, l, kPre);
       put(f, kOpCoarse, l, 0);
     }
-    put(f, kOpSweep, 0, d.coarse);
+    put(f, kOpSweep, 0, kCoarse);
     for (int l = 1; l <= lt; l++) {
       put(f, kOpCorrect, l, 0);
-      put(f, kOpSweep, l, d.post);
+      put(f, kOpSweep, l, kPost);
     }
   };
-  vcycle_at(0, top);
-  for (int l = top; l > 0; l--) put(1, kOpCoarse, l, 0);
-  put(1, kOpSweep, 0, d.coarse);
-  for (int l = 1; l <= top; l++) {
+  vcycle_at(0, T.top);
+  for (int l = T.top; l > 0; l--) put(1, kOpCoarse, l, 0);
+  put(1, kOpSweep, 0, kCoarse);
+  for (int l = 1; l <= T.top; l++) {
     put(1, kOpCorrect, l, 0);
     vcycle_at(1, l);
   }
@@ -3718,7 +3725,7 @@ int tail_plan(const gmunu_mg *m, int kind, MgTail &T) {
     V.uo = take(nc);  // used when a level above belongs to the tail too
     at = p;
   }
-  if (T.top >= 0) tail_program(d, T.top, T.prog, T.nprog);
+  if (T.top >= 0) tail_program(d, T);
   return T.top;
 }
 
@@ -3752,13 +3759,12 @@ int vtail_plan(const gmunu_mg *m, MgvTail &T) {
     at += 9 * nc;
     T.top = l;
   }
-  if (T.top >= 0) tail_program(m->d, T.top, T.prog, T.nprog);
+  if (T.top >= 0) tail_program(m->d, T);
   return T.top;
 }
 
 // The tail's plans, geometries and array pointers, uploaded once.
 bool tail_plans(gmunu_mg *m) {
-  if (m->d.pre > 1 << 20 || m->d.post > 1 << 20 || m->d.coarse > 1 << 20) return true;  // sweeps of a program word
   std::vector<MgTail> T(4);
   int top = -1;
   for (int k = 0; k < 4; k++) {

@@ -126,4 +126,20 @@ def test_operator_at_a_zero_of_a_negative_power(power2):
     assert np.array_equal(np.isnan(g), np.isnan(o)) and np.array_equal(np.isposinf(g), np.isposinf(o))
     assert np.array_equal(np.isneginf(g), np.isneginf(o)) and np.isneginf(o).any()
     ok = np.isfinite(o)
-    assert np.abs(g - o)[ok].max() <= 1e-12 * np.abs(o[ok]).max()
+    assert np.abs(g[ok] - o[ok]).max() <= 1e-12 * np.abs(o[ok]).max()
+
+
+@pytest.mark.parametrize("vector", [False, True])
+def test_very_many_sweeps(vector):
+    """A coarsest level relaxed by any number of sweeps is one launch (here to
+    convergence; as launches of their own the cycle would be two million)."""
+    p = prob(2, CART, (4, 4), (0.0, 0.0), (1.0, 1.0), [[D, N], [D, D]], coarse=(1 << 20) + 1)
+    rng = np.random.default_rng(37)
+    shp = (3,) * vector + mg.shape(p)
+    f, o = rng.uniform(-1, 1, shp), np.zeros(shp)
+    opt = dict(tol=0.0, max_cycles=1, fmg=False)
+    M, u = gmu.Multigrid(p), dev(o)
+    few = dict(p, coarse=400)  # converged as well
+    (mg.vsolve if vector else mg.solve)(few, o, f, **opt)
+    (M.vsolve if vector else M.solve)(u, dev(f), **opt)
+    close(p, u, o)
