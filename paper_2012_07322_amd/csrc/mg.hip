@@ -1192,7 +1192,8 @@ __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm,
     lap -= av * (uc + G.offset);
     d -= av;
   }
-  return uc - (lap - fv) * mg_rcp(d);
+  // (a linear equation's d is 0 or infinite only where the cell has no solution)
+  return uc - (lap - fv) * (M == 2 ? mg_rcp(d) : rcp(d));
 }
 
 // f, a and a2 of one update.
