@@ -477,21 +477,27 @@ void free_batch(gmunu_batch *b) {
   delete b;
 }
 
-// Enqueue the upload of one list's entry table (host vectors must live until
-// the stream is synchronised).
-bool upload_list(gmunu_batch *b, int l, HList &h, int *meta_host, hipStream_t st) {
+// Enqueue the upload of one list's entries and of its {entries, items} (host
+// memory must live until the stream is synchronised).
+bool upload_entries(gmunu_batch *b, int l, HList &h, int *meta_host, hipStream_t st) {
   const int nent = (int)h.blk.size();
   h.start.push_back((int)h.total);
   meta_host[0] = nent;
   meta_host[1] = (int)h.total;
-  bool ok = true;
-  if (nent) {
-    ok = hipMemcpyAsync(b->d_blk + (size_t)l * b->maxb, h.blk.data(), sizeof(int) * nent, hipMemcpyHostToDevice,
-                        st) == hipSuccess;
-    ok = ok && hipMemcpyAsync(b->d_start + (size_t)l * (b->maxb + 1), h.start.data(), sizeof(int) * (nent + 1),
-                              hipMemcpyHostToDevice, st) == hipSuccess;
-  }
-  return ok && hipMemcpyAsync(b->d_meta + 2 * l, meta_host, sizeof(int) * 2, hipMemcpyHostToDevice, st) == hipSuccess;
+  if (!nent) return true;
+  return hipMemcpyAsync(b->d_blk + (size_t)l * b->maxb, h.blk.data(), sizeof(int) * nent, hipMemcpyHostToDevice, st) ==
+             hipSuccess &&
+         hipMemcpyAsync(b->d_start + (size_t)l * (b->maxb + 1), h.start.data(), sizeof(int) * (nent + 1),
+                        hipMemcpyHostToDevice, st) == hipSuccess;
+}
+
+bool upload_meta(gmunu_batch *b, int l, int nlists, const int *meta_host, hipStream_t st) {
+  return hipMemcpyAsync(b->d_meta + 2 * l, meta_host, sizeof(int) * 2 * nlists, hipMemcpyHostToDevice, st) ==
+         hipSuccess;
+}
+
+bool upload_list(gmunu_batch *b, int l, HList &h, int *meta_host, hipStream_t st) {
+  return upload_entries(b, l, h, meta_host, st) && upload_meta(b, l, 1, meta_host, st);
 }
 
 bool upload_records(gmunu_batch *b, hipStream_t st) {
@@ -860,7 +866,8 @@ int gmunu_batch_commit(gmunu_batch *b, void *stream) {
     if (h[l].total) mask |= (ListMask)1 << l;
   int meta[2 * L_IC2P];
   bool ok = upload_records(b, st);
-  for (int l = 0; l < L_IC2P; l++) ok = ok && upload_list(b, l, h[l], meta + 2 * l, st);
+  for (int l = 0; l < L_IC2P; l++) ok = ok && upload_entries(b, l, h[l], meta + 2 * l, st);
+  ok = ok && upload_meta(b, 0, L_IC2P, meta, st);
   ok = ok && hipMemcpyAsync(b->d_gfirst, gfirst.data(), sizeof(int) * b->maxg, hipMemcpyHostToDevice, st) == hipSuccess;
   ok = ok && hipMemcpyAsync(b->d_gcount, gcount.data(), sizeof(int) * b->maxg, hipMemcpyHostToDevice, st) == hipSuccess;
   static const int zero = 0;
