@@ -235,7 +235,10 @@ inline long ghost_total(const Grid &G) {
 // and larger grids march; the shape follows the grid's remainders.  A stage
 // with the limiter (pp) marches with MP5 alone: its second pair of states per
 // face spills in the marched kernel (a step of 128^3 cells: MC 2.72 ms marched,
-// 1.75 on tiles; PPM 3.56 and 3.25; MP5 4.11 and 4.63).
+// 1.75 on tiles; PPM 3.56 and 3.25; MP5 4.11 and 4.63).  Without the limiter the
+// same step takes 1.08 ms marched and 1.22 on tiles with MC, 2.35 and 3.85 with
+// MP5, 1.69 and 2.46 with PPM; one of 80^3 cells 0.31 and 0.34, 0.70 and 0.98,
+// 0.50 and 0.63.
 struct March3 {
   int zlen;
   bool wide;

@@ -143,10 +143,10 @@ __device__ __forceinline__ int met_index(int c, int x, int y, int z) {
 
 // Reconstruction REC of the two states at a face from the cells across it
 // (MC from four cells, halo H = 2; MP5 or PPM from six, H = 3): st(v, m),
-// m = 0 .. 2H-1, is variable v of the cell H - m below the face (H-1 and H
-// are the two adjacent cells).
-template <int REC, typename St>
-__device__ __forceinline__ void face_states(const St &st, double *pl, double *pr) {
+// m = 0 .. 2H-1, is variable v of the cell H - m below the face, cell(v, 0) and
+// cell(v, 1) those of the two adjacent cells.
+template <int REC, typename St, typename Cell>
+__device__ __forceinline__ void face_states(const St &st, const Cell &cell, double *pl, double *pr) {
   if constexpr (REC == GMUNU_RECON_MC) {
 #pragma unroll
     for (int v = 0; v < NV; v++) {
@@ -171,14 +171,20 @@ __device__ __forceinline__ void face_states(const St &st, double *pl, double *pr
     if (!(pl[0] > 0.0 && pl[4] > 0.0 && pr[0] > 0.0 && pr[4] > 0.0)) {
 #pragma unroll
       for (int v = 0; v < NV; v++) {
-        pl[v] = st(v, 2);
-        pr[v] = st(v, 3);
+        pl[v] = cell(v, 0);
+        pr[v] = cell(v, 1);
       }
     }
   }
 }
 
-// Face flux times face factor through the lower face (along D) of cell
+// Face factor of the lower face (along D) of cell (i,j,k); CA: Cartesian.
+template <bool CA, int D>
+__device__ __forceinline__ double face_factor(const Grid &G, int i, int j, int k) {
+  return CA ? 1.0 : G.geo.fa[D][(D == 0 ? i : D == 1 ? j : k) + G.g[D]];
+}
+
+// Face flux times face factor fa through the lower face (along D) of cell
 // (i,j,k) from its two reconstructed states pl and pr: metric as the mean of
 // the two adjacent centres (psi, alpha, beta^1..3: ma below, mb above), HLLE
 // (R = 0) or TVDLF (R = 1); cell(v, s) is variable v of the cell below
@@ -193,13 +199,11 @@ __device__ __forceinline__ void face_states(const St &st, double *pl, double *pr
 // CA: a Cartesian grid (unit face factors and reference metric; cell widths
 // from the grid's parameters).
 template <bool CA, int D, int R, int P, typename Cell>
-__device__ __forceinline__ void face_flux(const Grid &G, const double *pl, const double *pr, const Cell &cell,
-                                          const double *ma, const double *mb, int i, int j, int k, double *Fo,
-                                          bool &nonflat, const PPBase &pb = PPBase{nullptr, 0.0}) {
-  const int cd = (D == 0 ? i : D == 1 ? j : k) + G.g[D];
+__device__ __forceinline__ void face_flux(const Grid &G, const double fa, const double *pl, const double *pr,
+                                          const Cell &cell, const double *ma, const double *mb, int i, int j, int k,
+                                          double *Fo, bool &nonflat, const PPBase &pb = PPBase{nullptr, 0.0}) {
   // zero-area faces (r = 0, theta = 0 or pi) are evaluated like any other
   // and their flux replaced by 0 at the end; no load-dependent branch here
-  const double fa = CA ? 1.0 : G.geo.fa[D][cd];
   const double psi = 0.5 * (ma[0] + mb[0]);
   const double alpha = 0.5 * (ma[1] + mb[1]);
   double beta[3];
@@ -627,10 +631,27 @@ __device__ __forceinline__ void pass_fluxes(const Grid &G, const double *S, cons
         mb[w] = met[w * G.nv + ob];
       }
     }
-    double pl[NV], pr[NV];
-    face_states<REC>([&](int v, int m) { return S[v * NP + ix[m]]; }, pl, pr);
-    face_flux<false, D, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + ix[H - 1 + m]]; }, ma, mb, ci, cj, ck, Fo,
-                       nonflat, pb);
+    double pl[NV], pr[NV], fa;
+    auto cell = [&](int v, int m) { return S[v * NP + ix[H - 1 + m]]; };
+    if constexpr (REC == GMUNU_RECON_MC || (P && ND == 3)) {
+      face_states<REC>([&](int v, int m) { return S[v * NP + ix[m]]; }, cell, pl, pr);
+      fa = face_factor<false, D>(G, ci, cj, ck);
+    } else {
+      // the stencil's address has another form than the adjacent cells', so that
+      // the compiler reads those again where PPM's fallback or the limiter takes
+      // them instead of keeping them in registers (PPM: 170 VGPRs against 198; a
+      // step of 1500^2 cells 1037 us against 1091, of 60^3 308 against 317; MP5
+      // 1348 against 1383 and 470 against 478; the limited 3D stages are 1% faster
+      // with the one form above)
+      fa = face_factor<false, D>(G, ci, cj, ck);
+      face_states<REC>(
+          [&](int v, int m) {
+            const double *Sv = S + v * NP;
+            return Sv[ix[m]];
+          },
+          cell, pl, pr);
+    }
+    face_flux<false, D, R, P>(G, fa, pl, pr, cell, ma, mb, ci, cj, ck, Fo, nonflat, pb);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; v++) Fo[v] = 0.0;
@@ -957,9 +978,9 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
           ma[w] = Sm[w * NPM + pm - 1];
           mc[w] = Sm[w * NPM + pm];
         }
-        face_states<REC>([&](int v, int m) { return S[v * NP + m]; }, pl, pr);
-        face_flux<true, 0, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + H - 1 + m]; }, ma, mc, i, j, z, Fo,
-                                 nonflat, pp);
+        auto cell = [&](int v, int m) { return S[v * NP + H - 1 + m]; };
+        face_states<REC>([&](int v, int m) { return S[v * NP + m]; }, cell, pl, pr);
+        face_flux<true, 0, R, P>(G, 1.0, pl, pr, cell, ma, mc, i, j, z, Fo, nonflat, pp);
       } else {
 #pragma unroll
         for (int v = 0; v < NV; v++) Fo[v] = 0.0;
@@ -974,9 +995,9 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
           ma[w] = Sm[w * NPM + pm - WM];
           mc[w] = Sm[w * NPM + pm];
         }
-        face_states<REC>([&](int v, int m) { return S[v * NP + m * W]; }, pl, pr);
-        face_flux<true, 1, R, P>(G, pl, pr, [&](int v, int m) { return S[v * NP + (H - 1 + m) * W]; }, ma, mc, i, j,
-                                 z, Fo, nonflat, pp);
+        auto cell = [&](int v, int m) { return S[v * NP + (H - 1 + m) * W]; };
+        face_states<REC>([&](int v, int m) { return S[v * NP + m * W]; }, cell, pl, pr);
+        face_flux<true, 1, R, P>(G, 1.0, pl, pr, cell, ma, mc, i, j, z, Fo, nonflat, pp);
 #pragma unroll
         for (int v = 0; v < NV; v++) SY[v * NT + tid] = Fo[v];
       }
@@ -1011,6 +1032,7 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
     flat = flat && !nfz;
     if (valid) {
       double pl[NV], pr[NV], Fo[NV];
+      auto cell = [&](int v, int m) { return m ? u1[v] : sF[v * NP + p]; };
       if constexpr (REC == GMUNU_RECON_MC) {
 #pragma unroll
         for (int v = 0; v < NV; v++) {
@@ -1021,11 +1043,11 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
         }
       } else {
         face_states<REC>(
-            [&](int v, int m) { return m == 2 ? sF[v * NP + p] : m == 3 ? u1[v] : uz[m < 2 ? m : m - 2][v]; }, pl, pr);
+            [&](int v, int m) { return m == 2 ? sF[v * NP + p] : m == 3 ? u1[v] : uz[m < 2 ? m : m - 2][v]; }, cell, pl,
+            pr);
       }
       bool nf = false;
-      face_flux<true, 2, R, P>(G, pl, pr, [&](int v, int m) { return m ? u1[v] : sF[v * NP + p]; }, ma, mb, i, j,
-                               z + 1, Fo, nf, pp);
+      face_flux<true, 2, R, P>(G, 1.0, pl, pr, cell, ma, mb, i, j, z + 1, Fo, nf, pp);
       if (z >= z0) {
 #pragma unroll
         for (int v = 0; v < NV; v++) {
