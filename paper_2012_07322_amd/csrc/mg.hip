@@ -387,6 +387,16 @@ __device__ __forceinline__ void mg_line_sync(bool one_wave) {
     __syncthreads();
 }
 
+// This workgroup's place in the contiguous runs of a 1D grid, one run per XCD
+// (workgroups are dispatched round-robin over the eight XCDs).  Lines along y
+// and z whose cells share cache lines are then in flight beside each other on
+// one L2: 162 us per colour of z-lines at 256^3, against 525 with neighbouring
+// lines on different XCDs, each of which fetched every cache line.
+__device__ __forceinline__ int mg_xcd_run() {
+  const int nt = gridDim.x, b = blockIdx.x, x = b % 8, q = nt / 8, r = nt % 8;
+  return x * q + (x < r ? x : r) + b / 8;
+}
+
 // Parallel cyclic reduction of NS systems of n rows at once, row m in this
 // lane's registers (a x_{m-s} + x_m + c x_{m+s} = d, s = 1; rows of lanes with
 // !on do not exist): on return d is the solution.  sm: 6 NS n doubles.
@@ -458,7 +468,7 @@ __global__ __launch_bounds__(kMaxLine) void k_mg_line(const MgGeo G, double *u, 
                                                       int ax, int colour) {
   extern __shared__ double sm[];
   int c[3];
-  if (!mg_line(G, ax, colour, blockIdx.x, c)) return;
+  if (!mg_line(G, ax, colour, mg_xcd_run(), c)) return;
   mg_line_step(G, u, f, a, a2, ax, c, true, sm, threadIdx.x, blockDim.x == kLineWave);
 }
 
@@ -1380,8 +1390,7 @@ __global__ __launch_bounds__((RbTile<ND, NS>::threads), (ND > 2 && CA && M < 2 &
   __shared__ double sm[R::P * R::ring];
   // contiguous runs of tiles (x fastest, then y, then chunks of z) per XCD
   const int gx = (G.n[0] + R::TX - 1) / R::TX, gy = (G.n[1] + R::TY - 1) / R::TY;
-  const int nt = gridDim.x, b = blockIdx.x, xc = b % 8, qn = nt / 8, rn = nt % 8;
-  const int t = xc * qn + (xc < rn ? xc : rn) + b / 8;
+  const int t = mg_xcd_run();
   const int i0 = t % gx * R::TX, j0 = t / gx % gy * R::TY;
   const int h = threadIdx.x % R::HX, y = threadIdx.x / R::HX;
   const RbCell<CA> c[2] = {mg_rb_cell<ND, NS, CA>(G, i0, j0, h, y, 0), mg_rb_cell<ND, NS, CA>(G, i0, j0, h, y, 1)};
@@ -1972,8 +1981,7 @@ __global__ __launch_bounds__(3 * kPlQuads) void k_mgv_planes(const MgGeo G, cons
   __shared__ double sm[9 * kPlCS];  // [component][plane k - 1, k, k + 1][row][x]
   // contiguous runs of tiles (x fastest, then y, then k) per XCD
   const int gx = (G.n[0] + kPlX - 1) / kPlX, gy = (G.n[1] + kPlY - 1) / kPlY;
-  const int nt = gridDim.x, b = blockIdx.x, xc = b % 8, qn = nt / 8, rn = nt % 8;
-  const int t = xc * qn + (xc < rn ? xc : rn) + b / 8;
+  const int t = mg_xcd_run();
   const int i0 = (t % gx) * kPlX, j0 = (t / gx) % gy * kPlY, k = kpar + 2 * (t / (gx * gy));
   // one component per three wavefronts (the branch is uniform in each of them,
   // and its three sides pass the same barriers)
@@ -2433,7 +2441,7 @@ __global__ __launch_bounds__(THREADS) void k_mgv_line(const MgGeo G, double *u, 
                                                       int colour) {
   extern __shared__ double sm[];
   int c[3];
-  if (!mg_line(G, ax, colour, blockIdx.x, c)) return;
+  if (!mg_line(G, ax, colour, mg_xcd_run(), c)) return;
   mgv_line_any<KIND>(G, u, f, ax, c, true, sm, threadIdx.x, blockDim.x == kLineWave);
 }
 
