@@ -79,10 +79,34 @@ def test_rhs_parity(n, opt, col, zlen):
     rng = np.random.default_rng(5)
     cells = [np.stack([rng.integers(0, m, 600) for m in n], axis=1)]
     tx, ty = COLUMNS[col]
-    at = [sorted({c for e in range(0, m + s, s) for c in (e - 1, e) if 0 <= c < m}) for m, s in zip(n, (tx, ty, zlen))]
+    edges = [range(0, m + s, s) for m, s in zip(n, (tx, ty, zlen))]
+    at = [sorted({c for e in es for c in (e - 1, e) if 0 <= c < m}) for m, es in zip(n, edges)]
     at = [a if len(a) < 8 else a[:4] + a[-4:] for a in at]
     cells.append(np.array([(i, j, k) for i in at[0] for j in at[1] for k in at[2]]))
     rhs_check(p, pr, met, cells=np.concatenate(cells).astype(np.int32))
+
+
+@pytest.mark.parametrize("n,opt", [g[:2] for g in GRIDS if g[2] != 2],
+                         ids=[i for i, g in zip(IDS, GRIDS) if g[2] != 2])
+def test_limited_stage_on_tiles_agrees(n, opt):
+    """With MC and PPM a limited stage stays on tiles where the unlimited one
+    marches.  Where every theta is 1 both are the same terms in the same order:
+    1e-12 of the variable's (or its vector's) scale."""
+    p, pr, met = make(n, opt)
+    dt = torch.full((1,), 1e-4, dtype=torch.float64, device="cuda")
+    out = []
+    for pp in (0, 1):
+        g = gmu.Grid(dict(p, pp_limiter=pp))
+        prd, metd = torch.from_numpy(pr.copy()).cuda(), torch.from_numpy(met).cuda()
+        g.fill_ghosts(prd)
+        qn = g.prim2con(prd, metd)
+        qs, q = qn.clone(), torch.zeros_like(qn)
+        g.rk_stage(1, dt, qn, qs, q, prd, prd, metd)
+        torch.cuda.synchronize()
+        out.append((W.interior(p, q.cpu().numpy()), W.interior(p, prd.cpu().numpy())))
+    for a, b in zip(*out):
+        for grp in ([0], [1, 2, 3], [4], [5, 6, 7]):
+            assert np.abs(a[grp] - b[grp]).max() <= 1e-12 * np.abs(b[grp]).max(), grp
 
 
 def test_marching_blocks_beside_tiles():
@@ -137,7 +161,8 @@ def test_capacity_is_counted_in_tiles():
 def test_served_solve_equals_alone():
     """A large 3D solve among smaller ones, of both integrators."""
     probs = []
-    for i, (kind, n, rk, ms) in enumerate([(3, 72, 3, 5), (3, 14, 3, 6), (2, 272, 3, 4), (3, 80, 2, 5), (1, 300, 2, None)]):
+    spec = [(3, 72, 3, 5), (3, 14, 3, 6), (2, 272, 3, 4), (3, 80, 2, 5), (1, 300, 2, None)]
+    for i, (kind, n, rk, ms) in enumerate(spec):
         p, pr, met, te, m0 = W.serving_problem({"kind": kind, "n": n, "seed": 60 + i, "arrival": 0.0}, "cuda")
         p["rk"] = rk
         probs.append((p, pr, met, te, m0 if ms is None else ms))
