@@ -184,7 +184,8 @@ int gmunu_cfl_dt(gmunu_ctx *ctx, const double *prim, const double *metric, doubl
  * for bit (this saves the recovery's pass over q and the metric but runs the
  * iterative root finder at the stage kernel's occupancy; large Cartesian 3D
  * grids, whose stage marches along z, recover separately in this call too,
- * as gmunu_step does on every grid).  dt is read from dt_dev.  kij: as in gmunu_rhs (nullable). */
+ * as gmunu_step does on every grid).  dt is read from dt_dev.  kij: as in
+ * gmunu_rhs (nullable). */
 int gmunu_rk_stage(gmunu_ctx *ctx, int stage, const double *dt_dev, const double *q_n, const double *q_s,
                    double *q_out, const double *prim_in, double *prim_out, const double *metric,
                    const double *kij, uint8_t *flags, unsigned int *nfatal_dev, void *stream);
@@ -247,9 +248,10 @@ int gmunu_step_static(const gmunu_grid_desc *desc, double *q_n, double *q_s, dou
  * wavefront per group for its dt and time), and per RK stage the stage
  * kernels, the recovery kernel (whose threads also write the face ghosts
  * copied from the cells they recover, on the leading axes -- x, x and y, or
- * all three -- whose faces are periodic, outflow or reflecting and that hold
- * at least ng cells) and the ghost kernel for the rest (none when the
- * recovery writes every ghost).  A group whose dt is 0 (t >= t_end, or no time set) is
+ * all three -- whose faces all have a rule that copies one interior cell (every
+ * rule but NONE; a polar axis in x or y, the centre in x) and that hold at
+ * least ng cells) and the ghost kernel for the rest (none when the recovery
+ * writes every ghost).  A group whose dt is 0 (t >= t_end, or no time set) is
  * left untouched by a step.  Every block uses its own grid description and
  * arrays exactly as a single-grid context would.
  * ------------------------------------------------------------------------ */

@@ -69,9 +69,12 @@ __device__ __forceinline__ long mg_off(const MgGeo &G, int i, int j, int k) {
   return (long)(k + G.g[2]) * G.s2 + (long)(j + G.g[1]) * G.s1 + (i + G.g[0]);
 }
 
-// 1 / x with a division's results where the refinement would give NaN (0 and
+// 1 / x; IEEE: with a division's results where the refinement gives NaN (0 and
 // infinity).
-__device__ __forceinline__ double mg_rcp(double x) { return __builtin_amdgcn_div_fixup(rcp(x), x, 1.0); }
+template <bool IEEE>
+__device__ __forceinline__ double mg_rcp(double x) {
+  return IEEE ? __builtin_amdgcn_div_fixup(rcp(x), x, 1.0) : rcp(x);
+}
 
 // sqrt(ri / rg): the ratio of two distances from the origin from their squares,
 // as one refined root of their product; 0 and infinity where the one or the
@@ -83,11 +86,17 @@ __device__ __forceinline__ double mg_dist_ratio(double ri, double rg) {
 // w^q, q >= 0.
 __device__ __forceinline__ double mg_ipow(double w, int q) {
   double r = 1.0;
+#pragma unroll 1
   for (; q > 0; q--) r *= w;
   return r;
 }
 
-// a (u + c)^p + a2 (u + c)^q and its derivative in u.
+// a (u + c)^p + a2 (u + c)^q and its derivative in u.  IEEE: at a zero of a
+// negative power the infinities of a division, for the operator itself (a
+// sweep or a norm ends in NaN or infinity there either way, and the fix-ups
+// would take 8% of the general sweep pairs: 472 us at 256^3 with Robin faces,
+// 434 without).
+template <bool IEEE = false>
 __device__ __forceinline__ double mg_nl_both(int power, int power2, double offset, double a, double a2, double u,
                                              double &du) {
   const double w = u + offset;
@@ -97,26 +106,22 @@ __device__ __forceinline__ double mg_nl_both(int power, int power2, double offse
     nl = a * w;
     du = a;
   } else if (power == -1) {
-    rw = mg_rcp(w);
+    rw = mg_rcp<IEEE>(w);
     nl = a * rw;
     du = -nl * rw;
   }
   if (a2 != 0.0) {
-    if (power2 > 0) {  // (without a reciprocal: u + c may be 0)
-      const double v = a2 * mg_ipow(w, power2 - 1);
-      nl += v * w;
-      du += power2 * v;
-    } else {
-      if (power != -1) rw = mg_rcp(w);
-      double t;
-      if (power2 == -7) {
-        const double r2 = rw * rw;
-        t = a2 * (r2 * r2) * (r2 * rw);
-      } else {
-        t = a2 * mg_ipow(rw, -power2);
-      }
+    if (power2 <= 0 && power != -1) rw = mg_rcp<IEEE>(w);
+    if (power2 == -7) {
+      const double r2 = rw * rw, t = a2 * (r2 * r2) * (r2 * rw);
       nl += t;
       du += power2 * t * rw;
+    } else {
+      // (a positive power without a reciprocal: u + c may be 0)
+      const bool pos = power2 > 0;
+      const double b = pos ? w : rw, v = a2 * mg_ipow(b, (pos ? power2 : -power2) - 1);
+      nl += v * b;
+      du += power2 * (pos ? v : v * b * b);
     }
   }
   return nl;
@@ -192,7 +197,7 @@ __device__ __forceinline__ double mg_L(const MgGeo &G, const double *__restrict_
     d -= 2.0 * w;
   }
   double du;
-  const double nl = mg_nl_both(G.power, G.power2, G.offset, av, a2v, uc, du);
+  const double nl = mg_nl_both<GH>(G.power, G.power2, G.offset, av, a2v, uc, du);
   if (dg) *dg = d - du;
   return lap - nl;
 }
@@ -307,7 +312,7 @@ __global__ __launch_bounds__(NT) void k_mg_smooth(const MgGeo G, double *u, cons
   const long o = mg_off(G, i, j, k);
   double dg;
   const double Lu = mg_L<false>(G, u, a ? a[o] : 0.0, a2 ? a2[o] : 0.0, i, j, k, o, &dg);
-  u[o] -= (Lu - f[o]) * mg_rcp(dg);
+  u[o] -= (Lu - f[o]) * rcp(dg);
 }
 
 // ---- Line relaxation --------------------------------------------------------
@@ -877,7 +882,7 @@ __device__ __forceinline__ void mg_tail_sweeps(const MgTail &T, const MgLev &Vg,
           if (!on[m][s]) continue;
           double dg;
           const double L = mg_tail_L<CA, NL>(T, V, sm, c[m][s], av[m][s], a2v[m][s], dg);
-          sm[V.u + c[m][s].o] -= (L - f[m][s]) * mg_rcp(dg);
+          sm[V.u + c[m][s].o] -= (L - f[m][s]) * rcp(dg);
         }
         if (one_wave)
           wave_fence();
@@ -1156,8 +1161,8 @@ __device__ __forceinline__ RbCell<CA> mg_rb_cell(const MgGeo &G, int i0, int j0,
 // Newton update of cell c on the plane at sm + zc (neighbour planes at zm and
 // zp; on a face of axis 2 the plane itself), zs: s - 1 of that face (0 off the
 // faces), zr: bits of a face of axis 2 whose s depends on the position, k the
-// index along axis 2 (of the cell itself where the plane is a periodic image).  M: the terms (0: none, 1: a (u + c), 2: general).
-// Returns the new value.
+// index along axis 2 (of the cell itself where the plane is a periodic image).
+// M: the terms (0: none, 1: a (u + c), 2: general).  Returns the new value.
 template <int ND, bool CA, int M, bool ROB>
 __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm, const RbCell<CA> &c, int zc, int zm,
                                                int zp, double zs, unsigned zr, int k, double fv, double av,
@@ -1190,8 +1195,8 @@ __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm,
     const double wm1 = CA ? G.vih2[1] : c.w[CA ? 0 : 2], wp1 = CA ? G.vih2[1] : c.w[CA ? 0 : 3];
     if (c.rob & 3u) cc += (c.rob & 1u ? wm0 : wp0) * mg_robin1(rr, c.x, c.rob & 1u ? c.x - G.h[0] : c.x + G.h[0]);
     if (c.rob & 12u) cc += (c.rob & 4u ? wm1 : wp1) * mg_robin1(rr, c.y, c.rob & 4u ? c.y - G.h[1] : c.y + G.h[1]);
-    if (zr & 1u) cc += zw * mg_robin1(rr, z, z - G.h[2]);
-    if (zr & 2u) cc += zw * mg_robin1(rr, z, z + G.h[2]);
+    // (a level has two planes or more: a cell lies on one z face)
+    if (zr) cc += zw * mg_robin1(rr, z, zr & 1u ? z - G.h[2] : z + G.h[2]);
   }
   lap += cc * uc;
   if constexpr (M == 2) {
@@ -1202,8 +1207,7 @@ __device__ __forceinline__ double mg_rb_update(const MgGeo &G, const double *sm,
     lap -= av * (uc + G.offset);
     d -= av;
   }
-  // (a linear equation's d is 0 or infinite only where the cell has no solution)
-  return uc - (lap - fv) * (M == 2 ? mg_rcp(d) : rcp(d));
+  return uc - (lap - fv) * rcp(d);
 }
 
 // f, a and a2 of one update.
@@ -1281,14 +1285,16 @@ __device__ __forceinline__ void mg_rb_march(const MgGeo &G, const double *__rest
   const RbCell<CA> A = flip ? c[1] : c[0], B = flip ? c[0] : c[1];
   const bool store = y >= R::H && y < R::RY - R::H && h >= NS && h < R::HX - NS;
   const bool outA = store && A.on, outB = store && B.on;
-  // po[m], sl[m]: offset in the arrays and place in LDS of plane p + 2 - m
+  // po[m], sl[m]: offset in the arrays and place in LDS of plane p + 2 - m;
+  // zi[m]: its index, a periodic image's that of its cell (for the Robin factor)
   constexpr int NP = 2 * S + 3;
   long po[NP];
-  int sl[NP], top = 2;  // the ring's next slot, for plane lo + 2
+  int sl[NP], zi[NP], top = 2;  // top: the ring's next slot, for plane lo + 2
 #pragma unroll
   for (int m = 0; m < NP; m++) {
     po[m] = plane(lo + 2 - m);
     sl[m] = (2 - m + R::ring) % R::ring * R::P;
+    if (ROB) zi[m] = pz ? mg_wrap(lo + 2 - m, n2) : lo + 2 - m;
   }
   const double zs0 = pz ? 0.0 : mg_fold1(G, 2, 0), zs1 = pz ? 0.0 : mg_fold1(G, 2, 1);
   const unsigned zr0 = ROB && mg_robin(G, 2, 0) ? 1u : 0u, zr1 = ROB && mg_robin(G, 2, 1) ? 2u : 0u;
@@ -1319,11 +1325,9 @@ __device__ __forceinline__ void mg_rb_march(const MgGeo &G, const double *__rest
       const int q = p - (2 * s - 1), m = 2 * s + 1;
       const bool zlo = face && q == 0, zhi = face && q == n2 - 1;
       const RbSrc &r = s & 1 ? qo[2 * s] : qe[2 * s];
-      // a periodic image is relaxed with its cell's position in the Robin factor
-      const int k = ROB && pz ? mg_wrap(q, n2) : q;
       w[s] = mg_rb_update<3, CA, M, ROB>(G, sm, s & 1 ? X : Y, sl[m], zlo ? sl[m] : sl[m + 1], zhi ? sl[m] : sl[m - 1],
-                                         zlo ? zs0 : zhi ? zs1 : 0.0, (zlo ? zr0 : 0u) | (zhi ? zr1 : 0u), k, r.f, r.a,
-                                         r.a2);
+                                         zlo ? zs0 : zhi ? zs1 : 0.0, (zlo ? zr0 : 0u) | (zhi ? zr1 : 0u),
+                                         ROB ? zi[m] : 0, r.f, r.a, r.a2);
     }
 #pragma unroll
     for (int s = 1; s <= S; s++) sm[sl[2 * s + 1] + (s & 1 ? X : Y).ow] = w[s];
@@ -1348,7 +1352,16 @@ __device__ __forceinline__ void mg_rb_march(const MgGeo &G, const double *__rest
       po[m] = po[m - 1];
       sl[m] = sl[m - 1];
     }
-    if (pz) {
+    if constexpr (ROB) {
+#pragma unroll
+      for (int m = NP - 1; m > 0; m--) zi[m] = zi[m - 1];
+      zi[0]++;
+      if (pz && zi[0] == n2) zi[0] = 0;
+      if (pz)
+        po[0] = zi[0] ? po[1] + G.s2 : G.s2;
+      else if (p + 3 < n2)
+        po[0] = po[1] + G.s2;
+    } else if (pz) {
       zn = zn + 1 == n2 ? 0 : zn + 1;
       po[0] = zn ? po[1] + G.s2 : G.s2;
     } else if (p + 3 < n2) {
