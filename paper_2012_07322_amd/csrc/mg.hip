@@ -1059,8 +1059,8 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(const MgTail *__restri
 // 2 NS independent updates per thread; the planes of u, f, a and a2 are loaded
 // two steps ahead, f, a and a2 once (kept in registers over the pipeline).  As launches per colour a pair of
 // sweeps moves 96 bytes per cell (u four times, f and a in half lines); here
-// 32.  Measured on 256^3 cells with a (u + c): 194 us per pair of sweeps against
-// 480 as four launches (38 B per cell with the halo in flight: 3.3 TB/s; two
+// 32.  Measured on 256^3 cells with a (u + c): 200 us per pair of sweeps against
+// 474 as four launches (38 B per cell with the halo in flight: 3.2 TB/s; two
 // wavefronts per SIMD in each of two workgroups, VALU and LDS about half busy
 // each).  What it took: f and a fetched once (fetched per colour in half lines
 // they missed the L2: 285 us), no branch in a step (the loads' waits cannot
@@ -1842,10 +1842,10 @@ __global__ __launch_bounds__(NT) void k_mgv_smooth2(const MgGeo G, double *u, co
 // the launches and reads each plane from memory about once per parity.  Bound
 // by the staged bytes (1.5 times the tile for its halo) on large levels and
 // by one workgroup's chain of load, four colours and store on small ones:
-// 50 us per launch at 128^3 (3.4 TB/s of staged, f and written bytes) and
-// 7.4 us from 16^3 to 32^3 cells, against 33 and 7 us for each of the twice
-// as many launches of a colour pair (one thread per quad and all components:
-// 64 and 13 us).
+// 51 us per launch at 128^3 (3.4 TB/s of staged, f and written bytes, 2.0 of
+// those needed) and 7.5 us from 16^3 to 32^3 cells, against 30 and 7 us for each
+// of the twice as many launches of a colour pair (one thread per quad and all
+// components: 64 and 13 us).
 constexpr int kPlX = 32, kPlY = 16;           // tile
 constexpr int kPlRow = kPlX + 8, kPlRows = kPlY + 3;  // staged: x -3 .. TX + 3 (row of 40), y -1 .. TY + 1
 constexpr int kPlQx = kPlX / 2 + 3, kPlQy = kPlY / 2 + 1;
