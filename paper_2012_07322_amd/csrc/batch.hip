@@ -159,7 +159,7 @@ __global__ __launch_bounds__(NT, 2) void k_bstage_march(const BlockRec *__restri
     const int gx = (b.G.n[0] + TX - 1) / TX, gy = (b.G.n[1] + TY - 1) / TY;
     const int z0 = l / (gx * gy) * b.zlen, z1 = z0 + b.zlen < b.G.n[2] ? z0 + b.zlen : b.G.n[2];
     double GM_GLOBAL *out = out_qn ? b.qn : b.qs;
-    stage_march<TX, TY, 1, REC, R, 0>(b.G, l % gx * TX, l / gx % gy * TY, z0, z1, (const double *)b.prim,
+    stage_march<TX, TY, 1, REC, R, 0>(b.G, l % gx, l / gx % gy * TY, z0, z1, (const double *)b.prim,
                                       (const double *)b.met, (const double *)b.qn, (const double *)b.qs, (double *)out,
                                       dtp, ca, cb, sF, nullptr);
   }

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(NT, 2) void k_stage_march(
   int bx, by, bz;
   xcd_tile(G, TX, TY, zlen, bx, by, bz);
   const int z0 = bz * zlen, z1 = z0 + zlen < G.n[2] ? z0 + zlen : G.n[2];
-  stage_march<TX, TY, MODE, REC, R, P>(G, bx * TX, by * TY, z0, z1, prim, met, qn, qs, out, dtp, ca, cb, sF, kij);
+  stage_march<TX, TY, MODE, REC, R, P>(G, bx, by * TY, z0, z1, prim, met, qn, qs, out, dtp, ca, cb, sF, kij);
 }
 
 // Recovery of one interior cell per thread.  gaxes: also write the face

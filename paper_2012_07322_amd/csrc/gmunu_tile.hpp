@@ -862,6 +862,12 @@ __device__ __forceinline__ void stage_tile(const Grid &G, int i0, int j0, int k0
 // of three left one workgroup per CU).  Loads cost about 36 clocks of the
 // memory pipe each in rows of 16 lanes, so rows of 32 (31x7 cells) beat rows
 // of 16 (15x15) by 6% although fewer of their faces are shared.
+//
+// Columns of 15x15 share the cells along x out evenly: two workgroups with one
+// or two cells each on one CU hold each other up (full columns and a remainder,
+// 17x104x88: PPM 140 us, MP5 125, against 85 and 89 evenly; 31x97x156: 200 and
+// 176 against 148 and 153; MC, 46x226x45: 74 against 67).  Those of 31x7 stay
+// full: even ones lose 0.4% on average and 0.6% of a solve at 256^3.
 template <int TX, int TY, int REC>
 struct March {
   static_assert((TX + 1) * (TY + 1) == NT, "one lower x-face and y-face per thread");
@@ -881,7 +887,7 @@ __device__ __forceinline__ double lane_next(double x) {
 }
 
 template <int TX, int TY, int MODE, int REC, int R, int P>
-__device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z0, int z1,
+__device__ __forceinline__ void stage_march(const Grid &G, int bx, int j0, int z0, int z1,
                                             const double *__restrict__ prim, const double *__restrict__ met,
                                             const double *qn, const double *qs, double *out,
                                             const double *__restrict__ dtp, double ca, double cb, double *sF,
@@ -892,12 +898,19 @@ __device__ __forceinline__ void stage_march(const Grid &G, int i0, int j0, int z
   constexpr int H = M::H, W = M::W, NP = M::NP, WM = M::WM, NPM = M::NPM;
   const int tid = threadIdx.x, tx = tid % (TX + 1), ty = tid / (TX + 1);
   constexpr int NC = M::NC;
+  // the cells [i0, i1) along x of column bx (above)
+  int i0 = bx * TX, i1 = G.n[0];
+  if constexpr (TX < 31) {
+    const int gx = (i1 + TX - 1) / TX, wx = i1 / gx, rx = i1 - wx * gx;
+    i0 = bx * wx + (bx < rx ? bx : rx);
+    i1 = i0 + wx + (bx < rx);
+  }
   const int i = i0 + tx, j = j0 + ty, own_at = tx < TX && ty < TY ? tx + TX * ty : 0;
   // SY: the plane's y-fluxes; SZ, SL: the cell's lower z-flux and, with MC,
   // its half slope along z (own cells only, so no barrier)
   double *Sm = sF + NV * NP, *SY = Sm + 5 * NPM, *SZ = SY + NV * NT + own_at, *SL = SZ + NV * NC;
-  const bool own = tx < TX && ty < TY, valid = own && i < G.n[0] && j < G.n[1];
-  const bool fx = ty < TY && i <= G.n[0] && j < G.n[1], fy = tx < TX && i < G.n[0] && j <= G.n[1];
+  const bool own = tx < TX && ty < TY, valid = own && i < i1 && j < G.n[1];
+  const bool fx = ty < TY && i <= i1 && j < G.n[1], fy = tx < TX && i < i1 && j <= G.n[1];
   // loads past the array (ragged columns) repeat its last cell; no valid
   // face or cell uses them
   const int ic = i < G.n[0] + G.g[0] ? i : G.n[0] + G.g[0] - 1, jc = j < G.n[1] + G.g[1] ? j : G.n[1] + G.g[1] - 1;

@@ -88,3 +88,15 @@ def test_limited_stage_parity(monkeypatch, axis, riemann):
     flow = test_gpu_pp._flow
     monkeypatch.setattr(test_gpu_pp, "_flow", lambda *a, **k: flow(*a, ng=3, recon=1, **k))
     test_gpu_pp.test_limited_stage_parity(W.CART, 3, axis, None, (62, 57, 73), riemann)
+
+
+@pytest.mark.parametrize("n,opt", [
+    ((17, 104, 88), dict(recon=2, ng=3)),               # columns of 9 and 8 cells
+    ((32, 97, 101), dict(recon=1, riemann=1, ng=3)),    # 11, 11 and 10
+    ((46, 226, 45), {}),                                # 12, 12, 11 and 11
+    ((15, 210, 88), dict(recon=2, ng=3)),               # one column
+], ids=["17", "32", "46", "15"])
+def test_rhs_parity_of_columns_shared_out_along_x(n, opt):
+    p, pr, met = _grid(n, opt, 0.05)
+    cells = [(i, j, k) for i in range(n[0]) for j in (0, 14, 15, n[1] - 1) for k in (0, 3, 4, n[2] - 1)]
+    rhs_check(p, pr, met, cells=np.array(cells, dtype=np.int32))
